@@ -3,137 +3,242 @@
 // each other; columns are strictly sequential (each column's code depends on every earlier
 // column's error), so the work is cut as the listing cuts it:
 //
-//   gptq_block_kernel    : walks the B columns of a block for the rows of one wave: Algorithm 1
-//                          on the current weight (mq_quant_core.h: the operations of the
-//                          whole-matrix kernel, the 256 candidates spread over the 4, 16 or 64
-//                          lanes that share a row), the error averaged over R and divided by
-//                          U[j,j], rank-1 update of the block's remaining columns, which live in
-//                          LDS;
+//   gptq_block_kernel    : walks the B columns of a block for the rows of one workgroup: Algorithm 1
+//                          on the current weight (mq_code_search.h), the error averaged over R and
+//                          divided by U[j,j], rank-1 update of the block's remaining columns;
 //   gptq_trailing_kernel : W[:, i+B:] -= E @ U[i:i+B, i+B:], eight rows x four columns per lane.
 //
 // Every rounding decides later codes, so the arithmetic is fixed: binary32, each operation
 // rounded on its own (no contraction), the error sum over r ascending as ((w - D_r1) + (w - D_r2))
 // + ..., then / |R|, then / U[j,j]; an update is w = w - (E * U[j,k]); the update of the rest is
 // applied as the same rank-1 terms in ascending j, so results do not depend on B.
-#include "mq_quant_core.h"
+#include "mq_code_search.h"
+#include "mq_internal.h"
+#include "mq_static_for.h"
 
 namespace mq {
 
 constexpr int kGptqMaxBlock = 128;
 constexpr int kTrailRows = 8;
+constexpr int kRowLanes = 16;  // lanes that share a row: one DPP row
 
-__device__ __forceinline__ float slice_value(uint32_t q, int r) {
-    const int sh = kC - r;
-    uint32_t t = sh ? (q + (1u << (sh - 1))) >> sh : q;
-    const uint32_t top = (1u << r) - 1;
-    t = t < top ? t : top;
-    return (float)(t << sh);
+// ---- one column decision, spread over the lanes of a row
+// Entries of the candidate list (mq_code_search.h), two lanes each: U (its second lane: width 7's candidate, where
+// the variant has it), U - 1, and one per coarser width; the second lane of an entry evaluates the code below, so that
+// the minimum also shows whether a smaller code has the same E.
+constexpr int gptq_coarse(uint32_t mask) { return popc8(mask & 0x3Fu); }  // widths 1 .. 6
+constexpr int gptq_lanes(uint32_t mask) {  // lanes that hold different entries: a power of two, 4 .. 16
+    const int need = 2 * (2 + gptq_coarse(mask));
+    return need <= 4 ? 4 : need <= 8 ? 8 : 16;
 }
-
-// Lexicographic minimum of (E, q) over groups of LPR consecutive lanes, result in every lane of the
-// group.  E >= 0, so the float order is the order of the bit patterns; equal E -> smaller q.
-template <int CTRL> __device__ __forceinline__ void argmin_dpp(float &e, uint32_t &q) {
-    const float oe = __builtin_bit_cast(
-        float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, e), CTRL, 0xf, 0xf, false));
-    const uint32_t oq = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)q, CTRL, 0xf, 0xf, false);
-    const bool take = oe < e || (oe == e && oq < q);
-    e = take ? oe : e;
-    q = take ? oq : q;
-}
-__device__ __forceinline__ void argmin_xor(float &e, uint32_t &q, int mask) {
-    const float oe = __shfl_xor(e, mask);
-    const uint32_t oq = (uint32_t)__shfl_xor((int)q, mask);
-    const bool take = oe < e || (oe == e && oq < q);
-    e = take ? oe : e;
-    q = take ? oq : q;
-}
-template <int LPR> __device__ __forceinline__ void row_argmin(float &e, uint32_t &q) {
-    static_assert(LPR == 4 || LPR == 16 || LPR == 64, "lanes per row");
-    argmin_dpp<0xB1>(e, q);  // quad_perm [1,0,3,2]
-    argmin_dpp<0x4E>(e, q);  // quad_perm [2,3,0,1]
-    if constexpr (LPR >= 16) {
-        argmin_dpp<0x141>(e, q);  // row_half_mirror: the two quads of each 8 lanes
-        argmin_dpp<0x140>(e, q);  // row_mirror: the two halves of each 16 lanes
+// What a lane evaluates, given U:  T - (T < U ? left : 0) - second, T = roundup(U, step) - half
+struct LaneCandidate {
+    int step, half, left, second;
+    bool seven;  // width 7's candidate: reported as a second one where it is below U (its own lower neighbour is not listed)
+};
+template <uint32_t MASK> __device__ __forceinline__ LaneCandidate lane_candidate(int part) {
+    const int e = (part & (gptq_lanes(MASK) - 1)) >> 1, second = part & 1;
+    LaneCandidate c{1, 0, 0, 0, false};  // U
+    if (e == 0 && second && (MASK & 0x40u)) c = {2, 1, 1, 0, true};
+    if (e == 1) c = {1, 1, 0, second, false};  // U - 1
+    int k = 2;
+#pragma unroll
+    for (int r = 1; r <= 6; ++r) {
+        if (!((MASK >> (r - 1)) & 1)) continue;
+        const int step = 1 << (kC - r);
+        if (e == k) c = {step, step / 2, 1, second, false};
+        ++k;
     }
-    if constexpr (LPR == 64) {
-        argmin_xor(e, q, 16);
-        argmin_xor(e, q, 32);
-    }
+    return c;
 }
 
-// One wave per workgroup; LPR lanes share a row: each evaluates 256 / LPR of the candidates, and
-// they split the columns of the in-block update.  The block's current weights live in LDS as
-// [column][row of the wave]; the values of U a lane needs for column j+1 are fetched into
-// registers while column j is being decided.
-template <uint32_t MASK, int LPR>
-__global__ __launch_bounds__(64) void gptq_block_kernel(const float *__restrict__ W, int64_t ldw, int64_t N, int64_t i0,
-                                                        int B, const float *__restrict__ U, int64_t ldu,
-                                                        const _Float16 *__restrict__ scales,
-                                                        const _Float16 *__restrict__ zeros, int64_t G,
-                                                        const QuantLambda lam, float n_widths,
-                                                        uint8_t *__restrict__ Q, int64_t ldq, float *__restrict__ E) {
+template <int CTRL> __device__ __forceinline__ uint32_t dpp_u(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL> __device__ __forceinline__ float dpp_f(float v) {
+    return __builtin_bit_cast(float, dpp_u<CTRL>(__builtin_bit_cast(uint32_t, v)));
+}
+// lexicographic minimum of (E's bits, key) with err carried along, over two lanes
+template <int CTRL> __device__ __forceinline__ void argmin_step(uint32_t &E, uint32_t &key, float &err) {
+    const float oerr = dpp_f<CTRL>(err);
+    const uint32_t oE = dpp_u<CTRL>(E), okey = dpp_u<CTRL>(key);
+    const bool take = (((uint64_t)oE << 32) | okey) < (((uint64_t)E << 32) | key);
+    E = take ? oE : E;
+    key = take ? okey : key;
+    err = take ? oerr : err;
+}
+
+// E(q), the sum (w - D_r1) + (w - D_r2) + ... over the widths with lambda_r != 0 (r ascending), and the residual of
+// width 8.  ALL: every width of MASK has lambda_r != 0.
+template <uint32_t MASK, bool ALL, int R = 1>
+__device__ __forceinline__ void code_terms(uint32_t q, float w, float s, float z, const QuantLambda &lam, float &E,
+                                           float &acc, bool &any, float &e) {
 #pragma clang fp contract(off)
-    constexpr int RPW = 64 / LPR, CPL = 256 / LPR, CNT = kGptqMaxBlock / LPR;
-    __shared__ float wl[kGptqMaxBlock * RPW];
-    const int lane = threadIdx.x;
-    const int rl = lane / LPR, part = lane % LPR;
-    const int64_t n = (int64_t)blockIdx.x * RPW + rl;
+    if constexpr (R <= kC) {
+        if constexpr ((MASK >> (R - 1)) & 1) {
+            constexpr bool first = (MASK & ((1u << (R - 1)) - 1)) == 0;
+            e = code_residual(slice_of<R>(q), w, s, z);
+            const float p = e * e;
+            const float term = lam.v[R - 1] * p;
+            E = first ? term : E + term;
+            if constexpr (ALL) {
+                acc = first ? e : acc + e;
+            } else if (lam.v[R - 1] != 0.f) {
+                acc = any ? acc + e : e;
+                any = true;
+            }
+        }
+        code_terms<MASK, ALL, R + 1>(q, w, s, z, lam, E, acc, any, e);
+    }
+}
+// a / b, correctly rounded, y = RN(1 / b): the first correction brings a * y (off by up to two units in the last place) to
+// within one unit, from where one more exact remainder rounds correctly (Markstein's theorem; no over- or underflow on the
+// way while |a| and |b| are within 2^-60 .. 2^60, or a = 0).  Half as long a chain as the general division.
+__device__ __forceinline__ float divide_by(float a, float b, float y) {
+    const float q0 = a * y;
+    const float q1 = __builtin_fmaf(__builtin_fmaf(-b, q0, a), y, q0);
+    return __builtin_fmaf(__builtin_fmaf(-b, q1, a), y, q1);
+}
+__device__ __forceinline__ bool divides_plainly(float a) {  // from below; normal weights are small enough
+    return (a == 0.f) | (__builtin_fabsf(a) > 0x1p-50f);
+}
+
+// The 128 columns of a block for the rows of one workgroup.  What bounds it is the serial chain of the column steps
+// (a column's code decides the next column's weight), so a step is made short and everything else is kept off it:
+//   * kRowLanes lanes share a row and evaluate the handful of candidates that can win (mq_code_search.h) side by side, each with
+//     the error it would propagate (two correctly rounded divisions, beside the chain that compares the E); DPP steps pick the winner;
+//   * the block's weights live in registers, column k = 16 c + part in register c of lane `part` (after 16 columns the
+//     registers move up by one), so that a column's weight reaches its row in one DPP broadcast;
+//   * the block of U lives in LDS; 16 steps are straight-line code, so that its values are read well ahead.
+// 4096 rows x 4096 columns, R = {3,4,8}: 44 us a block = 0.34 us a step, of about 145 instructions of one wave per SIMD (160 us
+// with all 256 candidates over 64 lanes and the weights in LDS); the whole loop 6.85 -> 2.98 ms.
+template <uint32_t MASK, bool ALL>
+__global__ __launch_bounds__(1024) void gptq_block_kernel(const float *__restrict__ W, int64_t ldw, int64_t N, int64_t i0,
+                                                          int B, const float *__restrict__ U, int64_t ldu,
+                                                          const _Float16 *__restrict__ scales,
+                                                          const _Float16 *__restrict__ zeros, int64_t G,
+                                                          const QuantLambda lam, float n_widths,
+                                                          uint8_t *__restrict__ Q, int64_t ldq, float *__restrict__ E) {
+#pragma clang fp contract(off)
+    constexpr int NC = kGptqMaxBlock / kRowLanes;
+    __shared__ float ul[kGptqMaxBlock * kGptqMaxBlock + kGptqMaxBlock];  // row j of the block at ul + 128 j; padding
+    __shared__ float rd[kGptqMaxBlock];                  // 1 / U[j,j]
+    const int tid = threadIdx.x;
+    const int part = tid & (kRowLanes - 1);
+    const int64_t n = (int64_t)blockIdx.x * (blockDim.x / kRowLanes) + tid / kRowLanes;
     const bool valid = n < N;
-    const int64_t nr = valid ? n : N - 1;  // idle lanes shadow the last row and store nothing
-    for (int k = part; k < B; k += LPR) wl[k * RPW + rl] = W[nr * ldw + i0 + k];
+    const int64_t nr = valid ? n : N - 1;  // idle rows shadow the last one and store nothing
+    float wreg[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) wreg[c] = c * kRowLanes < B ? W[nr * ldw + i0 + c * kRowLanes + part] : 0.f;
     // a block never straddles a group (B divides the group size and blocks start at multiples of B)
     const int64_t g = i0 / kGroup;
     const float s = (float)scales[nr * G + g];
     const float z = (float)zeros[nr * G + g];
-    // this lane's pieces of row j of U: the diagonal and columns j + 1 + part + c * LPR (clamped into the block)
-    float un[CNT], ujj_n;
-    auto fetch_u = [&](int j) {
-        const float *urow = U + (i0 + j) * ldu + i0;
-        ujj_n = urow[j];
+    const float inv_s = 1.f / s, z1 = z + 1.f;
+    const LaneCandidate lc = lane_candidate<MASK>(part);
+    const bool grid_ok = code_grid_normal(s, z);
+    const bool runs = !ALL && lam.v[kC - 1] == 0.f;  // uniform
+    const float nw = ALL ? (float)popc8(MASK) : n_widths, inv_nw = 1.f / nw;
+    {
+        // the upper triangle, columns fastest (B is 16, 32, 64 or 128: a thread keeps its column), sixteen loads in flight
+        // per thread; what lies below it is not read from U, and not used
+        const int col = tid & (B - 1), row0 = tid / B, rows = blockDim.x / B;
+        const float *src = U + i0 * ldu + i0 + col;
+        for (int j0 = row0; j0 < B; j0 += 16 * rows) {
+            float v[16];
 #pragma unroll
-        for (int c = 0; c < CNT; ++c) {
-            const int k = j + 1 + part + c * LPR;
-            un[c] = urow[k < B ? k : B - 1];
-        }
-    };
-    fetch_u(0);
-    __syncthreads();
-    for (int j = 0; j < B; ++j) {
-        float uc[CNT];
+            for (int i = 0; i < 16; ++i) {
+                const int j = j0 + i * rows;
+                v[i] = src[(int64_t)(j < col ? j : col) * ldu];
+            }
 #pragma unroll
-        for (int c = 0; c < CNT; ++c) uc[c] = un[c];
-        const float ujj = ujj_n;
-        if (j + 1 < B) fetch_u(j + 1);
-        const float w = wl[j * RPW + rl];
-        float best;
-        uint32_t q;
-        choose_codes_part<MASK, CPL>(w, s, z, lam, (uint32_t)(part * CPL), best, q);
-        row_argmin<LPR>(best, q);
-        float acc = 0.f;
-        bool first = true;
-#pragma unroll
-        for (int r = 1; r <= kC; ++r) {
-            if (lam.v[r - 1] != 0.f) {  // uniform: R is the set of widths with a non-zero lambda
-                const float t = slice_value(q, r) - z;
-                const float D = s * t;
-                const float d = w - D;
-                acc = first ? d : acc + d;
-                first = false;
+            for (int i = 0; i < 16; ++i) {
+                const int j = j0 + i * rows;
+                if (j < B) ul[j * kGptqMaxBlock + col] = v[i];
             }
         }
-        const float err = (acc / n_widths) / ujj;
-        if (valid && part == 0) {
-            Q[n * ldq + i0 + j] = (uint8_t)q;
-            E[n * B + j] = err;
+    }
+    bool u_ok = true;
+    if (tid < B) {
+        const float ujj = U[(i0 + tid) * ldu + i0 + tid];
+        rd[tid] = 1.f / ujj;
+        u_ok = __builtin_fabsf(ujj) > 0x1p-50f && __builtin_fabsf(ujj) < 0x1p50f;
+    }
+    const bool fast_ok = grid_ok & (__syncthreads_and(u_ok) != 0);
+    for (int c0 = 0; c0 < B; c0 += kRowLanes) {
+        // 16 columns, one of them per lane of a row in wreg[0]; register k holds this lane's column 16 k further on.
+        // (Past the block's end the registers hold nothing of use, and the rows of U run into the padding.)
+        const float *urows = ul + c0 * kGptqMaxBlock + c0;
+        float keep_err = 0.f;
+        uint32_t keep_q = 0;
+        float ur[2][NC], ujj[2], rjj[2];  // row jj of these 16 columns and row jj + 1, on its way
+        int u_off = part;
+        auto fetch_u = [&](auto jc) {
+            constexpr int jj = jc;
+            // (opaque: else the rows of all 16 steps are read at once, into more registers than there are)
+            asm volatile("" : "+v"(u_off));
+            ujj[jj % 2] = urows[jj * kGptqMaxBlock + jj];
+            rjj[jj % 2] = rd[c0 + jj];
+#pragma unroll
+            for (int k = 0; k < NC; ++k) ur[jj % 2][k] = urows[jj * kGptqMaxBlock + k * kRowLanes + u_off];
+        };
+        fetch_u(IntC<0>{});
+        static_for<kRowLanes>([&](auto jc) {
+#pragma clang fp contract(off)
+            constexpr int jj = jc;
+            if constexpr (jj + 1 < kRowLanes) fetch_u(IntC<jj + 1>{});
+            const float w = dpp_f<0x150 + jj>(wreg[0]);  // row_newbcast: column jj's weight, to all lanes of the row
+            const int Uc = code_estimate(w, inv_s, z1);
+            const int T = ((Uc + lc.step - 1) & -lc.step) - lc.half;
+            int q = T - (T < Uc ? lc.left : 0);
+            int second = lc.second;
+            if constexpr (!ALL) {
+                if (runs) q = code_run_start(code_clamp(q), lam);
+                if (lc.seven) second = T < Uc ? 1 : 0;
+                q = code_clamp(lc.seven ? q : q - second);
+            } else {
+                q = code_clamp(q - second);
+            }
+            float E = 0.f, acc = 0.f, e8 = 0.f;
+            bool any = false;
+            code_terms<MASK, ALL>((uint32_t)q, w, s, z, lam, E, acc, any, e8);
+            float err = divide_by(divide_by(acc, nw, inv_nw), ujj[jj % 2], rjj[jj % 2]);
+            // key: the code; bit 1: the search does not hold here (such a lane wins);
+            // bit 0: look closer if this one wins
+            const bool bad = !(fast_ok & code_weight_normal(w) & code_side_ok(q, Uc, e8));
+            uint32_t Eb = code_bits(E), key = 4u * (uint32_t)q + (((second != 0) | !divides_plainly(acc)) ? 1u : 0u);
+            asm volatile("" : "+v"(Eb), "+v"(key));  // selects below, no branch
+            Eb = bad ? 0u : Eb;
+            key = bad ? 2u : key;
+            constexpr int NL = gptq_lanes(MASK);
+            argmin_step<0xB1>(Eb, key, err);  // quad_perm [1,0,3,2]
+            argmin_step<0x4E>(Eb, key, err);  // quad_perm [2,3,0,1]
+            if constexpr (NL >= 8) argmin_step<0x141>(Eb, key, err);   // row_half_mirror: the quads of 8 lanes
+            if constexpr (NL >= 16) argmin_step<0x140>(Eb, key, err);  // row_mirror: the halves of 16 lanes
+            uint32_t qw = key >> 2;
+            if (__builtin_expect((key & 3u) != 0, 0)) {  // rare; the lanes of a row take it together
+                qw = code_search_closely<MASK>(Uc, w, s, z, lam);
+                float e2 = 0.f, a2 = 0.f, e8_2;
+                bool any2 = false;
+                code_terms<MASK, ALL>(qw, w, s, z, lam, e2, a2, any2, e8_2);
+                err = (a2 / nw) / ujj[jj % 2];
+            }
+            keep_q = part == jj ? qw : keep_q;
+            keep_err = part == jj ? err : keep_err;
+#pragma unroll
+            for (int k = 0; k < NC; ++k) {
+                const float p = err * ur[jj % 2][k];
+                wreg[k] = wreg[k] - p;
+                asm volatile("" : "+v"(wreg[k]));  // here: put off to the end of the 16 steps it would hold their rows of U in registers
+            }
+        });
+        if (valid) {
+            Q[n * ldq + i0 + c0 + part] = (uint8_t)keep_q;
+            E[n * B + c0 + part] = keep_err;
         }
 #pragma unroll
-        for (int c = 0; c < CNT; ++c) {
-            const int k = j + 1 + part + c * LPR;
-            if (k < B) {
-                const float p = err * uc[c];
-                wl[k * RPW + rl] = wl[k * RPW + rl] - p;
-            }
-        }
+        for (int k = 0; k + 1 < NC; ++k) wreg[k] = wreg[k + 1];
     }
 }
 
@@ -210,39 +315,23 @@ __global__ __launch_bounds__(64) void gptq_trailing_kernel(float *__restrict__ W
     }
 }
 
-template <uint32_t MASK, int LPR>
-static hipError_t launch_gptq_block(const float *W, int64_t ldw, int64_t N, int64_t i0, int B, const float *U, int64_t ldu,
-                              const _Float16 *scales, const _Float16 *zeros, int64_t G, const QuantLambda &lam,
-                              float n_widths, uint8_t *Q, int64_t ldq, float *E, hipStream_t s) {
-    constexpr int RPW = 64 / LPR;
-    return launch((gptq_block_kernel<MASK, LPR>), dim3((unsigned)((N + RPW - 1) / RPW)), dim3(64), 0, s, W, ldw, N, i0, B, U,
-                  ldu, scales, zeros, G, lam, n_widths, Q, ldq, E);
-}
+// Waves per workgroup (four rows each): four while the rows then make at most two workgroups per compute unit (64 KB of
+// LDS each), more beyond, so that the rows stay resident at one time up to 32768 of them.
+inline int gptq_block_waves(int64_t N) { return N <= 8192 ? 4 : N <= 16384 ? 8 : 16; }
 
-// Lanes per row: the column steps are a dependent chain, so the chip is filled by spreading each
-// step's rows x candidates over the waves: the most lanes per row that keep the launch within about
-// four waves per SIMD (measured on 4096 and 11008 rows: 64 lanes 7.0 / 14.2 ms, 16 lanes 8.1 / 11.5 ms,
-// 4 lanes 15.6 / 17.9 ms for 4096 columns).
-inline int gptq_lanes_per_row(int64_t N) { return N > 16384 ? 4 : N > 4096 ? 16 : 64; }
-
-template <uint32_t MASK>
+template <uint32_t MASK, bool ALL>
 static hipError_t launch_gptq_mask(float *W, int64_t ldw, int64_t N, int64_t K, const float *U, int64_t ldu,
                                    const _Float16 *scales, const _Float16 *zeros, const QuantLambda &lam, float n_widths,
                                    int B, uint8_t *Q, int64_t ldq, float *E, hipStream_t s) {
     const int64_t G = K / kGroup;
     if (((K + 63) / 64) * ((N + kTrailRows - 1) / kTrailRows) > (int64_t)0x7fffffff) return hipErrorInvalidValue;
-    const int lpr = gptq_lanes_per_row(N);
+    const int waves = gptq_block_waves(N), rows = waves * (64 / kRowLanes);
     // B, K and the block starts are multiples of 16, so only the strides and base addresses decide
     const bool vec4 = ldw % 4 == 0 && ldu % 4 == 0 && (reinterpret_cast<uintptr_t>(W) & 15) == 0 &&
                       (reinterpret_cast<uintptr_t>(U) & 15) == 0;
     for (int64_t i0 = 0; i0 < K; i0 += B) {
-        hipError_t e;
-        if (lpr == 4)
-            e = launch_gptq_block<MASK, 4>(W, ldw, N, i0, B, U, ldu, scales, zeros, G, lam, n_widths, Q, ldq, E, s);
-        else if (lpr == 16)
-            e = launch_gptq_block<MASK, 16>(W, ldw, N, i0, B, U, ldu, scales, zeros, G, lam, n_widths, Q, ldq, E, s);
-        else
-            e = launch_gptq_block<MASK, 64>(W, ldw, N, i0, B, U, ldu, scales, zeros, G, lam, n_widths, Q, ldq, E, s);
+        hipError_t e = launch((gptq_block_kernel<MASK, ALL>), dim3((unsigned)((N + rows - 1) / rows)), dim3(64 * waves), 0, s,
+                              W, ldw, N, i0, B, U, ldu, scales, zeros, G, lam, n_widths, Q, ldq, E);
         if (e != hipSuccess) return e;
         const int64_t c0 = i0 + B, ncols = K - c0;
         if (ncols > 0) {
@@ -277,11 +366,14 @@ hipError_t launch_gptq(float *W, int64_t ldw, int64_t N, int64_t K, const float 
     }
     const float n_widths = (float)nw;
     switch (quant_variant_mask(need)) {
-        case 0x80u: return launch_gptq_mask<0x80u>(W, ldw, N, K, U, ldu, scales, zeros, lam, n_widths, B, Q, ldq, E, s);
-        case 0x8Cu: return launch_gptq_mask<0x8Cu>(W, ldw, N, K, U, ldu, scales, zeros, lam, n_widths, B, Q, ldq, E, s);
-        case 0xAEu: return launch_gptq_mask<0xAEu>(W, ldw, N, K, U, ldu, scales, zeros, lam, n_widths, B, Q, ldq, E, s);
+        case 0x80u: return launch_gptq_mask<0x80u, true>(W, ldw, N, K, U, ldu, scales, zeros, lam, n_widths, B, Q, ldq, E, s);
+        case 0x8Cu:
+            if (need == 0x8Cu)
+                return launch_gptq_mask<0x8Cu, true>(W, ldw, N, K, U, ldu, scales, zeros, lam, n_widths, B, Q, ldq, E, s);
+            return launch_gptq_mask<0x8Cu, false>(W, ldw, N, K, U, ldu, scales, zeros, lam, n_widths, B, Q, ldq, E, s);
+        case 0xAEu: return launch_gptq_mask<0xAEu, false>(W, ldw, N, K, U, ldu, scales, zeros, lam, n_widths, B, Q, ldq, E, s);
     }
-    return launch_gptq_mask<0xFFu>(W, ldw, N, K, U, ldu, scales, zeros, lam, n_widths, B, Q, ldq, E, s);
+    return launch_gptq_mask<0xFFu, false>(W, ldw, N, K, U, ldu, scales, zeros, lam, n_widths, B, Q, ldq, E, s);
 }
 
 }  // namespace mq

@@ -1,0 +1,58 @@
+"""The column loop where its decisions leave the common path: ties between codes, sets of widths without 8 (whole runs of codes
+have the same error), estimates that are off, weights far outside the grid, and the row counts at which its launch shape changes."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle  # noqa: E402
+import paper_2602_03537_amd as mq  # noqa: E402
+from paper_2602_03537_amd import synth  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+def _factor(K, seed):
+    rng = np.random.default_rng(seed)
+    U = np.triu(rng.uniform(-0.2, 0.2, (K, K)), 1) / np.sqrt(K) + np.diag(rng.uniform(0.5, 2.0, K))
+    return U.astype(np.float32)
+
+
+@pytest.mark.parametrize("widths", [(3, 4, 8), (3, 4), (4,), (7,), (6, 7), (1, 2, 8), (2, 3, 4, 6, 8), (1, 2, 3, 4, 5, 6, 7, 8)])
+@pytest.mark.parametrize("exact_factor", [False, True])
+def test_column_loop_ties_runs_and_outliers(widths, exact_factor):
+    N, K, block = 37, 256, 64
+    rng = np.random.default_rng([101, len(widths)])
+    s = np.full((N, K // 128), 2.0 ** -6, np.float16)
+    z = rng.integers(0, 256, (N, K // 128)).astype(np.float16)
+    s[5], z[5] = 0.013, 101.5
+    s[6] = 0.0                                   # every code has the same error
+    s[7] = -s[7]                                 # the search's assumptions do not hold
+    zk, sk = np.repeat(z, 128, 1).astype(np.float32), np.repeat(np.abs(s), 128, 1).astype(np.float32)
+    W = ((rng.integers(-80, 680, (N, K)) / 2 - zk) * sk).astype(np.float32)   # codes, ties and beyond the grid
+    W[8] *= 1e6
+    W[9, ::3] = 1e16                             # above the search's bound
+    W[10] = 0.0
+    # identity: no error reaches a later column, so the ties stay ties
+    U = np.eye(K, dtype=np.float32) if exact_factor else _factor(K, 102)
+    lam = [1.0] * len(widths)
+    with np.errstate(over="ignore", invalid="ignore"):
+        ref, _ = oracle.matgptq_quantize(W, U, s, z, 8, widths, lam, 128, block, np.float32)
+    got = mq.mq_matgptq_quantize(dev(W.copy()), dev(U), dev(s), dev(z), widths, lam, block=block).cpu().numpy()
+    assert np.array_equal(got, ref), np.argwhere(got != ref)[:5]
+
+
+@pytest.mark.parametrize("N", [1, 15, 17, 8192, 8193, 16385])   # rows of a workgroup; 4, 8 and 16 waves
+def test_column_loop_row_counts(N):
+    K = 128
+    W = synth.make_weights(N, K, [103, N])
+    _, s, z = synth.quantize_parent(W)
+    U = _factor(K, 104)
+    rows = np.unique(np.clip([0, 1, 14, 15, 16, N // 2, N - 2, N - 1], 0, N - 1))
+    q = mq.mq_matgptq_quantize(dev(W.copy()), dev(U), dev(s), dev(z), (3, 4, 8), (1.0, 1.0, 1.0)).cpu().numpy()
+    ref, _ = oracle.matgptq_quantize(W[rows], U, s[rows], z[rows], 8, (3, 4, 8), (1.0, 1.0, 1.0), 128, 128, np.float32)
+    assert np.array_equal(q[rows], ref)
