@@ -279,14 +279,17 @@ mq_status run_single(const mq_layer &l, int64_t M, void *ws, size_t ws_bytes, mq
     p.slot_floats = slot_floats(M);
     p.n_jobs = (use_wide(M) ? wide_chunks_padded(M) : p.single.CB) * p.single.G;
     hipError_t e;
-    if (!use_mfma(M) && (l.flags & MQ_X_BF16)) {
+    // bf16 activations: the low-latency launch of packed layers converts them itself
+    const bool rb = !use_mfma(M) && linear_rb_fits(p.single, part_b);
+    if (!use_mfma(M) && (l.flags & MQ_X_BF16) && (!rb || l.from_parent)) {
         if (launch_xcvt(p, (hipStream_t)stream) != hipSuccess) return MQ_ERR_HIP;
+        p.single.x_bf16 = nullptr;  // from here on x is the fp16 copy
     }
     if (use_wide(M))
         e = launch_stack_wide(p, p.single.cost, (hipStream_t)stream);
     else if (use_mfma(M))
         e = launch_stack_mfma(p, p.single.cost, (hipStream_t)stream);
-    else if (linear_rb_fits(p.single, part_b))
+    else if (rb)
         e = launch_linear_rb(p.single, p.part, p.cnt, (hipStream_t)stream);
     else
         e = launch_stack(p, p.single.cost, l.from_parent != 0, (hipStream_t)stream);

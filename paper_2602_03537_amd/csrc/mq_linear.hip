@@ -80,7 +80,8 @@ __device__ __forceinline__ uint32_t slice_pair(uint32_t v, const SliceConst &c) 
 
 // xlds: this wave's M x 64 dwords of LDS (kXLds only)
 // SL (R == 8 only): the tile holds the unsliced parent; its codes are sliced to L.rs bits first.
-template <int R, int M, int XP, bool SL = false>
+// XB: the activations are bf16 and are converted here
+template <int R, int M, int XP, bool SL = false, bool XB = false>
 __device__ __forceinline__ void tile_math(const TileRegs<R, M> &t, const LayerDesc &L, int g, int lane,
                                           uint32_t *xlds, float (&yacc)[M]) {
     using T = Layout<R>;
@@ -91,7 +92,7 @@ __device__ __forceinline__ void tile_math(const TileRegs<R, M> &t, const LayerDe
     cptr32 xs[M];
 #pragma unroll
     for (int m = 0; m < M; ++m) {
-        const uint32_t xl = t.xl[m];
+        const uint32_t xl = XB ? bf16_pair_to_f16_pair(t.xl[m]) : t.xl[m];
         xg[m] = wave_sum(dot2(xl, 0x3C003C00u, 0.f));  // (1.0, 1.0)
         if constexpr (XP == kXLds)
             xlds[m * 64 + lane] = xl;
@@ -289,7 +290,7 @@ __device__ __forceinline__ void chain_announce(const ChainCtl &c, int stage, int
 }
 
 // CH: the launch is a chained small stack (`chain` is live); the plain variants carry none of its code
-template <int R, int M, int XP, bool SL, bool CH = false>
+template <int R, int M, int XP, bool SL, bool CH = false, bool XB = false>
 __device__ __forceinline__ void linear_rb_body(const LayerDesc &L, const int KS, const int blk, const int slot0,
                                                float *part, int32_t *cnt, float (*red)[M][64], uint32_t *xlds_all,
                                                const ChainCtl chain = ChainCtl{nullptr, nullptr, 0}) {
@@ -326,7 +327,7 @@ __device__ __forceinline__ void linear_rb_body(const LayerDesc &L, const int KS,
                 have_nxt = false;
                 load_tile_x<R, M>(nxt, L, g2, lane, waits);
             }
-            tile_math<R, M, XP, SL>(cur, L, g, lane, xlds, yacc);
+            tile_math<R, M, XP, SL, XB>(cur, L, g, lane, xlds, yacc);
             if (g2 >= g_hi) break;
             cur = nxt;
             g = g2;
@@ -386,11 +387,15 @@ __device__ __forceinline__ void linear_rb_body(const LayerDesc &L, const int KS,
         if (row < L.N) store_y(L.y, (size_t)m * L.N + row, tot[m], L.flags);
 }
 
-template <int R, int M, int XP, bool SL = false>
+// XB: L.x holds bf16 activations.  One variant per kind, because this launch is short: converting ahead of it costs a launch of
+// its own (13003 x 5120, r = 6, M = 3: 22.4 us with it, 20.3 without), while in the tile loop it is four operations per lane,
+// row and tile.
+template <int R, int M, int XP, bool SL = false, bool XB = false>
 __global__ __launch_bounds__(1024) void linear_rb_kernel(const LayerDesc L, const int KS, float *part, int32_t *cnt) {
+    static_assert(XP == kXLds || !XB, "converted activations reach the lanes through LDS");
     __shared__ float red[16][M][64];
     __shared__ __attribute__((aligned(16))) uint32_t xlds_all[XP == kXLds ? 16 * M * 64 : 4];
-    linear_rb_body<R, M, XP, SL>(L, KS, (int)blockIdx.x, 0, part, cnt, red, xlds_all);
+    linear_rb_body<R, M, XP, SL, false, XB>(L, KS, (int)blockIdx.x, 0, part, cnt, red, xlds_all);
 }
 
 // Launch shape, from sweeps on Llama-2-7B / Llama-3-70B shapes (cold weights): enough K slices
@@ -422,6 +427,15 @@ template <int R, int M, bool SL = false>
 static hipError_t launch_linear_rb_rm(const LayerDesc &L, float *part, int32_t *cnt, hipStream_t s) {
     const int KS = pick_k_slices(L);
     const int W = rb_waves(L, KS);
+    if constexpr (!SL) {
+        if (L.x_bf16) {
+            LayerDesc B = L;
+            B.x = static_cast<const _Float16 *>(L.x_bf16);
+            return launch((linear_rb_kernel<R, M, kXLds, false, true>), dim3((unsigned)(L.RB * KS)), dim3(64 * W), 0, s, B, KS, part,
+                          cnt);
+        }
+    }
+    if (L.x_bf16) return hipErrorInvalidValue;  // from the parent: converted ahead of the launch by the caller
     return launch((linear_rb_kernel<R, M, kXLds, SL>), dim3((unsigned)(L.RB * KS)), dim3(64 * W), 0, s, L, KS, part,
                        cnt);
 }
@@ -648,7 +662,8 @@ hipError_t launch_stack(StackParams p, int max_cost, bool from_parent, hipStream
 }
 
 // ------------------------------------------------------------------ bf16 activations for the kernels above
-// One small launch ahead of a vector-ALU launch whose layers (some of them) take bf16 activations: those layers'
+// One small launch ahead of a vector-ALU launch whose layers (some of them) take bf16 activations (but for a single packed
+// layer in the low-latency shape, which converts them itself): those layers'
 // activations (LayerDesc::x_bf16) go, as fp16, to the room the workspace keeps for them, which is where LayerDesc::x of
 // such a layer points: the kernels above never see the difference.  32 workgroups per layer; layers without the flag
 // return at once.
