@@ -573,9 +573,9 @@ FP32_VECTOR_PEAK_TFLOPS = 157.3
 # Vector lanes x clock without the factor two of a fused multiply-add: 256 CUs x 4 SIMDs x 32 lanes per clock x 2.4 GHz.
 # Algorithm 1's arithmetic is defined operation by operation (nothing may be fused), so this is its ceiling.
 VECTOR_LANE_OPS_PEAK_T = 78.6
-# Vector instructions the compiled quant_kernel<140, 4> executes per candidate and weight (R = {3,4,8}), from the
-# SQ_INSTS_VALU counter in profiles/quant_kernel_alg1_llama2_7b_shapes.txt (8117 per wave of 64 lanes x 4 weights x 256
-# candidates); the definition counts 19 per candidate and weight, the kernel skips recomputing terms that cannot change.
+# Vector instructions the compiled quant_kernel<140, 4> executes per weight (R = {3,4,8}): the SQ_INSTS_VALU counter in
+# profiles/quant_kernel_alg1_llama2_7b_shapes.txt.  The definition counts 19 per candidate and weight; the kernel evaluates the
+# few candidates that can win.
 QUANT_PROFILE = os.path.join(ROOT, "profiles", "quant_kernel_alg1_llama2_7b_shapes.txt")
 
 
@@ -583,9 +583,9 @@ def quant_executed_ops_per_weight():
     """executed vector lane-operations per weight of quant_kernel<140, 4>, read from the committed counter summary"""
     import re
     try:
-        m = re.search(r"R = \{3,4,8\}, \d+ weights: SQ_INSTS_VALU [^\n]*?= ([0-9.]+) per candidate and lane \(4 weights\)",
+        m = re.search(r"R = \{3,4,8\}, \d+ weights: SQ_INSTS_VALU [^\n]*?= ([0-9.]+) per weight",
                       open(QUANT_PROFILE).read())
-        return float(m.group(1)) * 256.0 / 4.0
+        return float(m.group(1))
     except (OSError, AttributeError, ValueError):
         return None
 
@@ -628,8 +628,8 @@ def bench_quant(args, mq, synth, torch, np, dev):
     out["dtype"] = "f32"
     out["table"] = table
     # roofline: the lane-operations the kernel EXECUTES per second against the unfused vector peak (the brute force as
-    # defined counts 19 operations per candidate and weight; the kernel executes fewer because a width's term is only
-    # recomputed where its slice changes, so the counted-work rate would exceed the peak and say nothing)
+    # defined counts 19 operations per candidate and weight and 256 candidates; the kernel evaluates |R| + 1 of them, so the
+    # counted-work rate would exceed the peak many times over and say nothing)
     ops_w = quant_executed_ops_per_weight()
     counted = tot_fl / tot_t / 1e12
     if ops_w is not None:
@@ -861,7 +861,7 @@ def bench_gptq(args, mq, synth, torch, np, dev):
     out["table"] = table
     ach = tot_fl / tot_t / 1e12
     # a dependent chain over the columns: the figure is low by construction (latency per column step x K)
-    out["roofline"] = {"bound": "alu", "kernel": "mq::gptq_block_kernel<140, LPR> + mq::gptq_trailing_kernel<true>",
+    out["roofline"] = {"bound": "alu", "kernel": "mq::gptq_block_kernel<140, true> + mq::gptq_trailing_kernel<true>",
                        "achieved": round(ach, 1), "peak": FP32_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
                        "frac": round(ach / FP32_VECTOR_PEAK_TFLOPS, 4), "avg_launch_us": None,
                        "algorithmic_flops_per_launch": None, "traffic": None}

@@ -194,8 +194,8 @@ mq_status mq_pack_meta(const mq_half *scales, const mq_half *zeros, int64_t N, i
  * Algorithm 1 ("Generate Q^c given weight matrix W, target bit-widths R, and weights
  * lambda_R"; Section 3.2, item 2): for every weight the parent code q in 0 .. 2^c - 1 with the
  * smallest  E(q) = sum_{r in R} lambda_r * (w - scale * (S(q, r) - zero))^2,  S = Eq. 1, scale
- * and zero-offset those of the master width for every r.  All 256 candidates are evaluated (the
- * paper's brute force).  The argmin is taken in IEEE binary32 with every operation rounded on its
+ * and zero-offset those of the master width for every r.  The result is that of evaluating all 256
+ * candidates (the paper's brute force).  The argmin is taken in IEEE binary32 with every operation rounded on its
  * own, in the order  t = S - zero; D = scale * t; e = w - D; p = e * e; E = E + lambda_r * p,
  * r ascending; the smallest q wins a tie.  Inputs must be finite.
  *   W       : device, fp32, N rows of `ncols` weights, row stride ldw elements: columns

@@ -141,7 +141,7 @@ def _stream(stream=None):
         import torch
         C = torch._C
         if hasattr(C, "_cuda_getCurrentRawStream") and hasattr(C, "_cuda_getDevice"):
-                # the handle without the Stream object around it: a 4096 x 4096 mq_linear call takes 5.6 instead of 7.9 us
+            # the handle without the Stream object around it: a 4096 x 4096 mq_linear call takes 5.6 instead of 7.9 us
             torch.cuda.current_stream()  # initialises the device as it always did
             _raw_stream = lambda: C._cuda_getCurrentRawStream(C._cuda_getDevice())  # noqa: E731
         else:
