@@ -132,6 +132,15 @@ def lib():
 _raw_stream = None
 
 
+def _forget_raw_stream():
+    global _raw_stream
+    _raw_stream = None
+
+
+# A child forked after torch has initialised the device may not use it: it asks torch again, which refuses.
+os.register_at_fork(after_in_child=_forget_raw_stream)
+
+
 def _stream(stream=None):
     """The stream's handle (the current one of the current device if none is given)."""
     global _raw_stream
