@@ -128,13 +128,15 @@ __global__ __launch_bounds__(1024) void gptq_block_kernel(const float *__restric
     const int64_t n = (int64_t)blockIdx.x * (blockDim.x / kRowLanes) + tid / kRowLanes;
     const bool valid = n < N;
     const int64_t nr = valid ? n : N - 1;  // idle rows shadow the last one and store nothing
-    float wreg[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) wreg[c] = c * kRowLanes < B ? W[nr * ldw + i0 + c * kRowLanes + part] : 0.f;
     // a block never straddles a group (B divides the group size and blocks start at multiples of B)
     const int64_t g = i0 / kGroup;
-    const float s = (float)scales[nr * G + g];
+    const float s_in = (float)scales[nr * G + g];
     const float z = (float)zeros[nr * G + g];
+    // a row with a negative scale is decided on its negative: every step of the loop is odd in (w, scale)
+    const float sign = code_sign(s_in), s = s_in * sign;
+    float wreg[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) wreg[c] = c * kRowLanes < B ? W[nr * ldw + i0 + c * kRowLanes + part] * sign : 0.f;
     const float inv_s = 1.f / s, z1 = z + 1.f;
     const LaneCandidate lc = lane_candidate<MASK>(part);
     const bool grid_ok = code_grid_normal(s, z);
@@ -235,7 +237,7 @@ __global__ __launch_bounds__(1024) void gptq_block_kernel(const float *__restric
         });
         if (valid) {
             Q[n * ldq + i0 + c0 + part] = (uint8_t)keep_q;
-            E[n * B + c0 + part] = keep_err;
+            E[n * B + c0 + part] = keep_err * sign;
         }
 #pragma unroll
         for (int k = 0; k + 1 < NC; ++k) wreg[k] = wreg[k + 1];
