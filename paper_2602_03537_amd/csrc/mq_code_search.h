@@ -19,14 +19,14 @@
 //     U - 1,  U,  and for every width r < 8:  T_r if T_r >= U, else T_r - 1
 // (clamped to 0 .. 255): |R| + 1 candidates instead of 256, and more candidates do no harm.
 // The smallest minimiser: E is monotone (not strictly: a rounded sum can absorb a difference) on the way from any
-// other minimiser to a candidate, so a smaller code with the same E is next to the smallest winning candidate:
-// walking down from it while E does not change finds it.  Where lambda_8 = 0 E is constant on whole runs of codes;
+// other minimiser to a candidate, so the codes with the same E below the smallest winning candidate are a run that ends
+// at it (code_lowest_equal).  Where lambda_8 = 0 E is constant on whole runs of codes;
 // code_run_start takes the step down to the start of a run at once.
 //
 // U itself is estimated with a reciprocal and then checked in the arithmetic above (D(U-1) <= w < D(U)), and found in it
 // where the check fails.
-// What lies outside the argument needs no search.  Scale 0, a weight so large that no D changes it (code_flat), an infinity or a
-// NaN anywhere: E is the same for every code, or infinite or NaN for every code, and the answer is code 0.  A negative scale:
+// What lies outside the argument needs no search.  Scale 0, a weight so large that no D shows in it, an infinity or a NaN
+// anywhere (code_flat): E is the same for every code, or infinite or NaN for every code, and the answer is code 0.  A negative scale:
 // negating w and scale together negates every D and e and changes no E, so the callers do that first (code_sign).
 #pragma once
 #include <stdint.h>
@@ -90,9 +90,12 @@ MQ_HD float code_error(uint32_t q, float w, float s, float z, const QuantLambda 
 // The fast search applies: monotone in S, no overflow in e * e, no NaN.  (scale and zero are fp16 values.)
 MQ_HD bool code_grid_normal(float s, float z) { return (s >= 0.f) & (s < 1e6f) & (__builtin_fabsf(z) < 1e6f); }
 MQ_HD bool code_weight_normal(float w) { return __builtin_fabsf(w) < 0x1p46f; }
-// Every code has the same E, or none has one that is a number.  (Finite grid: |D| <= 65504 * (65504 + 255) < 2^33, half the
-// distance of neighbours just below 2^58, so w - D rounds to w from there on.)
-MQ_HD bool code_flat(float w, float s, float z) { return !(code_grid_normal(s, z) & (s != 0.f) & (__builtin_fabsf(w) < 0x1p58f)); }
+// Every code has the same E, or none has one that is a number (scale not negative): w - D falls with the slice value, so where it is
+// the same at the two ends it is the same throughout.  (Finite w and grid: |D| < 2^33, no more than half the distance of
+// neighbours at 2^58, so from there on every weight is one of these.)
+MQ_HD bool code_flat(float w, float s, float z) {
+    return !(code_grid_normal(s, z) & (code_residual_f(0.f, w, s, z) > code_residual_f(255.f, w, s, z)));
+}
 // The factor that scale and weights of a group are multiplied by before a search: exact, and E stays the same
 MQ_HD float code_sign(float s) { return s < 0.f ? -1.f : 1.f; }
 // Estimate of U from 1 / scale and zero + 1, in 0 .. 256.  It is right if and only if the residual of width 8 is
@@ -106,13 +109,29 @@ MQ_HD int code_estimate(float w, float inv_s, float z1) {
 #endif
 }
 MQ_HD bool code_side_ok(int q, int U, float e8) { return (e8 < 0.f) == (q >= U); }
-// U from an estimate next to it
+// The smallest x in 0 .. hi from which on `holds` is true (it is true from some x on; hi itself is not asked), looked for from
+// `at` (< hi) outwards in steps that double, then by halves: few evaluations where it is near, 2 log2(hi) at most.
+template <class F> MQ_HD int code_first(int at, int hi, F &&holds) {
+    int lo = 0, step = 1;
+    bool above = false, below = false;  // of an answer already tried
+#pragma unroll 1
+    while (lo < hi) {
+        if (holds(at)) {
+            hi = at;
+            above = true;
+        } else {
+            lo = at + 1;
+            below = true;
+        }
+        const int down = hi - step > 0 ? hi - step : 0, up = lo + step < hi ? lo + step - 1 : hi - 1;
+        at = (above && below) ? (lo + hi) >> 1 : above ? down : up;
+        step *= 2;
+    }
+    return hi;
+}
+// U from an estimate
 MQ_HD int code_first_above(int U, float w, float s, float z) {
-#pragma unroll 1
-    while (U > 0 && code_residual_f((float)(U - 1), w, s, z) < 0.f) --U;
-#pragma unroll 1
-    while (U < 256 && !(code_residual_f((float)U, w, s, z) < 0.f)) ++U;
-    return U;
+    return code_first(U < 255 ? U : 255, 256, [&](int q) { return code_residual_f((float)q, w, s, z) < 0.f; });
 }
 MQ_HD int code_clamp(int q) { return q < 0 ? 0 : q > 255 ? 255 : q; }
 // E as a number that sorts like it (E >= 0)
@@ -129,13 +148,15 @@ template <int R = 1> MQ_HD int code_run_start(int q, const QuantLambda &lam, int
     }
 }
 
-// Down to the smallest code with the same E
+// The smallest code with E's bits, q being one and the codes above it of no interest
 template <uint32_t MASK>
-MQ_HD int code_walk_down(int q, uint32_t bits, float w, float s, float z, const QuantLambda &lam) {
-    float e8;
-#pragma unroll 1
-    while (q > 0 && code_bits(code_error<MASK>((uint32_t)(q - 1), w, s, z, lam, e8)) == bits) --q;
-    return q;
+MQ_HD int code_lowest_equal(int q, uint32_t bits, float w, float s, float z, const QuantLambda &lam) {
+    if (lam.v[kCodeBits - 1] == 0.f) q = code_run_start(q, lam);
+    if (q == 0) return 0;
+    return code_first(q - 1, q, [&](int p) {
+        float e8;
+        return code_bits(code_error<MASK>((uint32_t)p, w, s, z, lam, e8)) == bits;
+    });
 }
 
 // ---- one weight per lane.  All in fp32 (codes and slice values are exact there, and fp32 operations issue faster than
@@ -252,12 +273,10 @@ MQ_HD CodeBest code_best(int U_estimate, float w, float s, float z, const QuantL
 // The decision for one weight, whatever it is (U: an estimate; scale not negative).  Seldom needed: 4e-5 of Gaussian weights have an estimate
 // that is off by one, fewer have a smaller code with the same E.
 template <uint32_t MASK> MQ_HD uint32_t code_search_closely(int U, float w, float s, float z, const QuantLambda &lam) {
-    if (code_flat(w, s, z)) return 0;
+    if (code_flat(w, s, z)) return 0;  // (|w| < 2^58 from here on)
     const CodeBest b = code_best<MASK>(code_first_above(U, w, s, z), w, s, z, lam);
-    int q = (int)b.q;
-    if (!b.tie) return (uint32_t)q;
-    if (lam.v[kCodeBits - 1] == 0.f) q = code_run_start(q, lam);
-    return (uint32_t)code_walk_down<MASK>(q, b.bits, w, s, z, lam);
+    const int q = (int)b.q;
+    return (uint32_t)(b.tie ? code_lowest_equal<MASK>(q, b.bits, w, s, z, lam) : q);
 }
 
 // The decision for VEC weights that share scale and zero

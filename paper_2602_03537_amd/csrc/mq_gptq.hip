@@ -91,6 +91,20 @@ __device__ __forceinline__ void code_terms(uint32_t q, float w, float s, float z
         code_terms<MASK, ALL, R + 1>(q, w, s, z, lam, E, acc, any, e);
     }
 }
+// The smallest code with E's bits, q being one (mq_code_search.h: they are a run that ends at q): the lanes of the row try every
+// 16th code below it, then the 15 in between
+template <uint32_t MASK>
+__device__ __forceinline__ uint32_t row_lowest_equal(int q, uint32_t bits, float w, float s, float z, const QuantLambda &lam, int part) {
+    const int row_bit = (threadIdx.x & 63) & ~(kRowLanes - 1);
+#pragma unroll 1
+    for (int step = kRowLanes; step; step /= kRowLanes) {
+        const int p = q - step * (part + 1);
+        float e8;
+        const bool same = p >= 0 && code_bits(code_error<MASK>((uint32_t)p & 255u, w, s, z, lam, e8)) == bits;
+        q -= step * __builtin_popcount((uint32_t)(__ballot(same) >> row_bit) & 0xffffu);
+    }
+    return (uint32_t)q;
+}
 // a / b, correctly rounded, y = RN(1 / b): the first correction brings a * y (off by up to two units in the last place) to
 // within one unit, from where one more exact remainder rounds correctly (Markstein's theorem; no over- or underflow on the
 // way while |a| and |b| are within 2^-60 .. 2^60, or a = 0).  Half as long a chain as the general division.
@@ -220,7 +234,9 @@ __global__ __launch_bounds__(1024) void gptq_block_kernel(const float *__restric
             if constexpr (NL >= 16) argmin_step<0x140>(Eb, key, err);  // row_mirror: the halves of 16 lanes
             uint32_t qw = key >> 2;
             if (__builtin_expect((key & 3u) != 0, 0)) {  // rare; the lanes of a row take it together
-                qw = code_search_closely<MASK>(Uc, w, s, z, lam);
+                // the list's minimum is the least E there is unless the search did not hold: then all that is left is a smaller code with it
+                if (key & 2u) qw = code_search_closely<MASK>(Uc, w, s, z, lam);
+                else qw = row_lowest_equal<MASK>((int)qw, Eb, w, s, z, lam, part);
                 float e2 = 0.f, a2 = 0.f, e8_2;
                 bool any2 = false;
                 code_terms<MASK, ALL>(qw, w, s, z, lam, e2, a2, any2, e8_2);

@@ -102,3 +102,19 @@ def test_weights_beyond_every_step_cost_no_sweep_of_the_codes(search, widths):
     # just below it a step can show
     w = np.array([np.nextafter(np.float32(2.0 ** 58), np.float32(0))] * 2, np.float32)
     search(w, np.array([65504, -65504], np.float16), np.array([-65504, 65504], np.float16), widths, [1.0] * len(widths))
+
+
+@pytest.mark.parametrize("widths", [s for s in SETS if len(s) > 1] + [(3, 4), (4,), (1,)])
+@pytest.mark.parametrize("fade", [0, 12, 24, 60, 90])
+def test_codes_with_the_same_error_cost_no_walk(search, widths, fade):
+    # each width's lambda 2^-fade of the one before (up to a range of 2^100): the sums absorb the finer terms, and long runs of codes
+    # have the same error; so have most or all codes for weights that few of the steps show in
+    rng = np.random.default_rng([302, len(widths), fade])
+    fade = min(fade, 100 / max(1, len(widths) - 1))
+    lam = [2.0 ** -int(fade * i) for i in range(len(widths))]
+    w = np.concatenate([rng.normal(0, 0.1, 300), 10.0 ** rng.uniform(0, 17, 300) * rng.choice([-1, 1], 300)]).astype(np.float32)
+    s = np.where(rng.random(w.size) < 0.1, 6e-8, rng.uniform(2e-4, 2e-3, w.size)).astype(np.float16)
+    z = rng.integers(0, 256, w.size).astype(np.float16)
+    cost = search(w, s, z, widths, lam)
+    built = 3 if set(widths) <= {3, 4, 8} else 5 if set(widths) <= {2, 3, 4, 6, 8} else 8
+    assert cost.max() <= 2 * _residuals(widths) + 16 + 16 * built   # the list twice, U found anew, the run's start

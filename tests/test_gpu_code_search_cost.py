@@ -62,3 +62,20 @@ def test_odd_scales_do_not_hold_up_a_launch(kind, widths):
     plain = [t[:, :256 // (1 if t.shape[1] > 8 else 128)].contiguous() for t in plain]
     odd = _odd_scales(kind, *plain)
     assert _loop_time(*odd, widths, lam) < 3 * _loop_time(*plain, widths, lam)
+
+
+@pytest.mark.parametrize("lam", [(1.0, 1.0, 1e-7), (1.0, 1e-3, 1e-9), (1e-30, 1e-20, 1e-38)])
+def test_uneven_lambdas_do_not_hold_up_a_launch(lam):
+    # the sums absorb the finer terms: long runs of codes have the same error
+    W, s, z = _inputs(2048, 1024, 312)
+    assert _quant_time(W, s, z, (3, 4, 8), lam) < 6 * _quant_time(W, s, z, (3, 4, 8), (1.0, 1.0, 1.0))
+    W, s, z = W[:, :256].contiguous(), s[:, :2].contiguous(), z[:, :2].contiguous()
+    assert _loop_time(W, s, z, (3, 4, 8), lam) < 6 * _loop_time(W, s, z, (3, 4, 8), (1.0, 1.0, 1.0))
+
+
+def test_far_outliers_do_not_hold_up_a_launch():
+    # so far out that no step shows: every code has the same error
+    W, s, z = _inputs(2048, 256, 313)
+    far = W.clone()
+    far[7, ::5] = 1e16
+    assert _loop_time(far, s, z, (3, 4, 8), (1.0, 1.0, 1.0)) < 6 * _loop_time(W, s, z, (3, 4, 8), (1.0, 1.0, 1.0))
