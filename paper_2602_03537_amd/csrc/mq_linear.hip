@@ -427,7 +427,7 @@ template <int R, int M, bool SL = false>
 static hipError_t launch_linear_rb_rm(const LayerDesc &L, float *part, int32_t *cnt, hipStream_t s) {
     const int KS = pick_k_slices(L);
     const int W = rb_waves(L, KS);
-    if constexpr (!SL) {
+    if constexpr (!SL) {  // a single from-parent call takes fp16 activations
         if (L.x_bf16) {
             LayerDesc B = L;
             B.x = static_cast<const _Float16 *>(L.x_bf16);
@@ -435,7 +435,6 @@ static hipError_t launch_linear_rb_rm(const LayerDesc &L, float *part, int32_t *
                           cnt);
         }
     }
-    if (L.x_bf16) return hipErrorInvalidValue;  // from the parent: converted ahead of the launch by the caller
     return launch((linear_rb_kernel<R, M, kXLds, SL>), dim3((unsigned)(L.RB * KS)), dim3(64 * W), 0, s, L, KS, part,
                        cnt);
 }
