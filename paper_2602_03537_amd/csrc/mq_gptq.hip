@@ -20,6 +20,7 @@ namespace mq {
 
 constexpr int kGptqMaxBlock = 128;
 constexpr int kTrailRows = 8;
+constexpr int kGptqMaxWaves = 8;  // of a workgroup of the block kernel
 constexpr int kRowLanes = 16;  // lanes that share a row: one DPP row
 
 // ---- one column decision, spread over the lanes of a row
@@ -127,7 +128,7 @@ __device__ __forceinline__ bool divides_plainly(float a) {  // from below; norma
 // 4096 rows x 4096 columns, R = {3,4,8}: 44 us a block = 0.34 us a step, of about 145 instructions of one wave per SIMD (160 us
 // with all 256 candidates over 64 lanes and the weights in LDS); the whole loop 6.85 -> 2.98 ms.
 template <uint32_t MASK, bool ALL>
-__global__ __launch_bounds__(1024) void gptq_block_kernel(const float *__restrict__ W, int64_t ldw, int64_t N, int64_t i0,
+__global__ __launch_bounds__(64 * kGptqMaxWaves, 4) void gptq_block_kernel(const float *__restrict__ W, int64_t ldw, int64_t N, int64_t i0,
                                                           int B, const float *__restrict__ U, int64_t ldu,
                                                           const _Float16 *__restrict__ scales,
                                                           const _Float16 *__restrict__ zeros, int64_t G,
@@ -333,9 +334,11 @@ __global__ __launch_bounds__(64) void gptq_trailing_kernel(float *__restrict__ W
     }
 }
 
-// Waves per workgroup (four rows each): four while the rows then make at most two workgroups per compute unit (64 KB of
-// LDS each), more beyond, so that the rows stay resident at one time up to 32768 of them.
-inline int gptq_block_waves(int64_t N) { return N <= 8192 ? 4 : N <= 16384 ? 8 : 16; }
+// Waves per workgroup (four rows each): four up to 8192 rows, which is two workgroups per compute unit, and all that a
+// workgroup's 67 KB of LDS let in; eight beyond, so that twice the rows share a compute unit's LDS and are resident at one time
+// (R = {3,4,8}, us a block: 16384 rows 97, with four waves 112; 20480 rows 132 and 141).  Sixteen would leave one workgroup per compute unit
+// (at most 128 registers a lane: 16 waves), the same rows in coarser pieces: 20480 rows 162, 65536 rows 328 against 323, and {2,3,4,6,8} 233 against 176.
+inline int gptq_block_waves(int64_t N) { return N <= 8192 ? 4 : kGptqMaxWaves; }
 
 template <uint32_t MASK, bool ALL>
 static hipError_t launch_gptq_mask(float *W, int64_t ldw, int64_t N, int64_t K, const float *U, int64_t ldu,

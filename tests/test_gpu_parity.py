@@ -876,7 +876,7 @@ def test_matgptq_column_loop_rejects_bad_arguments_loudly():
         mq.mq_matgptq_quantize(Wd, Ud, sd, zd, (8,), (1.0,), c=4)
 
 
-@pytest.mark.parametrize("N,K", [(4096, 256), (4100, 128), (16384, 128), (16390, 256)])   # workgroups of 4, 4, 8 and 16 waves
+@pytest.mark.parametrize("N,K", [(4096, 256), (4100, 128), (16384, 128), (16390, 256)])   # workgroups of 4, 4, 8 and 8 waves
 def test_matgptq_column_loop_many_rows_sampled(N, K):
     # more rows per workgroup with more rows: the same codes, checked on sampled rows
     W, s, z = _quant_inputs(N, K, [95, N, K])
