@@ -129,9 +129,12 @@ template <class F> MQ_HD int code_first(int at, int hi, F &&holds) {
     }
     return hi;
 }
-// U from an estimate
+// U from an estimate: off by one nearly always, which four residuals side by side settle
 MQ_HD int code_first_above(int U, float w, float s, float z) {
-    return code_first(U < 255 ? U : 255, 256, [&](int q) { return code_residual_f((float)q, w, s, z) < 0.f; });
+    auto above = [&](int q) { return (q > 255) | ((q >= 0) & (code_residual_f((float)q, w, s, z) < 0.f)); };
+    const bool a = above(U - 2), b = above(U - 1), c = above(U), d = above(U + 1);
+    if (!a & d) return U + 1 - b - c;
+    return code_first(U < 255 ? U : 255, 256, above);
 }
 MQ_HD int code_clamp(int q) { return q < 0 ? 0 : q > 255 ? 255 : q; }
 // E as a number that sorts like it (E >= 0)

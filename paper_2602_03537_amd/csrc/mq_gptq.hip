@@ -151,7 +151,7 @@ __global__ __launch_bounds__(64 * kGptqMaxWaves, 4) void gptq_block_kernel(const
     const float sign = code_sign(s_in), s = s_in * sign;
     float wreg[NC];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) wreg[c] = c * kRowLanes < B ? W[nr * ldw + i0 + c * kRowLanes + part] * sign : 0.f;
+    for (int c = 0; c < NC; ++c) wreg[c] = c * kRowLanes < B ? W[nr * ldw + i0 + c * kRowLanes + part] : 0.f;
     const float inv_s = 1.f / s, z1 = z + 1.f;
     const LaneCandidate lc = lane_candidate<MASK>(part);
     const bool grid_ok = code_grid_normal(s, z);
@@ -183,6 +183,9 @@ __global__ __launch_bounds__(64 * kGptqMaxWaves, 4) void gptq_block_kernel(const
         u_ok = __builtin_fabsf(ujj) > 0x1p-50f && __builtin_fabsf(ujj) < 0x1p50f;
     }
     const bool fast_ok = grid_ok & (__syncthreads_and(u_ok) != 0);
+    // (not where W is loaded: the loads of U would wait for it, 1.5 us a launch)
+#pragma unroll
+    for (int c = 0; c < NC; ++c) wreg[c] *= sign;
     for (int c0 = 0; c0 < B; c0 += kRowLanes) {
         // 16 columns, one of them per lane of a row in wreg[0]; register k holds this lane's column 16 k further on.
         // (Past the block's end the registers hold nothing of use, and the rows of U run into the padding.)
