@@ -151,15 +151,17 @@ template <int R = 1> MQ_HD int code_run_start(int q, const QuantLambda &lam, int
     }
 }
 
+// E(q) has these bits (q from -255 on; below 0 there is none)
+template <uint32_t MASK> MQ_HD bool code_same(int q, uint32_t bits, float w, float s, float z, const QuantLambda &lam) {
+    float e8;
+    return (q >= 0) & (code_bits(code_error<MASK>((uint32_t)q & 255u, w, s, z, lam, e8)) == bits);
+}
 // The smallest code with E's bits, q being one and the codes above it of no interest
 template <uint32_t MASK>
 MQ_HD int code_lowest_equal(int q, uint32_t bits, float w, float s, float z, const QuantLambda &lam) {
     if (lam.v[kCodeBits - 1] == 0.f) q = code_run_start(q, lam);
     if (q == 0) return 0;
-    return code_first(q - 1, q, [&](int p) {
-        float e8;
-        return code_bits(code_error<MASK>((uint32_t)p, w, s, z, lam, e8)) == bits;
-    });
+    return code_first(q - 1, q, [&](int p) { return code_same<MASK>(p, bits, w, s, z, lam); });
 }
 
 // ---- one weight per lane.  All in fp32 (codes and slice values are exact there, and fp32 operations issue faster than

@@ -12,7 +12,7 @@
 // rounded on its own (no contraction), the error sum over r ascending as ((w - D_r1) + (w - D_r2))
 // + ..., then / |R|, then / U[j,j]; an update is w = w - (E * U[j,k]); the update of the rest is
 // applied as the same rank-1 terms in ascending j, so results do not depend on B.
-#include "mq_code_search.h"
+#include "mq_code_lanes.h"
 #include "mq_internal.h"
 #include "mq_static_for.h"
 
@@ -21,37 +21,6 @@ namespace mq {
 constexpr int kGptqMaxBlock = 128;
 constexpr int kTrailRows = 8;
 constexpr int kGptqMaxWaves = 8;  // of a workgroup of the block kernel
-constexpr int kRowLanes = 16;  // lanes that share a row: one DPP row
-
-// ---- one column decision, spread over the lanes of a row
-// Entries of the candidate list (mq_code_search.h), two lanes each: U (its second lane: width 7's candidate, where
-// the variant has it), U - 1, and one per coarser width; the second lane of an entry evaluates the code below, so that
-// the minimum also shows whether a smaller code has the same E.
-constexpr int gptq_coarse(uint32_t mask) { return popc8(mask & 0x3Fu); }  // widths 1 .. 6
-constexpr int gptq_lanes(uint32_t mask) {  // lanes that hold different entries: a power of two, 4 .. 16
-    const int need = 2 * (2 + gptq_coarse(mask));
-    return need <= 4 ? 4 : need <= 8 ? 8 : 16;
-}
-// What a lane evaluates, given U:  T - (T < U ? left : 0) - second, T = roundup(U, step) - half
-struct LaneCandidate {
-    int step, half, left, second;
-    bool seven;  // width 7's candidate: reported as a second one where it is below U (its own lower neighbour is not listed)
-};
-template <uint32_t MASK> __device__ __forceinline__ LaneCandidate lane_candidate(int part) {
-    const int e = (part & (gptq_lanes(MASK) - 1)) >> 1, second = part & 1;
-    LaneCandidate c{1, 0, 0, 0, false};  // U
-    if (e == 0 && second && (MASK & 0x40u)) c = {2, 1, 1, 0, true};
-    if (e == 1) c = {1, 1, 0, second, false};  // U - 1
-    int k = 2;
-#pragma unroll
-    for (int r = 1; r <= 6; ++r) {
-        if (!((MASK >> (r - 1)) & 1)) continue;
-        const int step = 1 << (kC - r);
-        if (e == k) c = {step, step / 2, 1, second, false};
-        ++k;
-    }
-    return c;
-}
 
 template <int CTRL> __device__ __forceinline__ uint32_t dpp_u(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xf, 0xf, true);
@@ -69,29 +38,6 @@ template <int CTRL> __device__ __forceinline__ void argmin_step(uint32_t &E, uin
     err = take ? oerr : err;
 }
 
-// E(q), the sum (w - D_r1) + (w - D_r2) + ... over the widths with lambda_r != 0 (r ascending), and the residual of
-// width 8.  ALL: every width of MASK has lambda_r != 0.
-template <uint32_t MASK, bool ALL, int R = 1>
-__device__ __forceinline__ void code_terms(uint32_t q, float w, float s, float z, const QuantLambda &lam, float &E,
-                                           float &acc, bool &any, float &e) {
-#pragma clang fp contract(off)
-    if constexpr (R <= kC) {
-        if constexpr ((MASK >> (R - 1)) & 1) {
-            constexpr bool first = (MASK & ((1u << (R - 1)) - 1)) == 0;
-            e = code_residual(slice_of<R>(q), w, s, z);
-            const float p = e * e;
-            const float term = lam.v[R - 1] * p;
-            E = first ? term : E + term;
-            if constexpr (ALL) {
-                acc = first ? e : acc + e;
-            } else if (lam.v[R - 1] != 0.f) {
-                acc = any ? acc + e : e;
-                any = true;
-            }
-        }
-        code_terms<MASK, ALL, R + 1>(q, w, s, z, lam, E, acc, any, e);
-    }
-}
 // The smallest code with E's bits, q being one (mq_code_search.h: they are a run that ends at q): the lanes of the row try every
 // 16th code below it, then the 15 in between
 template <uint32_t MASK>
@@ -99,25 +45,11 @@ __device__ __forceinline__ uint32_t row_lowest_equal(int q, uint32_t bits, float
     const int row_bit = (threadIdx.x & 63) & ~(kRowLanes - 1);
 #pragma unroll 1
     for (int step = kRowLanes; step; step /= kRowLanes) {
-        const int p = q - step * (part + 1);
-        float e8;
-        const bool same = p >= 0 && code_bits(code_error<MASK>((uint32_t)p & 255u, w, s, z, lam, e8)) == bits;
+        const bool same = code_same<MASK>(q - step * (part + 1), bits, w, s, z, lam);
         q -= step * __builtin_popcount((uint32_t)(__ballot(same) >> row_bit) & 0xffffu);
     }
     return (uint32_t)q;
 }
-// a / b, correctly rounded, y = RN(1 / b): the first correction brings a * y (off by up to two units in the last place) to
-// within one unit, from where one more exact remainder rounds correctly (Markstein's theorem; no over- or underflow on the
-// way while |a| and |b| are within 2^-60 .. 2^60, or a = 0).  Half as long a chain as the general division.
-__device__ __forceinline__ float divide_by(float a, float b, float y) {
-    const float q0 = a * y;
-    const float q1 = __builtin_fmaf(__builtin_fmaf(-b, q0, a), y, q0);
-    return __builtin_fmaf(__builtin_fmaf(-b, q1, a), y, q1);
-}
-__device__ __forceinline__ bool divides_plainly(float a) {  // from below; normal weights are small enough
-    return (a == 0.f) | (__builtin_fabsf(a) > 0x1p-50f);
-}
-
 // The 128 columns of a block for the rows of one workgroup.  What bounds it is the serial chain of the column steps
 // (a column's code decides the next column's weight), so a step is made short and everything else is kept off it:
 //   * kRowLanes lanes share a row and evaluate the handful of candidates that can win (mq_code_search.h) side by side, each with
@@ -180,7 +112,7 @@ __global__ __launch_bounds__(64 * kGptqMaxWaves, 4) void gptq_block_kernel(const
     if (tid < B) {
         const float ujj = U[(i0 + tid) * ldu + i0 + tid];
         rd[tid] = 1.f / ujj;
-        u_ok = __builtin_fabsf(ujj) > 0x1p-50f && __builtin_fabsf(ujj) < 0x1p50f;
+        u_ok = divisor_plain(ujj);
     }
     const bool fast_ok = grid_ok & (__syncthreads_and(u_ok) != 0);
     // (not where W is loaded: the loads of U would wait for it, 1.5 us a launch)
@@ -210,36 +142,22 @@ __global__ __launch_bounds__(64 * kGptqMaxWaves, 4) void gptq_block_kernel(const
             if constexpr (jj + 1 < kRowLanes) fetch_u(IntC<jj + 1>{});
             const float w = dpp_f<0x150 + jj>(wreg[0]);  // row_newbcast: column jj's weight, to all lanes of the row
             const int Uc = code_estimate(w, inv_s, z1);
-            const int T = ((Uc + lc.step - 1) & -lc.step) - lc.half;
-            int q = T - (T < Uc ? lc.left : 0);
-            int second = lc.second;
-            if constexpr (!ALL) {
-                if (runs) q = code_run_start(code_clamp(q), lam);
-                if (lc.seven) second = T < Uc ? 1 : 0;
-                q = code_clamp(lc.seven ? q : q - second);
-            } else {
-                q = code_clamp(q - second);
-            }
-            float E = 0.f, acc = 0.f, e8 = 0.f;
-            bool any = false;
-            code_terms<MASK, ALL>((uint32_t)q, w, s, z, lam, E, acc, any, e8);
-            float err = divide_by(divide_by(acc, nw, inv_nw), ujj[jj % 2], rjj[jj % 2]);
-            // key: the code; bit 1: the search does not hold here (such a lane wins);
-            // bit 0: look closer if this one wins
-            const bool bad = !(fast_ok & code_weight_normal(w) & code_side_ok(q, Uc, e8));
-            uint32_t Eb = code_bits(E), key = 4u * (uint32_t)q + (((second != 0) | !divides_plainly(acc)) ? 1u : 0u);
+            const LaneDecision d = lane_decision<MASK, ALL>(lc, Uc, w, s, z, lam, runs, fast_ok, nw, inv_nw, ujj[jj % 2], rjj[jj % 2]);
+            uint32_t Eb = d.bits, key = d.key;
+            float err = d.err;
+            const bool bad = d.bad;
             asm volatile("" : "+v"(Eb), "+v"(key));  // selects below, no branch
             Eb = bad ? 0u : Eb;
-            key = bad ? 2u : key;
-            constexpr int NL = gptq_lanes(MASK);
+            key = bad ? kLaneBad : key;
+            constexpr int NL = lanes_used(MASK);
             argmin_step<0xB1>(Eb, key, err);  // quad_perm [1,0,3,2]
             argmin_step<0x4E>(Eb, key, err);  // quad_perm [2,3,0,1]
             if constexpr (NL >= 8) argmin_step<0x141>(Eb, key, err);   // row_half_mirror: the quads of 8 lanes
             if constexpr (NL >= 16) argmin_step<0x140>(Eb, key, err);  // row_mirror: the halves of 16 lanes
             uint32_t qw = key >> 2;
-            if (__builtin_expect((key & 3u) != 0, 0)) {  // rare; the lanes of a row take it together
+            if (__builtin_expect((key & (kLaneBad | kLaneLook)) != 0, 0)) {  // rare; the lanes of a row take it together
                 // the list's minimum is the least E there is unless the search did not hold: then all that is left is a smaller code with it
-                if (key & 2u) qw = code_search_closely<MASK>(Uc, w, s, z, lam);
+                if (key & kLaneBad) qw = code_search_closely<MASK>(Uc, w, s, z, lam);
                 else qw = row_lowest_equal<MASK>((int)qw, Eb, w, s, z, lam, part);
                 float e2 = 0.f, a2 = 0.f, e8_2;
                 bool any2 = false;

@@ -56,3 +56,20 @@ def test_column_loop_row_counts(N):
     q = mq.mq_matgptq_quantize(dev(W.copy()), dev(U), dev(s), dev(z), (3, 4, 8), (1.0, 1.0, 1.0)).cpu().numpy()
     ref, _ = oracle.matgptq_quantize(W[rows], U, s[rows], z[rows], 8, (3, 4, 8), (1.0, 1.0, 1.0), 128, 128, np.float32)
     assert np.array_equal(q[rows], ref)
+
+
+@pytest.mark.parametrize("widths,lam", [((3, 4, 8), (1.0, 1.0, 1e-7)), ((3, 4, 8), (1.0, 1e-3, 1e-9)), ((3, 4, 8), (1e-6, 1e-3, 1.0)),
+                                        ((3, 4), (1.0, 1e-9)), ((2, 3, 4, 6, 8), (1.0, 1e-3, 1e-6, 1e-9, 1e-12)),
+                                        ((6, 7), (1.0, 1e-9)), ((1, 2, 3, 4, 5, 6, 7, 8), tuple(10.0 ** -(3 * i) for i in range(8)))])
+def test_uneven_lambdas(widths, lam):
+    # the sums absorb the finer terms: runs of codes with the same error, in both calls
+    N, K = 21, 256
+    W = synth.make_weights(N, K, [105, len(widths)])
+    _, s, z = synth.quantize_parent(W)
+    s[3], s[4], s[5] = -s[3], 0, s[5] * np.float16(1e-3)
+    U = _factor(K, 106)
+    got = mq.mq_quant_matgptq(dev(W), dev(s), dev(z), widths, lam).cpu().numpy()
+    assert np.array_equal(got, oracle.quant_matgptq(W, s, z, 8, widths, lam, 128, np.float32))
+    ref, _ = oracle.matgptq_quantize(W, U, s, z, 8, widths, lam, 128, 128, np.float32)
+    got = mq.mq_matgptq_quantize(dev(W.copy()), dev(U), dev(s), dev(z), widths, lam).cpu().numpy()
+    assert np.array_equal(got, ref), np.argwhere(got != ref)[:5]
