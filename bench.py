@@ -569,10 +569,20 @@ def bench_resident_parent(args, mq, synth, torch, np, dev):
     return 0
 
 
-FP32_VECTOR_PEAK_TFLOPS = 157.3
 # Vector lanes x clock without the factor two of a fused multiply-add: 256 CUs x 4 SIMDs x 32 lanes per clock x 2.4 GHz.
-# Algorithm 1's arithmetic is defined operation by operation (nothing may be fused), so this is its ceiling.
+# Algorithm 1's and the column loop's arithmetic is defined operation by operation (nothing may be fused), so this is the ceiling.
 VECTOR_LANE_OPS_PEAK_T = 78.6
+
+
+def gptq_ops(N, K, n_widths):
+    """Defined fp32 operations that the column loop has to do for N x K weights and n_widths target widths, one each for a
+    rounded add, subtract, multiply or divide: Algorithm 1 on the n + 1 candidates that decide it (5 to a width: S - zero,
+    * scale, w - D, square, * lambda; n - 1 adds; one compare), the propagated error (3 to a width, n - 1 adds, two divisions), and
+    a multiply and a subtract per weight for every earlier column."""
+    n = n_widths
+    return N * K * ((n + 1) * (5 * n + (n - 1) + 1) + (3 * n + (n - 1) + 2)) + N * K * (K - 1)
+
+
 # Vector instructions the compiled quant_kernel<140, 4> executes per weight (R = {3,4,8}): the SQ_INSTS_VALU counter in
 # profiles/quant_kernel_alg1_llama2_7b_shapes.txt.  The definition counts 19 per candidate and weight; the kernel evaluates the
 # few candidates that can win.
@@ -593,7 +603,7 @@ def quant_executed_ops_per_weight():
 def bench_quant(args, mq, synth, torch, np, dev):
     """Algorithm 1 over whole layers: one mq_quant_matgptq launch per (shape, R); fp32 weights resident in HBM."""
     sets = {"3,4,8": ((3, 4, 8), (1.0, 1.0, 1.0)), "2,3,4,6,8": ((2, 3, 4, 6, 8), (1.0,) * 5), "8": ((8,), (1.0,))}
-    table, tot_w, tot_t, tot_fl = {}, 0.0, 0.0, 0.0
+    table, tot_w, tot_t = {}, 0.0, 0.0
     g = torch.Generator(device=dev)
     g.manual_seed(4242)
     for (N, K) in ((4096, 4096), (11008, 4096), (4096, 11008)):
@@ -612,38 +622,28 @@ def bench_quant(args, mq, synth, torch, np, dev):
             e1.record()
             torch.cuda.synchronize()
             t = e0.elapsed_time(e1) * 1e-3 / reps
-            # the brute force as defined: per candidate and width sub, mul, sub, mul, mul, add; one compare per candidate
-            fl = (6.0 * len(widths) + 1.0) * 256.0 * N * K
-            table[f"{N}x{K}:R{{{name}}}"] = {"us": round(t * 1e6, 1), "Gweights_per_s": round(N * K / t / 1e9, 2),
-                                             "TFLOPs": round(fl / t / 1e12, 1)}
+            table[f"{N}x{K}:R{{{name}}}"] = {"us": round(t * 1e6, 1), "Gweights_per_s": round(N * K / t / 1e9, 2)}
             if name == "3,4,8":
                 tot_w += N * K
                 tot_t += t
-                tot_fl += fl
         del W, Q, L
-    out = _base_line("Algorithm 1 (brute-force cross-bit-width code choice) throughput, R = {3,4,8}", tot_w / tot_t / 1e9,
+    out = _base_line("Algorithm 1 (cross-bit-width code choice) throughput, R = {3,4,8}", tot_w / tot_t / 1e9,
                      "Gweights/s", args, tot_t * 1e3,
                      "Llama-2-7B layer shapes (4096x4096, 11008x4096, 4096x11008), fp32 weights, group 128, "
                      "c = 8, R = {3,4,8} with lambda = 1 (the paper's setting); other R in `table`", {})
     out["dtype"] = "f32"
     out["table"] = table
-    # roofline: the lane-operations the kernel EXECUTES per second against the unfused vector peak (the brute force as
-    # defined counts 19 operations per candidate and weight and 256 candidates; the kernel evaluates |R| + 1 of them, so the
-    # counted-work rate would exceed the peak many times over and say nothing)
+    # roofline: the lane-operations the kernel EXECUTES per second (the few candidates that can win, not the 256 of the
+    # definition) against the unfused vector peak
     ops_w = quant_executed_ops_per_weight()
-    counted = tot_fl / tot_t / 1e12
+    out["roofline"] = {"bound": "alu", "kernel": "mq::quant_kernel<140, 4>", "achieved": None,
+                       "peak": VECTOR_LANE_OPS_PEAK_T, "unit": "T lane-op/s", "frac": None,
+                       "avg_launch_us": round(tot_t / 3 * 1e6, 1), "traffic": None}
     if ops_w is not None:
         ach = ops_w * tot_w / tot_t / 1e12
-        out["roofline"] = {"bound": "alu", "kernel": "mq::quant_kernel<140, 4>", "achieved": round(ach, 1),
-                           "peak": VECTOR_LANE_OPS_PEAK_T, "unit": "T lane-op/s", "frac": round(ach / VECTOR_LANE_OPS_PEAK_T, 4),
-                           "avg_launch_us": round(tot_t / 3 * 1e6, 1),
-                           "executed_lane_ops_per_weight": round(ops_w, 1),
-                           "executed_ops_source": os.path.relpath(QUANT_PROFILE, ROOT),
-                           "counted_brute_force_Tops": round(counted, 1), "traffic": None}
-    else:
-        out["roofline"] = {"bound": "alu", "kernel": "mq::quant_kernel<140, 4>", "achieved": None,
-                           "peak": VECTOR_LANE_OPS_PEAK_T, "unit": "T lane-op/s", "frac": None,
-                           "counted_brute_force_Tops": round(counted, 1), "traffic": None}
+        out["roofline"].update(achieved=round(ach, 1), frac=round(ach / VECTOR_LANE_OPS_PEAK_T, 4),
+                               executed_lane_ops_per_weight=round(ops_w, 1),
+                               executed_ops_source=os.path.relpath(QUANT_PROFILE, ROOT))
     cpu = None
     if not args.no_cpu:
         import oracle
@@ -821,7 +821,7 @@ def bench_gptq(args, mq, synth, torch, np, dev):
     widths, lam = (3, 4, 8), (1.0, 1.0, 1.0)
     g = torch.Generator(device=dev)
     g.manual_seed(777)
-    table, tot_w, tot_t, tot_fl = {}, 0.0, 0.0, 0.0
+    table, tot_w, tot_t, tot_ops = {}, 0.0, 0.0, 0.0
     for (N, K) in ((4096, 4096), (11008, 4096), (4096, 11008)):
         L = synth.make_layer_device(N, K, 1, seed=8100 + N, device=dev, want_x=False)
         W = torch.randn((N, K), generator=g, device=dev, dtype=torch.float32) * 0.02
@@ -845,25 +845,23 @@ def bench_gptq(args, mq, synth, torch, np, dev):
             e1.record()
             torch.cuda.synchronize()
             t = e0.elapsed_time(e1) * 1e-3                      # the last repetition is reported
-        # algorithmic flops: Algorithm 1's brute force per weight (256 x (6|R| + 1)), the error (3|R| + 1 per weight)
-        # and the updates (every weight receives one multiply and one subtract from each earlier column: N K (K-1))
-        fl = N * K * (256.0 * (6 * len(widths) + 1) + 3 * len(widths) + 1) + float(N) * K * (K - 1)
+        ops = gptq_ops(N, K, len(widths))
         table[f"{N}x{K}"] = {"ms": round(t * 1e3, 2), "Mweights_per_s": round(N * K / t / 1e6, 1),
-                             "us_per_column": round(t / K * 1e6, 2), "TFLOPs": round(fl / t / 1e12, 1)}
+                             "us_per_column": round(t / K * 1e6, 2), "T_lane_ops_per_s": round(ops / t / 1e12, 1)}
         tot_w += N * K
         tot_t += t
-        tot_fl += fl
+        tot_ops += ops
         del W, Wc, Q, U, L
     out = _base_line("MatGPTQ column loop (Algorithm 2) throughput, R = {3,4,8}", tot_w / tot_t / 1e9, "Gweights/s", args,
                      tot_t * 1e3, "Llama-2-7B layer shapes (4096x4096, 11008x4096, 4096x11008), fp32 weights, group 128, "
                      "block 128, c = 8, R = {3,4,8}, lambda = 1; Cholesky factor of the inverse Hessian given", {})
     out["dtype"] = "f32"
     out["table"] = table
-    ach = tot_fl / tot_t / 1e12
-    # a dependent chain over the columns: the figure is low by construction (latency per column step x K)
+    ach = tot_ops / tot_t / 1e12
+    # the decisions are a dependent chain over the columns (latency per column step x K), the update of the rest is vector work
     out["roofline"] = {"bound": "alu", "kernel": "mq::gptq_block_kernel<140, true> + mq::gptq_trailing_kernel<true>",
-                       "achieved": round(ach, 1), "peak": FP32_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
-                       "frac": round(ach / FP32_VECTOR_PEAK_TFLOPS, 4), "avg_launch_us": None,
+                       "achieved": round(ach, 1), "peak": VECTOR_LANE_OPS_PEAK_T, "unit": "T lane-op/s",
+                       "frac": round(ach / VECTOR_LANE_OPS_PEAK_T, 4), "avg_launch_us": None,
                        "algorithmic_flops_per_launch": None, "traffic": None}
     out["cpu_baseline"] = None
     print(json.dumps(out))
