@@ -345,7 +345,7 @@ def main() -> int:
                               "algorithmic_GB": round(m["bytes"] / 1e9, 3)}
         del m
         torch.cuda.empty_cache()
-        # a cut of configs[4]: the first 16 blocks of the Llama-3-70B-shaped stack (widths drawn for those blocks), at the
+        # a cut of the batched workload: the first 16 blocks of the Llama-3-70B-shaped stack (widths drawn for those blocks), at the
         # batch sizes of the three kernel families (vector ALUs, narrow and wide matrix-core kernels)
         cut70 = {}
         for Mb in (1, 8, 64):

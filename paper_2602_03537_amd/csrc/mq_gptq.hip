@@ -57,8 +57,8 @@ __device__ __forceinline__ uint32_t row_lowest_equal(int q, uint32_t bits, float
 //   * the block's weights live in registers, column k = 16 c + part in register c of lane `part` (after 16 columns the
 //     registers move up by one), so that a column's weight reaches its row in one DPP broadcast;
 //   * the block of U lives in LDS; 16 steps are straight-line code, so that its values are read well ahead.
-// 4096 rows x 4096 columns, R = {3,4,8}: 44 us a block = 0.34 us a step, of about 145 instructions of one wave per SIMD (160 us
-// with all 256 candidates over 64 lanes and the weights in LDS); the whole loop 6.85 -> 2.98 ms.
+// 4096 rows x 4096 columns, R = {3,4,8}: 43 - 45 us a block = 0.34 us a step, of about 145 instructions of one wave per SIMD (160 us
+// with all 256 candidates over 64 lanes and the weights in LDS); the whole loop 6.85 -> 2.95 ms.
 template <uint32_t MASK, bool ALL>
 __global__ __launch_bounds__(64 * kGptqMaxWaves, 4) void gptq_block_kernel(const float *__restrict__ W, int64_t ldw, int64_t N, int64_t i0,
                                                           int B, const float *__restrict__ U, int64_t ldu,

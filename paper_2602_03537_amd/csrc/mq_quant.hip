@@ -2,9 +2,10 @@
 // q in 0..255 that minimises
 //     E(q) = sum_{r in R} lambda_r * (w - scale * (S(q, r) - zero))^2,      S = Eq. 1 (Section 2)
 // (arithmetic, and why |R| + 1 candidates decide it bit for bit: mq_code_search.h).
-// One lane owns VEC consecutive weights of a row (same group: same scale and zero).  Bound by the vector ALUs: 142
-// operations a weight for R = {3,4,8}, most of them fp32.  4096 x 4096: 40.9 us (2.1 TB/s), against 494 us with all 256
-// candidates (about 2000 operations a weight); a plain copy of as many bytes would take 17 us.
+// One lane owns VEC consecutive weights of a row (same group: same scale and zero).  4096 x 4096, R = {3,4,8}: 40.3 us a call in long
+// runs (2.1 TB/s; 48.6 five at a time), against 494 (599) with all 256 candidates; a plain copy of as many bytes would take 17 us.  142
+// vector instructions a weight, most of them fp32, fill 63 % of the issue cycles at this size (73 % at 4096 x 11008): a lane loads
+// once, works through one dependent chain and is done, so the rest is waiting at the two ends of short waves.
 #include "mq_code_search.h"
 #include "mq_internal.h"
 
