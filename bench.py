@@ -859,7 +859,7 @@ def bench_gptq(args, mq, synth, torch, np, dev):
     out["table"] = table
     ach = tot_ops / tot_t / 1e12
     # the decisions are a dependent chain over the columns (latency per column step x K), the update of the rest is vector work
-    out["roofline"] = {"bound": "alu", "kernel": "mq::gptq_block_kernel<140, true> + mq::gptq_trailing_kernel<true>",
+    out["roofline"] = {"bound": "alu", "kernel": "mq::gptq_step_kernel<140, true>",
                        "achieved": round(ach, 1), "peak": VECTOR_LANE_OPS_PEAK_T, "unit": "T lane-op/s",
                        "frac": round(ach / VECTOR_LANE_OPS_PEAK_T, 4), "avg_launch_us": None,
                        "algorithmic_flops_per_launch": None, "traffic": None}

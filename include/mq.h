@@ -223,14 +223,15 @@ mq_status mq_quant_matgptq(const float *W, int64_t ldw, int64_t N, int64_t ncols
  * zero-offset are inputs fixed before the loop.  Arithmetic: binary32, every operation rounded on
  * its own, error terms added over r ascending, then / |R|, then / U[j,j]; each update is
  * w - (E * U[j,k]), applied in ascending j (the result does not depend on `block`).
- *   W       : device, fp32 [N, K], row stride ldw; OVERWRITTEN (working copy of the loop)
+ *   W       : device, fp32 [N, K], row stride ldw; OVERWRITTEN (working copy of the loop; the errors E take the place of
+ *             columns that are done)
  *   U       : device, fp32 [K, K], row stride ldu; only the upper triangle is read
  *   scales, zeros : device, fp16 [N, K/group] row-major (NOT tiled)
  *   lambda  : HOST, 8 floats as for mq_quant_matgptq
- *   block   : 16, 32, 64 or 128 (the paper's B)
+ *   block   : 16, 32, 64 or 128 (the paper's B; the result does not depend on it, and the loop takes 128 columns at a time)
  *   Q       : device, uint8 [N, K], row stride ldq
  *   ws      : device, 4-byte aligned, ws_bytes >= mq_matgptq_workspace_bytes(N, block)
- * Enqueues 2 * K / block - 1 launches on `stream`; rows run in parallel, columns in sequence.
+ * Enqueues K / 128 launches on `stream`; rows run in parallel, columns in sequence.
  * Errors: NULL, BAD_R, BAD_SHAPE, BAD_GROUP, ALIGN, BUF_TOO_SMALL, HIP. */
 size_t mq_matgptq_workspace_bytes(int64_t N, int block);
 mq_status mq_matgptq_quantize(float *W, int64_t ldw, int64_t N, int64_t K, const float *U, int64_t ldu,

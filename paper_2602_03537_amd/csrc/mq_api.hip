@@ -514,8 +514,7 @@ mq_status mq_matgptq_quantize(float *W, int64_t ldw, int64_t N, int64_t K, const
         return MQ_ERR_ALIGN;
     if (ws_bytes < mq_matgptq_workspace_bytes(N, block)) return MQ_ERR_BUF_TOO_SMALL;
     return launch_gptq(W, ldw, N, K, U, ldu, reinterpret_cast<const _Float16 *>(scales),
-                       reinterpret_cast<const _Float16 *>(zeros), lambda, block, Q, ldq, static_cast<float *>(ws),
-                       (hipStream_t)stream) == hipSuccess
+                       reinterpret_cast<const _Float16 *>(zeros), lambda, Q, ldq, (hipStream_t)stream) == hipSuccess
                ? MQ_OK
                : MQ_ERR_HIP;
 }

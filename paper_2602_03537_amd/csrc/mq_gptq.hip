@@ -1,26 +1,40 @@
 // The MatGPTQ column loop (Algorithm 2 of the paper's appendix), from the point where U, the
 // upper-triangular Cholesky factor of the inverse Hessian, is given.  Rows of W are independent of
 // each other; columns are strictly sequential (each column's code depends on every earlier
-// column's error), so the work is cut as the listing cuts it:
+// column's error).  One launch per 128 columns, with two kinds of workgroups:
 //
-//   gptq_block_kernel    : walks the B columns of a block for the rows of one workgroup: Algorithm 1
-//                          on the current weight (mq_code_search.h), the error averaged over R and
-//                          divided by U[j,j], rank-1 update of the block's remaining columns;
-//   gptq_trailing_kernel : W[:, i+B:] -= E @ U[i:i+B, i+B:], eight rows x four columns per lane.
+//   decide : walks the 128 columns of block k for 16 rows: first what block k - 1 owes them, then column by column
+//            Algorithm 1 on the current weight (mq_code_search.h), the error averaged over R and
+//            divided by U[j,j], rank-1 update of the block's remaining columns;
+//   update : W[:, after block k] -= E @ U[block k - 1, after block k], for the errors of the block before.
+//
+// The two touch different columns, so the update of one block runs beside the decisions of the next, which are a serial
+// chain that leaves half of a SIMD's issue slots free (4096 x 4096, R = {3,4,8}: 2.95 ms with the two one after the other, 2.22 now:
+// 43 us a block for the decisions, 5 for what they wait for first, 51 - 124 with the update beside them).  E of a block takes the
+// place of the block's columns in W, which nothing reads any more.
 //
 // Every rounding decides later codes, so the arithmetic is fixed: binary32, each operation
 // rounded on its own (no contraction), the error sum over r ascending as ((w - D_r1) + (w - D_r2))
 // + ..., then / |R|, then / U[j,j]; an update is w = w - (E * U[j,k]); the update of the rest is
-// applied as the same rank-1 terms in ascending j, so results do not depend on B.
+// applied as the same rank-1 terms in ascending j, so results do not depend on where blocks begin: whatever
+// block size a caller asks for, blocks are kBlock columns.
 #include "mq_code_lanes.h"
-#include "mq_internal.h"
-#include "mq_static_for.h"
+#include "mq_device.h"
 
 namespace mq {
 
-constexpr int kGptqMaxBlock = 128;
-constexpr int kTrailRows = 8;
-constexpr int kGptqMaxWaves = 8;  // of a workgroup of the block kernel
+constexpr int kBlock = kGroup;                   // columns of a block
+constexpr int kStepWaves = 4;                    // of a workgroup of either kind
+constexpr int kDecideRows = kStepWaves * 64 / kRowLanes;
+constexpr int kWaveRows = 64, kWaveCols = 16;    // of W that a wave updates
+constexpr int kUpdateCols = kStepWaves * kWaveCols;
+constexpr int kChunks = kBlock / kRowLanes;      // of 16 columns
+// The upper triangle of U's block in LDS, in chunks of 16 rows: chunk c holds its rows' columns from 16 c on
+constexpr int tri_width(int c) { return kBlock - kRowLanes * c; }
+constexpr int tri_base(int c) { return kRowLanes * (kBlock * c - kRowLanes / 2 * c * (c - 1)); }
+constexpr int kTri = tri_base(kChunks) + kBlock;  // and what the last rows' reads run over
+static_assert(kDecideRows * (kBlock + 4) <= kTri, "the workgroup's weights pass through the room of the triangle");
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 template <int CTRL> __device__ __forceinline__ uint32_t dpp_u(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xf, 0xf, true);
@@ -50,90 +64,154 @@ __device__ __forceinline__ uint32_t row_lowest_equal(int q, uint32_t bits, float
     }
     return (uint32_t)q;
 }
-// The 128 columns of a block for the rows of one workgroup.  What bounds it is the serial chain of the column steps
+// What the errors of the block before take from a workgroup's 16 rows of block k, its 128 terms in order, 32 columns per wave.
+// Here it is the number of instructions of a lone wave that counts, so the products come from the matrix core:
+// v_mfma_f32_16x16x1 with an addend of -0 leaves a product as a multiplication rounds it (subnormals, infinities and the sign of a zero
+// included), 1024 of them in one instruction; its four blocks are two terms times two blocks of 16 columns.  The result goes to
+// `out`, kDecideRows rows of kBlock + 4 columns in LDS.  4 - 6 us a launch; 18 with U's rows through LDS and a multiplication each.
+__device__ __forceinline__ void cross_update(const float *W, int64_t ldw, int64_t N, int64_t i0, int64_t n0, const float *U, int64_t ldu,
+                                             float *out) {
+#pragma clang fp contract(off)
+    const int lane = threadIdx.x & 63, col0 = (threadIdx.x >> 6) * 32;
+    constexpr int JC = 32;  // terms whose operands are fetched together
+    struct Terms {
+        float e[JC / 4], u[JC / 2];
+    };
+    const int quarter = lane >> 4;  // of the first operand: terms 0, 2, 1, 3 of each four
+    const int64_t er = n0 + (lane & 15);
+    const float *esrc = W + (er < N ? er : N - 1) * ldw + i0 - kBlock + ((quarter >> 1) | ((quarter & 1) << 1));
+    const float *usrc = U + (i0 - kBlock + (lane >> 5)) * ldu + i0 + col0 + (lane & 31);
+    auto fetch = [&](Terms &t, int j) {
+#pragma unroll
+        for (int i = 0; i < JC / 4; ++i) t.e[i] = esrc[j + 4 * i];
+#pragma unroll
+        for (int i = 0; i < JC / 2; ++i) t.u[i] = usrc[(int64_t)(j + 2 * i) * ldu];
+    };
+    Terms t[2];
+    fetch(t[0], 0);
+    float w[8];  // register v: row 4 (lane / 16) + v % 4, column 16 (v / 4) + lane % 16
+#pragma unroll
+    for (int v = 0; v < 8; ++v) {
+        const int64_t row = n0 + 4 * quarter + v % 4;
+        w[v] = W[(row < N ? row : N - 1) * ldw + i0 + col0 + 16 * (v / 4) + (lane & 15)];
+    }
+    f32x16 none;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) none[v] = -0.f;
+    auto apply = [&](const Terms &t) {
+        static_for<JC / 4>([&](auto ic) {
+#pragma clang fp contract(off)
+            constexpr int i = ic;
+            const f32x16 p0 = __builtin_amdgcn_mfma_f32_16x16x1f32(t.e[i], t.u[2 * i], none, 1, 0, 0);
+            const f32x16 p1 = __builtin_amdgcn_mfma_f32_16x16x1f32(t.e[i], t.u[2 * i + 1], none, 1, 1, 0);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) w[v % 8] = w[v % 8] - p0[v];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) w[v % 8] = w[v % 8] - p1[v];
+        });
+    };
+#pragma unroll 1
+    for (int j = 0; j < kBlock; j += 2 * JC) {
+        fetch(t[1], j + JC);
+        apply(t[0]);
+        fetch(t[0], j + 2 * JC < kBlock ? j + 2 * JC : 0);
+        apply(t[1]);
+    }
+#pragma unroll
+    for (int v = 0; v < 8; ++v) out[(4 * quarter + v % 4) * (kBlock + 4) + col0 + 16 * (v / 4) + (lane & 15)] = w[v];
+}
+
+// Decisions for the 128 columns of a block, kDecideRows rows per workgroup.  What bounds it is the serial chain of the column steps
 // (a column's code decides the next column's weight), so a step is made short and everything else is kept off it:
 //   * kRowLanes lanes share a row and evaluate the handful of candidates that can win (mq_code_search.h) side by side, each with
 //     the error it would propagate (two correctly rounded divisions, beside the chain that compares the E); DPP steps pick the winner;
-//   * the block's weights live in registers, column k = 16 c + part in register c of lane `part` (after 16 columns the
-//     registers move up by one), so that a column's weight reaches its row in one DPP broadcast;
-//   * the block of U lives in LDS; 16 steps are straight-line code, so that its values are read well ahead.
-// 4096 rows x 4096 columns, R = {3,4,8}: 43 - 45 us a block = 0.34 us a step, of about 145 instructions of one wave per SIMD (160 us
-// with all 256 candidates over 64 lanes and the weights in LDS); the whole loop 6.85 -> 2.95 ms.
+//   * the block's weights live in registers (after 16 columns they move up by one), so that a column's weight reaches its row in one
+//     DPP broadcast;
+//   * the upper triangle of the block of U lives in LDS (37 KB: the rest of a compute unit's LDS is for the workgroups that update);
+//     16 steps are straight-line code, so that its values are read well ahead.
 template <uint32_t MASK, bool ALL>
-__global__ __launch_bounds__(64 * kGptqMaxWaves, 4) void gptq_block_kernel(const float *__restrict__ W, int64_t ldw, int64_t N, int64_t i0,
-                                                          int B, const float *__restrict__ U, int64_t ldu,
-                                                          const _Float16 *__restrict__ scales,
-                                                          const _Float16 *__restrict__ zeros, int64_t G,
-                                                          const QuantLambda lam, float n_widths,
-                                                          uint8_t *__restrict__ Q, int64_t ldq, float *__restrict__ E) {
+__device__ __forceinline__ void decide_block(float *W, int64_t ldw, int64_t N, int64_t i0, int64_t blk, const float *U, int64_t ldu,
+                                             const _Float16 *__restrict__ scales, const _Float16 *__restrict__ zeros, int64_t G,
+                                             const QuantLambda &lam, float n_widths, uint8_t *__restrict__ Q, int64_t ldq,
+                                             float *ul, float2 *diag) {
 #pragma clang fp contract(off)
-    constexpr int NC = kGptqMaxBlock / kRowLanes;
-    __shared__ float ul[kGptqMaxBlock * kGptqMaxBlock + kGptqMaxBlock];  // row j of the block at ul + 128 j; padding
-    __shared__ float rd[kGptqMaxBlock];                  // 1 / U[j,j]
+    constexpr int NC = kChunks;
     const int tid = threadIdx.x;
     const int part = tid & (kRowLanes - 1);
-    const int64_t n = (int64_t)blockIdx.x * (blockDim.x / kRowLanes) + tid / kRowLanes;
+    const int64_t n = blk * kDecideRows + tid / kRowLanes;
     const bool valid = n < N;
     const int64_t nr = valid ? n : N - 1;  // idle rows shadow the last one and store nothing
-    // a block never straddles a group (B divides the group size and blocks start at multiples of B)
     const int64_t g = i0 / kGroup;
     const float s_in = (float)scales[nr * G + g];
     const float z = (float)zeros[nr * G + g];
     // a row with a negative scale is decided on its negative: every step of the loop is odd in (w, scale)
     const float sign = code_sign(s_in), s = s_in * sign;
-    float wreg[NC];
+    float wreg[NC];  // column 16 c + part in register c of lane `part`
+    if (i0 > 0) {  // uniform
+        cross_update(W, ldw, N, i0, blk * kDecideRows, U, ldu, ul);
+        __syncthreads();
 #pragma unroll
-    for (int c = 0; c < NC; ++c) wreg[c] = c * kRowLanes < B ? W[nr * ldw + i0 + c * kRowLanes + part] : 0.f;
+        for (int c = 0; c < NC; ++c) wreg[c] = ul[tid / kRowLanes * (kBlock + 4) + c * kRowLanes + part];
+        __syncthreads();
+    } else {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) wreg[c] = W[nr * ldw + i0 + c * kRowLanes + part];
+    }
     const float inv_s = 1.f / s, z1 = z + 1.f;
     const LaneCandidate lc = lane_candidate<MASK>(part);
     const bool grid_ok = code_grid_normal(s, z);
     const bool runs = !ALL && lam.v[kC - 1] == 0.f;  // uniform
     const float nw = ALL ? (float)popc8(MASK) : n_widths, inv_nw = 1.f / nw;
     {
-        // the upper triangle, columns fastest (B is 16, 32, 64 or 128: a thread keeps its column), sixteen loads in flight
-        // per thread; what lies below it is not read from U, and not used
-        const int col = tid & (B - 1), row0 = tid / B, rows = blockDim.x / B;
+        // the upper triangle, columns fastest (a thread keeps its column; what lies below the diagonal is not read from U, and not
+        // used), all loads of a thread in flight
+        const int col = tid & (kBlock - 1), row0 = tid / kBlock;
         const float *src = U + i0 * ldu + i0 + col;
-        for (int j0 = row0; j0 < B; j0 += 16 * rows) {
-            float v[16];
+        static_for<4>([&](auto q) {
+            constexpr int c0 = 2 * q;
+            float v[kRowLanes];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int j = j0 + i * rows;
+            for (int i = 0; i < kRowLanes; ++i) {
+                const int j = c0 * kRowLanes + 2 * i + row0;
                 v[i] = src[(int64_t)(j < col ? j : col) * ldu];
             }
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int j = j0 + i * rows;
-                if (j < B) ul[j * kGptqMaxBlock + col] = v[i];
+            for (int i = 0; i < kRowLanes; ++i) {
+                constexpr int half = kRowLanes / 2;
+                const int c = c0 + i / half, j = 2 * (i % half) + row0;  // row j of chunk c
+                if (col >= kRowLanes * c) ul[tri_base(c) + j * tri_width(c) + col - kRowLanes * c] = v[i];
             }
-        }
+        });
     }
     bool u_ok = true;
-    if (tid < B) {
+    if (tid < kBlock) {
         const float ujj = U[(i0 + tid) * ldu + i0 + tid];
-        rd[tid] = 1.f / ujj;
+        diag[tid] = make_float2(ujj, 1.f / ujj);
         u_ok = divisor_plain(ujj);
     }
     const bool fast_ok = grid_ok & (__syncthreads_and(u_ok) != 0);
     // (not where W is loaded: the loads of U would wait for it, 1.5 us a launch)
 #pragma unroll
     for (int c = 0; c < NC; ++c) wreg[c] *= sign;
-    for (int c0 = 0; c0 < B; c0 += kRowLanes) {
+#pragma unroll 1
+    for (int c0 = 0; c0 < NC; ++c0) {
         // 16 columns, one of them per lane of a row in wreg[0]; register k holds this lane's column 16 k further on.
-        // (Past the block's end the registers hold nothing of use, and the rows of U run into the padding.)
-        const float *urows = ul + c0 * kGptqMaxBlock + c0;
+        // (Past the block's end the registers hold nothing of use, and the rows of U run into the rows below and the padding.)
+        const int width = kBlock - kRowLanes * c0;
+        const float2 *dg = diag + c0 * kRowLanes;
         float keep_err = 0.f;
         uint32_t keep_q = 0;
-        float ur[2][NC], ujj[2], rjj[2];  // row jj of these 16 columns and row jj + 1, on its way
-        int u_off = part;
+        float ur[2][NC];  // row jj of these 16 columns and row jj + 1, on its way
+        float2 ujj[2];    // U[j,j] and its reciprocal
+        int u_off = kRowLanes * (kBlock * c0 - kRowLanes / 2 * c0 * (c0 - 1)) + part;
         auto fetch_u = [&](auto jc) {
             constexpr int jj = jc;
             // (opaque: else the rows of all 16 steps are read at once, into more registers than there are)
             asm volatile("" : "+v"(u_off));
-            ujj[jj % 2] = urows[jj * kGptqMaxBlock + jj];
-            rjj[jj % 2] = rd[c0 + jj];
+            ujj[jj % 2] = dg[jj];
 #pragma unroll
-            for (int k = 0; k < NC; ++k) ur[jj % 2][k] = urows[jj * kGptqMaxBlock + k * kRowLanes + u_off];
+            for (int k = 0; k < NC; ++k) ur[jj % 2][k] = ul[k * kRowLanes + u_off];
+            u_off += width;
         };
         fetch_u(IntC<0>{});
         static_for<kRowLanes>([&](auto jc) {
@@ -142,7 +220,7 @@ __global__ __launch_bounds__(64 * kGptqMaxWaves, 4) void gptq_block_kernel(const
             if constexpr (jj + 1 < kRowLanes) fetch_u(IntC<jj + 1>{});
             const float w = dpp_f<0x150 + jj>(wreg[0]);  // row_newbcast: column jj's weight, to all lanes of the row
             const int Uc = code_estimate(w, inv_s, z1);
-            const LaneDecision d = lane_decision<MASK, ALL>(lc, Uc, w, s, z, lam, runs, fast_ok, nw, inv_nw, ujj[jj % 2], rjj[jj % 2]);
+            const LaneDecision d = lane_decision<MASK, ALL>(lc, Uc, w, s, z, lam, runs, fast_ok, nw, inv_nw, ujj[jj % 2].x, ujj[jj % 2].y);
             uint32_t Eb = d.bits, key = d.key;
             float err = d.err;
             const bool bad = d.bad;
@@ -162,7 +240,7 @@ __global__ __launch_bounds__(64 * kGptqMaxWaves, 4) void gptq_block_kernel(const
                 float e2 = 0.f, a2 = 0.f, e8_2;
                 bool any2 = false;
                 code_terms<MASK, ALL>(qw, w, s, z, lam, e2, a2, any2, e8_2);
-                err = (a2 / nw) / ujj[jj % 2];
+                err = (a2 / nw) / ujj[jj % 2].x;
             }
             keep_q = part == jj ? qw : keep_q;
             keep_err = part == jj ? err : keep_err;
@@ -174,128 +252,113 @@ __global__ __launch_bounds__(64 * kGptqMaxWaves, 4) void gptq_block_kernel(const
             }
         });
         if (valid) {
-            Q[n * ldq + i0 + c0 + part] = (uint8_t)keep_q;
-            E[n * B + c0 + part] = keep_err * sign;
+            Q[n * ldq + i0 + c0 * kRowLanes + part] = (uint8_t)keep_q;
+            W[n * ldw + i0 + c0 * kRowLanes + part] = keep_err * sign;
         }
 #pragma unroll
         for (int k = 0; k + 1 < NC; ++k) wreg[k] = wreg[k + 1];
     }
 }
 
-// W[n, c0 + k] -= sum_j E[n, j] * U[i0 + j, c0 + k], the terms subtracted one by one in ascending j.
-// A wave owns kTrailRows rows x 256 columns (four consecutive columns per lane): per j one 16-byte
-// load of U per lane, the E values are the same for the whole wave (scalar loads), and 2 x 4 x
-// kTrailRows vector operations, so the kernel is bound by the vector ALUs, not by loads.
-// VEC4 needs c0, ldw, ldu multiples of 4 and 16-byte aligned W and U; otherwise one column per lane.
-template <bool VEC4>
-__global__ __launch_bounds__(64) void gptq_trailing_kernel(float *__restrict__ W, int64_t ldw, int64_t N, int64_t c0,
-                                                           int64_t ncols, const float *__restrict__ E, int B,
-                                                           const float *__restrict__ U, int64_t ldu, int64_t i0,
-                                                           int64_t kblocks) {
+// W[n, c0 + k] -= sum_j E[n, j] * U[j0 + j, c0 + k] over the 128 terms of a block, one by one in ascending j, for a wave's
+// kWaveRows rows and kWaveCols columns; E is W's columns j0 .. j0 + 127.  A row per lane: its error of a term is one register, the
+// 16 values of U are scalar registers, and nothing but multiplications and subtractions is issued: the vector ALUs bound it (4096 x
+// 4096, first update: 114 us alone, 80 without its loads and stores, 65 at the rate of independent instructions).
+// Measured and not kept: products by v_mfma_f32_16x16x1, as in cross_update (as fast alone, but the deciding waves beside it wait until
+// such an instruction, all of its 36 cycles, is through: the loop 2.43 ms against 2.22); errors spread over 16 lanes by DPP
+// operands (twice the time of a plain multiplication: 2.93); W and E through LDS (2.22); two rows a lane (2.27); several tiles per
+// workgroup with the next one's weights on their way (2.35 - 5.9: long workgroups leave the chip unevenly filled); blocks of
+// terms put off and taken two or four at a time (2.47, 3.08, for the same reason).
+__device__ __forceinline__ void update_block(float *W, int64_t ldw, int64_t N, int64_t j0, int64_t c0, int64_t n0, const float *U,
+                                             int64_t ldu) {
 #pragma clang fp contract(off)
-    constexpr int CPT = VEC4 ? 4 : 1;  // columns per lane
-    const int64_t rb = blockIdx.x / kblocks;
-    const int64_t k = ((blockIdx.x - rb * kblocks) * 64 + threadIdx.x) * CPT;
-    const int64_t n0 = rb * kTrailRows;
-    const bool in = k < ncols;  // ncols is a multiple of CPT on the VEC4 path
-    const int64_t kc = in ? k : 0;
-    float w[kTrailRows][CPT];
-    int64_t row[kTrailRows];
+    constexpr int C = kWaveCols, JE = 8, JU = 2;  // terms whose errors / rows of U are fetched together
+    const int64_t n = n0 + (threadIdx.x & 63);
+    float *row = W + (n < N ? n : N - 1) * ldw;
+    float e[2][JE], w[C];
+    auto fetch_e = [&](float (&v)[JE], int j) { __builtin_memcpy(v, row + j0 + j, sizeof(v)); };
+    const cptr32 usrc = as_const(U + j0 * ldu + c0);
+    uint32_t u[2][JU][C];
+    auto fetch_u = [&](uint32_t (&v)[JU][C], int j) {
 #pragma unroll
-    for (int i = 0; i < kTrailRows; ++i) {
-        row[i] = n0 + i < N ? n0 + i : N - 1;  // uniform over the wave
-        const float *src = W + row[i] * ldw + c0 + kc;
-        if constexpr (VEC4) {
-            const float4 v = *reinterpret_cast<const float4 *>(src);
-            w[i][0] = v.x; w[i][1] = v.y; w[i][2] = v.z; w[i][3] = v.w;
-        } else {
-            w[i][0] = src[0];
-        }
-    }
-    const float *u = U + i0 * ldu + c0 + kc;
-    // eight terms at a time: their loads (one 16-byte piece of U per lane and term, eight consecutive E values
-    // per row through the scalar unit) are all issued before the first of them is used
-    constexpr int JC = 8;  // B is a multiple of 16
-    for (int j0 = 0; j0 < B; j0 += JC) {
-        float uv[JC][CPT];
+        for (int i = 0; i < JU; ++i)
 #pragma unroll
-        for (int jj = 0; jj < JC; ++jj) {
-            if constexpr (VEC4) {
-                const float4 v = *reinterpret_cast<const float4 *>(u + (int64_t)(j0 + jj) * ldu);
-                uv[jj][0] = v.x; uv[jj][1] = v.y; uv[jj][2] = v.z; uv[jj][3] = v.w;
-            } else {
-                uv[jj][0] = u[(int64_t)(j0 + jj) * ldu];
-            }
-        }
-        float ev[kTrailRows][JC];
+            for (int c = 0; c < C; ++c) v[i][c] = usrc[(int64_t)(j + i) * ldu + c];
+    };
+    fetch_e(e[0], 0);
+    fetch_u(u[0], 0);
+    __builtin_memcpy(w, row + c0, sizeof(w));
+    auto eight = [&](const float (&ev)[JE], int j) {
+        static_for<JE / JU>([&](auto qc) {
+            constexpr int q = qc;
+            const int next = j + (q + 1) * JU;
+            // scalar loads come back in any order: these rows have to be here before the next are asked for
 #pragma unroll
-        for (int i = 0; i < kTrailRows; ++i)
+            for (int i = 0; i < JU; ++i) asm volatile("" : "+s"(u[q % 2][i][0]));
+            __builtin_amdgcn_sched_barrier(0);
+            fetch_u(u[(q + 1) % 2], next < kBlock ? next : 0);
+            __builtin_amdgcn_sched_barrier(0);
+            static_for<JU>([&](auto jc) {
+#pragma clang fp contract(off)
+                constexpr int jj = q * JU + jc;
 #pragma unroll
-            for (int jj = 0; jj < JC; ++jj) ev[i][jj] = E[row[i] * B + j0 + jj];
-#pragma unroll
-        for (int jj = 0; jj < JC; ++jj)
-#pragma unroll
-            for (int i = 0; i < kTrailRows; ++i)
-#pragma unroll
-                for (int c = 0; c < CPT; ++c) {
-                    const float p = ev[i][jj] * uv[jj][c];
-                    w[i][c] = w[i][c] - p;
+                for (int c = 0; c < C; ++c) {
+                    const float p = ev[jj] * __builtin_bit_cast(float, u[q % 2][jc][c]);
+                    w[c] = w[c] - p;
                 }
+            });
+        });
+    };
+#pragma unroll 1
+    for (int j = 0; j < kBlock; j += 2 * JE) {
+        fetch_e(e[1], j + JE);
+        eight(e[0], j);
+        fetch_e(e[0], j + 2 * JE < kBlock ? j + 2 * JE : 0);
+        eight(e[1], j + JE);
     }
-    if (!in) return;
-#pragma unroll
-    for (int i = 0; i < kTrailRows; ++i) {
-        if (n0 + i < N) {
-            float *dst = W + (n0 + i) * ldw + c0 + k;
-            if constexpr (VEC4)
-                *reinterpret_cast<float4 *>(dst) = make_float4(w[i][0], w[i][1], w[i][2], w[i][3]);
-            else
-                dst[0] = w[i][0];
-        }
-    }
+    if (n < N) __builtin_memcpy(row + c0, w, sizeof(w));
 }
 
-// Waves per workgroup (four rows each): four up to 8192 rows, which is two workgroups per compute unit, and all that a
-// workgroup's 67 KB of LDS let in; eight beyond, so that twice the rows share a compute unit's LDS and are resident at one time
-// (R = {3,4,8}, us a block: 16384 rows 97, with four waves 112; 20480 rows 132 and 141).  Sixteen would leave one workgroup per compute unit
-// (at most 128 registers a lane: 16 waves), the same rows in coarser pieces: 20480 rows 162, 65536 rows 328 against 323, and {2,3,4,6,8} 233 against 176.
-inline int gptq_block_waves(int64_t N) { return N <= 8192 ? 4 : kGptqMaxWaves; }
+// Launch k of a call: workgroups below n_decide take the decisions of block k, the others the update by block k - 1 of the columns
+// after block k.  The deciding ones come first, so that each finds a compute unit of its own, and ask for the issue slots
+// they can use.
+template <uint32_t MASK, bool ALL>
+__global__ __launch_bounds__(64 * kStepWaves, 4) void gptq_step_kernel(float *W, int64_t ldw, int64_t N, int64_t i0, const float *U,
+                                                                       int64_t ldu, const _Float16 *__restrict__ scales,
+                                                                       const _Float16 *__restrict__ zeros, int64_t G,
+                                                                       const QuantLambda lam, float n_widths,
+                                                                       uint8_t *__restrict__ Q, int64_t ldq, unsigned n_decide,
+                                                                       unsigned col_tiles) {
+    __shared__ __attribute__((aligned(16))) float ul[kTri];
+    __shared__ float2 diag[kBlock];
+    if (blockIdx.x < n_decide) {
+        __builtin_amdgcn_s_setprio(3);
+        decide_block<MASK, ALL>(W, ldw, N, i0, blockIdx.x, U, ldu, scales, zeros, G, lam, n_widths, Q, ldq, ul, diag);
+    } else {
+        const unsigned t = blockIdx.x - n_decide, rt = t / col_tiles, ct = t - rt * col_tiles;
+        const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        update_block(W, ldw, N, i0 - kBlock, i0 + kBlock + (int64_t)ct * kUpdateCols + wave * kWaveCols, (int64_t)rt * kWaveRows, U, ldu);
+    }
+}
 
 template <uint32_t MASK, bool ALL>
 static hipError_t launch_gptq_mask(float *W, int64_t ldw, int64_t N, int64_t K, const float *U, int64_t ldu,
                                    const _Float16 *scales, const _Float16 *zeros, const QuantLambda &lam, float n_widths,
-                                   int B, uint8_t *Q, int64_t ldq, float *E, hipStream_t s) {
-    const int64_t G = K / kGroup;
-    if (((K + 63) / 64) * ((N + kTrailRows - 1) / kTrailRows) > (int64_t)0x7fffffff) return hipErrorInvalidValue;
-    const int waves = gptq_block_waves(N), rows = waves * (64 / kRowLanes);
-    // B, K and the block starts are multiples of 16, so only the strides and base addresses decide
-    const bool vec4 = ldw % 4 == 0 && ldu % 4 == 0 && (reinterpret_cast<uintptr_t>(W) & 15) == 0 &&
-                      (reinterpret_cast<uintptr_t>(U) & 15) == 0;
-    for (int64_t i0 = 0; i0 < K; i0 += B) {
-        hipError_t e = launch((gptq_block_kernel<MASK, ALL>), dim3((unsigned)((N + rows - 1) / rows)), dim3(64 * waves), 0, s,
-                              W, ldw, N, i0, B, U, ldu, scales, zeros, G, lam, n_widths, Q, ldq, E);
+                                   uint8_t *Q, int64_t ldq, hipStream_t s) {
+    const int64_t n_decide = (N + kDecideRows - 1) / kDecideRows, row_tiles = (N + kWaveRows - 1) / kWaveRows;
+    if (n_decide + row_tiles * (K / kUpdateCols) > (int64_t)0x7fffffff) return hipErrorInvalidValue;
+    for (int64_t i0 = 0; i0 < K; i0 += kBlock) {
+        const int64_t col_tiles = i0 > 0 ? (K - i0 - kBlock) / kUpdateCols : 0;
+        hipError_t e = launch((gptq_step_kernel<MASK, ALL>), dim3((unsigned)(n_decide + row_tiles * col_tiles)), dim3(64 * kStepWaves),
+                              0, s, W, ldw, N, i0, U, ldu, scales, zeros, K / kGroup, lam, n_widths, Q, ldq, (unsigned)n_decide,
+                              (unsigned)col_tiles);
         if (e != hipSuccess) return e;
-        const int64_t c0 = i0 + B, ncols = K - c0;
-        if (ncols > 0) {
-            const int64_t rblocks = (N + kTrailRows - 1) / kTrailRows;
-            if (vec4) {
-                const int64_t kblocks = (ncols + 255) / 256;
-                e = launch(gptq_trailing_kernel<true>, dim3((unsigned)(kblocks * rblocks)), dim3(64), 0, s, W, ldw, N, c0,
-                           ncols, E, B, U, ldu, i0, kblocks);
-            } else {
-                const int64_t kblocks = (ncols + 63) / 64;
-                e = launch(gptq_trailing_kernel<false>, dim3((unsigned)(kblocks * rblocks)), dim3(64), 0, s, W, ldw, N, c0,
-                           ncols, E, B, U, ldu, i0, kblocks);
-            }
-            if (e != hipSuccess) return e;
-        }
     }
     return hipSuccess;
 }
 
 hipError_t launch_gptq(float *W, int64_t ldw, int64_t N, int64_t K, const float *U, int64_t ldu, const _Float16 *scales,
-                       const _Float16 *zeros, const float *lambda, int B, uint8_t *Q, int64_t ldq, float *E,
-                       hipStream_t s) {
+                       const _Float16 *zeros, const float *lambda, uint8_t *Q, int64_t ldq, hipStream_t s) {
     QuantLambda lam;
     uint32_t need = 0;
     int nw = 0;
@@ -308,14 +371,14 @@ hipError_t launch_gptq(float *W, int64_t ldw, int64_t N, int64_t K, const float 
     }
     const float n_widths = (float)nw;
     switch (quant_variant_mask(need)) {
-        case 0x80u: return launch_gptq_mask<0x80u, true>(W, ldw, N, K, U, ldu, scales, zeros, lam, n_widths, B, Q, ldq, E, s);
+        case 0x80u: return launch_gptq_mask<0x80u, true>(W, ldw, N, K, U, ldu, scales, zeros, lam, n_widths, Q, ldq, s);
         case 0x8Cu:
             if (need == 0x8Cu)
-                return launch_gptq_mask<0x8Cu, true>(W, ldw, N, K, U, ldu, scales, zeros, lam, n_widths, B, Q, ldq, E, s);
-            return launch_gptq_mask<0x8Cu, false>(W, ldw, N, K, U, ldu, scales, zeros, lam, n_widths, B, Q, ldq, E, s);
-        case 0xAEu: return launch_gptq_mask<0xAEu, false>(W, ldw, N, K, U, ldu, scales, zeros, lam, n_widths, B, Q, ldq, E, s);
+                return launch_gptq_mask<0x8Cu, true>(W, ldw, N, K, U, ldu, scales, zeros, lam, n_widths, Q, ldq, s);
+            return launch_gptq_mask<0x8Cu, false>(W, ldw, N, K, U, ldu, scales, zeros, lam, n_widths, Q, ldq, s);
+        case 0xAEu: return launch_gptq_mask<0xAEu, false>(W, ldw, N, K, U, ldu, scales, zeros, lam, n_widths, Q, ldq, s);
     }
-    return launch_gptq_mask<0xFFu, false>(W, ldw, N, K, U, ldu, scales, zeros, lam, n_widths, B, Q, ldq, E, s);
+    return launch_gptq_mask<0xFFu, false>(W, ldw, N, K, U, ldu, scales, zeros, lam, n_widths, Q, ldq, s);
 }
 
 }  // namespace mq

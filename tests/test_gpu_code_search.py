@@ -73,3 +73,23 @@ def test_uneven_lambdas(widths, lam):
     ref, _ = oracle.matgptq_quantize(W, U, s, z, 8, widths, lam, 128, 128, np.float32)
     got = mq.mq_matgptq_quantize(dev(W.copy()), dev(U), dev(s), dev(z), widths, lam).cpu().numpy()
     assert np.array_equal(got, ref), np.argwhere(got != ref)[:5]
+
+
+@pytest.mark.parametrize("N", [1, 15, 63, 65, 129])            # edges of the 16 rows that decide together and the 64 that are updated
+@pytest.mark.parametrize("K,block", [(256, 128), (640, 16)])   # one block of updates, and several
+@pytest.mark.parametrize("pad", [0, 3])                        # rows at any float's address
+def test_column_loop_update_edges(N, K, block, pad):
+    W = synth.make_weights(N, K, [105, N, K])
+    _, s, z = synth.quantize_parent(W)
+    U = _factor(K, 106) * np.float32(0.9)
+    W[0, 5::7] *= np.float32(1e-37)              # products and differences below the normal numbers
+    lower = U.copy()
+    lower[np.tril_indices(K, -1)] = np.nan       # only the upper triangle counts
+    Wd = torch.full((N, K + pad), float("nan"), device="cuda:0")
+    Wd[:, pad:] = dev(W)
+    Ud = torch.full((K, K + pad), float("nan"), device="cuda:0")
+    Ud[:, pad:] = dev(lower)
+    got = mq.mq_matgptq_quantize(Wd[:, pad:], Ud[:, pad:], dev(s), dev(z), (3, 4, 8), (1.0, 1.0, 1.0), block=block).cpu().numpy()
+    ref, _ = oracle.matgptq_quantize(W, U, s, z, 8, (3, 4, 8), (1.0, 1.0, 1.0), 128, block, np.float32)
+    assert np.array_equal(got, ref), np.argwhere(got != ref)[:5]
+    assert torch.isnan(Wd[:, :pad]).all()
