@@ -12,8 +12,9 @@ SOURCES = ["mq_api.hip", "mq_pack.hip", "mq_linear.hip", "mq_gemm.hip", "mq_wide
 FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument"]
-# mq_gptq.hip: the products that an MFMA leaves are subtracted by the vector ALUs at once, from vector registers
-EXTRA = {"mq_gptq.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+# Files whose matrix instructions' results go straight to vector instructions: keep them in vector registers
+_VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
+EXTRA = {"mq_gptq.hip": _VGPR_FORM, "mq_linear.hip": _VGPR_FORM}
 
 
 def build(verbose: bool = False) -> str:

@@ -27,12 +27,8 @@ mq_status check_shape(int64_t N, int64_t K, int group) {
 
 size_t counter_bytes(int64_t row_blocks) { return align_up((size_t)row_blocks * 4, kCounterBytesAlign); }
 bool use_mfma(int64_t M) { return M > kValuMaxM; }
-// A stack of packed layers at M = kValuMaxM runs on the matrix cores: measured on uniform stacks, four rows on the
-// vector ALUs take longer than five on the matrix cores at every width (1.34 against 1.02 ms at r = 2, 12 Llama-3-70B
-// blocks).  Single calls keep the vector-ALU kernels (their low-latency shape wins on one layer), and so do stacks
-// computed from the parent.  The "path batch" stands in for M wherever sizes and kernels are chosen.
-// A small stack (the few linears of a decoder block that share their input) keeps the vector-ALU kernels in their
-// low-latency shape, as a single call does.
+// The batch that a plan's workspace is laid out for: M, but for a stack of packed layers at M = kValuMaxM that is not small, which has the
+// layout of the next larger batch (its kernel once needed it).
 int64_t stack_path_m(int64_t M, bool from_parent, bool small) {
     return !from_parent && !small && M == kValuMaxM ? M + 1 : M;
 }
@@ -42,7 +38,7 @@ bool small_stack(const mq_layer *layers, int n_layers, int64_t M) {
     for (int i = 0; i < n_layers; ++i) tiles += pad_rows(layers[i].N) / kRowBlock * (layers[i].K / kGroup);
     return tiles <= 12288;
 }
-// column blocks the schedule sees: 1 (vector ALUs), 16-column chunks (narrow MFMA), passes (wide MFMA)
+// column blocks the schedule sees: 1 up to 16 rows, the wide kernel's passes above
 int64_t chunks(int64_t M) {
     return use_wide(M) ? wide_passes(M) : use_mfma(M) ? (M + kChunkCols - 1) / kChunkCols : 1;
 }
@@ -52,6 +48,8 @@ int slot_floats(int64_t M) {
            : use_mfma(M) ? kNarrowRowBlocks * 64 * kChunkCols
                          : 64 * (int)M;
 }
+// Shares of the schedule that part_bytes of partial sums hold slots for, row kernels
+int slots_in(size_t part_bytes, int64_t M) { return (int)(part_bytes / (2 * 64 * (size_t)vector_rows(M) * sizeof(float))); }
 size_t max_workers(int64_t M) {
     return use_wide(M)   ? (size_t)wide_max_groups(wide_chunks_per_pass(M))
            : use_mfma(M) ? (size_t)kMaxGroupsNarrow
@@ -62,7 +60,7 @@ size_t partial_bytes(int64_t M) { return max_workers(M) * 2 * (size_t)slot_float
 size_t xt_bytes(int64_t M, int64_t K, int) {
     if (use_wide(M)) return align_up((size_t)wide_chunks_padded(M) * (size_t)(K / kGroup) * kWideXtBlockBytes, 256);
     if (use_mfma(M)) return (size_t)(K / kGroup) * kNarrowXtBlockBytes;
-    return align_up((size_t)M * (size_t)K * 2, 256);  // vector-ALU path: bf16 activations converted to fp16
+    return align_up((size_t)M * (size_t)K * 2, 256);  // row kernels: bf16 activations converted to fp16
 }
 
 mq_status layer_status(const mq_layer &l, int64_t M) {
@@ -75,7 +73,7 @@ mq_status layer_status(const mq_layer &l, int64_t M) {
     // a chained layer reads x as the earlier layers leave it: there is no point before the launch at which bf16
     // activations could be converted for it
     if ((l.flags & MQ_X_AFTER_EARLIER) && (l.flags & MQ_X_BF16)) return MQ_ERR_UNSUPPORTED;
-    if (l.from_parent && use_mfma(M)) return MQ_ERR_UNSUPPORTED;  // slicing in registers: vector-ALU kernels only
+    if (l.from_parent && use_mfma(M)) return MQ_ERR_UNSUPPORTED;  // slicing in registers: row kernels only
     // the matrix-core paths move scales / zeros 16 bytes at a time
     const size_t meta_align = use_mfma(M) ? 16 : 2;
     if (!aligned(l.packed_W, 16) || !aligned(l.x, 4) || !aligned(l.scales_t, meta_align) ||
@@ -116,8 +114,8 @@ const _Float16 *sym_zero_line() {
 
 // xt: where the MFMA path keeps this layer's prepared activations (on the ALU path: the fp16 copy of bf16 activations)
 // sym_line: sym_zero_line() of the current device; needed (non-null) when the layer is symmetric
-// Mp: the path batch (== M except for stacks at M = kValuMaxM, see stack_path_m)
-LayerDesc make_desc(const mq_layer &l, int64_t M, int64_t Mp, uint64_t cost_start, int cnt_off, int job_start, void *xt,
+// Mp: the batch that the workspace is laid out for (see stack_path_m); rows: the row kernels serve it
+LayerDesc make_desc(const mq_layer &l, int64_t M, int64_t Mp, bool rows, uint64_t cost_start, int cnt_off, int job_start, void *xt,
                     const _Float16 *sym_line) {
     LayerDesc d{};
     d.Wp = static_cast<const uint4 *>(l.packed_W);
@@ -132,7 +130,7 @@ LayerDesc make_desc(const mq_layer &l, int64_t M, int64_t Mp, uint64_t cost_star
     d.y = reinterpret_cast<_Float16 *>(l.y);
     d.xt = static_cast<const uint4 *>(xt);
     d.x_bf16 = nullptr;
-    if (!use_mfma(Mp) && (l.flags & MQ_X_BF16)) {  // the vector-ALU kernels read the fp16 copy that launch_xcvt makes at xt
+    if (rows && (l.flags & MQ_X_BF16)) {  // the row kernels read the fp16 copy that launch_xcvt makes at xt
         d.x_bf16 = l.x;
         d.x = static_cast<const _Float16 *>(xt);
     }
@@ -147,7 +145,7 @@ LayerDesc make_desc(const mq_layer &l, int64_t M, int64_t Mp, uint64_t cost_star
         d.rs = l.r;
         d.cost = valu_tile_cost(kC, (int)M);
     }
-    if (use_mfma(Mp) && !use_wide(Mp)) {  // scheduled in super-tiles of kNarrowRowBlocks row blocks
+    if (!rows && !use_wide(Mp)) {  // scheduled in super-tiles of kNarrowRowBlocks row blocks
         d.RB = (d.RB + kNarrowRowBlocks - 1) / kNarrowRowBlocks;
         d.cost = mfma_tile_cost(l.r);
     }
@@ -175,8 +173,9 @@ struct PlanHeader {
     int32_t n_layers, M, max_cost, n_jobs;
     uint64_t table_off, cnt_off, part_off, total_bytes;
     int32_t from_parent, path_M;
+    int32_t rows;                 // the row kernels serve it
     int32_t ll_blocks, ll_waves;  // low-latency launch shape of a small stack, or 0
-    int32_t any_x_bf16;           // some layer takes bf16 activations (the vector-ALU launches convert them first)
+    int32_t any_x_bf16;           // some layer takes bf16 activations (launches of row kernels convert them first)
     int32_t ll_ks_cap;            // low-latency launch shape: most K slices per row block
     int32_t ll_start[16];         // ... and each layer's first workgroup
     int32_t chain_total;          // chained small stack: row blocks of all layers (0: not chained) ...
@@ -187,7 +186,7 @@ struct PlanHeader {
 constexpr size_t kPlanTableOff = 256;
 static_assert(sizeof(PlanHeader) <= kPlanTableOff && kPlanTableOff + sizeof(SmallTable) <= sizeof(mq_plan),
               "header and descriptors must fit the caller's handle");
-constexpr uint64_t kPlanMagic = 0x4d51504c414e3038ull;  // "MQPLAN08"
+constexpr uint64_t kPlanMagic = 0x4d51504c414e3039ull;  // "MQPLAN09"
 
 // ---- scratch of mq_linear_noalloc: device memory that exists without anybody allocating it.
 // The array's name is only a host-side stand-in; its device address is looked up once per device (each device
@@ -265,29 +264,31 @@ mq_status run_single(const mq_layer &l, int64_t M, void *ws, size_t ws_bytes, mq
     const size_t cnt_b = counter_bytes(counters_of(M, l.N));
     const size_t part_b = worker_cap ? (size_t)worker_cap * 2 * (size_t)slot_floats(M) * sizeof(float) : partial_bytes(M);
     char *act = base + cnt_b + part_b;
+    const int64_t row_blocks = pad_rows(l.N) / kRowBlock, tiles = row_blocks * (l.K / kGroup);
+    const bool rows = use_row_kernels(M, row_blocks, tiles, true, part_b);
     StackParams p{};
-    p.worker_cap = worker_cap;
+    p.worker_cap = use_mfma(M) && rows ? slots_in(part_b, M) : worker_cap;
     p.table = nullptr;
     p.n_layers = 1;
     const _Float16 *sym_line = nullptr;
     if (!l.zeros_t && !(sym_line = sym_zero_line())) return MQ_ERR_HIP;
-    p.single = make_desc(l, M, M, 0, 0, 0, act, sym_line);
+    p.single = make_desc(l, M, M, rows, 0, 0, 0, act, sym_line);
     p.cost_total = (uint64_t)p.single.CB * p.single.RB * p.single.G * p.single.cost;
     p.cnt = reinterpret_cast<int32_t *>(base);
     p.part = reinterpret_cast<float *>(base + cnt_b);
     p.M = (int32_t)M;
-    p.slot_floats = slot_floats(M);
+    p.slot_floats = rows ? 64 * vector_rows(M) : slot_floats(M);
     p.n_jobs = (use_wide(M) ? wide_chunks_padded(M) : p.single.CB) * p.single.G;
     hipError_t e;
     // bf16 activations (packed layers only: a single from-parent call takes fp16): the low-latency launch converts them itself
-    const bool rb = !use_mfma(M) && linear_rb_fits(p.single, part_b);
-    if (!use_mfma(M) && (l.flags & MQ_X_BF16) && !rb) {
+    const bool rb = rows && low_latency_fits(row_blocks, tiles, M, part_b);
+    if (rows && (l.flags & MQ_X_BF16) && !rb) {
         if (launch_xcvt(p, (hipStream_t)stream) != hipSuccess) return MQ_ERR_HIP;
         p.single.x_bf16 = nullptr;  // from here on x is the fp16 copy
     }
     if (use_wide(M))
         e = launch_stack_wide(p, p.single.cost, (hipStream_t)stream);
-    else if (use_mfma(M))
+    else if (!rows)
         e = launch_stack_mfma(p, p.single.cost, (hipStream_t)stream);
     else if (rb)
         e = launch_linear_rb(p.single, p.part, p.cnt, (hipStream_t)stream);
@@ -549,6 +550,13 @@ mq_status mq_stack_plan(const mq_layer *layers, int n_layers, int64_t M, void *p
     if (plan_bytes < need) return MQ_ERR_BUF_TOO_SMALL;
 
     const PlanLayout pl = plan_layout(layers, n_layers, Mp);
+    int64_t row_blocks = 0, tiles = 0;
+    for (int i = 0; i < n_layers; ++i) {
+        row_blocks += pad_rows(layers[i].N) / kRowBlock;
+        tiles += pad_rows(layers[i].N) / kRowBlock * (layers[i].K / kGroup);
+    }
+    // (more than kSmallStackLayers layers never have the low-latency shape)
+    const bool rows = use_row_kernels(M, row_blocks, n_layers > kSmallStackLayers && M > 8 ? INT64_MAX : tiles, false, partial_bytes(Mp));
     char *base_dev = static_cast<char *>(plan_ws);
     int64_t counters = 0, jobs = 0;
     uint64_t cost = 0;
@@ -559,7 +567,7 @@ mq_status mq_stack_plan(const mq_layer *layers, int n_layers, int64_t M, void *p
     for (int i = 0; i < n_layers; ++i) {
         const size_t xb = xt_bytes(Mp, layers[i].K, layers[i].r);
         if (!layers[i].zeros_t && !sym_line && !(sym_line = sym_zero_line())) return MQ_ERR_HIP;
-        table[i] = make_desc(layers[i], M, Mp, cost, (int)counters, (int)jobs, xb ? base_dev + act : nullptr, sym_line);
+        table[i] = make_desc(layers[i], M, Mp, rows, cost, (int)counters, (int)jobs, xb ? base_dev + act : nullptr, sym_line);
         act += xb;
         cost += (uint64_t)table[i].CB * table[i].RB * table[i].G * table[i].cost;
         counters += counters_of(Mp, layers[i].N);
@@ -582,10 +590,11 @@ mq_status mq_stack_plan(const mq_layer *layers, int n_layers, int64_t M, void *p
     h.total_bytes = pl.total;
     h.from_parent = layers[0].from_parent;
     h.path_M = (int32_t)Mp;
+    h.rows = rows;
     {
         int nb = 0, nw = 0, kc = 0;
         bool all_resident = false;
-        if (!use_mfma(Mp) && linear_rb_stack_shape(table.data(), n_layers, partial_bytes(Mp), layers[0].from_parent != 0,
+        if (rows && linear_rb_stack_shape(table.data(), n_layers, partial_bytes(Mp), layers[0].from_parent != 0,
                                                    chained, &nb, &nw, &kc, h.ll_start, &all_resident)) {
             h.ll_blocks = nb;
             h.ll_waves = nw;
@@ -638,18 +647,19 @@ mq_status mq_linear_stack(const mq_plan *plan, mq_stream stream) {
     p.cnt = reinterpret_cast<int32_t *>(base + h.cnt_off);
     p.part = reinterpret_cast<float *>(base + h.part_off);
     p.M = h.M;
-    p.slot_floats = slot_floats(h.path_M);
+    p.slot_floats = h.rows ? 64 * vector_rows(h.M) : slot_floats(h.path_M);
+    if (use_mfma(h.path_M) && h.rows) p.worker_cap = slots_in(partial_bytes(h.path_M), h.M);
     p.n_jobs = h.n_jobs;
     p.ks_cap = h.ll_ks_cap;
     std::memcpy(p.ll_start, h.ll_start, sizeof(p.ll_start));
     p.chain_total = h.chain_total;
     p.chain_off = h.chain_off;
     std::memcpy(p.stage_rb, h.stage_rb, sizeof(p.stage_rb));
-    if (!use_mfma(h.path_M) && h.any_x_bf16) {
+    if (h.rows && h.any_x_bf16) {
         if (launch_xcvt(p, (hipStream_t)stream) != hipSuccess) return MQ_ERR_HIP;
     }
     const hipError_t e = use_wide(h.path_M)   ? launch_stack_wide(p, h.max_cost, (hipStream_t)stream)
-                         : use_mfma(h.path_M) ? launch_stack_mfma(p, h.max_cost, (hipStream_t)stream)
+                         : !h.rows            ? launch_stack_mfma(p, h.max_cost, (hipStream_t)stream)
                          : h.ll_blocks        ? launch_linear_rb_stack(p, small, h.ll_blocks, h.ll_waves, h.from_parent != 0,
                                                                        (hipStream_t)stream)
                                               : launch_stack(p, h.max_cost, h.from_parent != 0, (hipStream_t)stream);

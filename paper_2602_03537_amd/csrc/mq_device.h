@@ -1,4 +1,4 @@
-// Device-side pieces shared by the vector-ALU kernel (mq_linear.hip) and the
+// Device-side pieces shared by the row kernels (mq_linear.hip) and the
 // MFMA kernel (mq_gemm.hip): the persistent schedule over all tiles of a stack
 // and the deterministic split-K hand-off.
 //
@@ -47,7 +47,7 @@ __device__ __forceinline__ uint32_t bf16_pair_to_f16_pair(uint32_t v) {
     return __builtin_bit_cast(uint32_t, h);
 }
 // (for the activation prep kernels of the matrix-core paths, where the conversion costs nothing that matters; the
-// vector-ALU kernels, but for the single-layer low-latency one, read activations that xcvt_kernel has converted: computed both ways and selected per
+// row kernels, but for the single-layer low-latency one, read activations that xcvt_kernel has converted: computed both ways and selected per
 // tile, the conversion costs the ALU-bound 2-bit tiles 3 %, branched around 10 %)
 __device__ __forceinline__ uint32_t x_pair(uint32_t v, int flags) { return flags & kFlagXBf16 ? bf16_pair_to_f16_pair(v) : v; }
 

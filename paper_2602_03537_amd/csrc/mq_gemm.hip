@@ -1,6 +1,6 @@
 // Small batch (4 < M <= 16): the same sliced linear layer on the matrix cores (Section 4 of the paper switches to
 // TensorCores from batch 8; here the switch is at M = 5).  Same packed tiles, same persistent schedule and
-// split-K hand-off (mq_device.h) as the vector-ALU kernel.
+// split-K hand-off (mq_device.h) as the row kernels.
 //
 // MFMA mapping.  v_mfma_f32_32x32x16_f16 computes D[32x32] += A[32x16] * B[16x32]; lane l supplies
 // A[l%32][8*(l/32) .. +7] and B[8*(l/32) .. +7][l%32].  In the tile layout lane l owns row l of the 64-row tile,
@@ -24,7 +24,7 @@
 // (A = z * 2^(r-17), exact for every zero >= 2) by -X_g * 2^(e-15) split into three fp16 pieces (relative error 2^-33),
 // so that D = 2^(e+r-32) * sum_k x_k * (S_k - z).  Per group and accumulator element what is left for the vector ALUs
 // is  y += scale * (F * D),  F = 2^(32-r-e)  from the prep kernel: integer codes stay exact and scales are never
-// rounded to fp16, as on the vector-ALU path.
+// rounded to fp16, as in the row kernels.
 //
 // Work split and memory pipeline.  A workgroup of eight waves walks a run of super-tiles (512 rows x one group);
 // wave w owns row block 8*srb + w.  Everything travels global -> LDS without registers (mq_dma.h): the prepared

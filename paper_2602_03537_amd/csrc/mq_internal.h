@@ -33,15 +33,37 @@ inline int max_workers_valu(int64_t M) {
 }
 constexpr int kCounterBytesAlign = 256;
 
-// Batches up to kValuMaxM run on the vector ALUs; up to kNarrowMaxM on MFMA with 16 columns per
-// chunk and one wave per tile; larger ones on MFMA with 32 columns per chunk, four waves per
-// super-tile of 256 rows and up to kWideMaxChunks chunks against one unpacked tile.
+// Three families of kernels.  "Row" kernels (mq_linear.hip): lane = row of the tile, no wave waits for another; one row of x on the
+// vector ALUs, more by 4x4x4 matrix instructions.  "Narrow" (mq_gemm.hip): 16 columns per chunk, eight waves share a stage of
+// activations.  "Wide" (mq_wide.hip): 32 columns per chunk, four waves per super-tile of 256 rows and up to kWideMaxChunks chunks
+// against one unpacked tile.  Workspaces are laid out by the batch alone: up to kValuMaxM, up to kNarrowMaxM, larger.
 constexpr int kValuMaxM = 4;
+constexpr int kQuadMaxM = 16;  // batch that a row kernel exists for
 constexpr int kChunkCols = 16;
 constexpr int kNarrowMaxM = 16;
 constexpr int kWideCols = 32;
 constexpr int kWideMaxChunks = 4;
 constexpr int kWideXtBlockBytes = 8 * 1024;  // prepared activations of one (group, chunk of 32 columns)
+// batch rows that the row kernel serving a batch of M is built for (its partial sums have as many)
+inline int vector_rows(int64_t M) { return M <= 4 ? (int)M : M <= 8 ? 8 : 16; }
+// The low-latency shape pays off while a wave owns few tiles; larger layers stream better under the persistent schedule.
+// A row block has up to eight partial-sum slots.
+inline bool low_latency_fits(int64_t row_blocks, int64_t tiles, int64_t M, size_t part_bytes) {
+    return tiles <= 12288 && (size_t)row_blocks * 8 * (size_t)vector_rows(M) * 64 * sizeof(float) <= part_bytes;
+}
+// Row kernels serve
+//   * every batch up to kValuMaxM;
+//   * 5 .. 8 rows: every single layer (us, narrow kernel / row kernel: 4096 x 4096 20.8 / 8.9, 28672 x 8192 40 / 31 at r = 4, 59.5 / 47.5 at
+//     r = 8), and stacks up to kRowStackTiles tiles (Llama-2-7B blocks at M = 8: four of them, 99 k tiles, 102 / 90; Llama-3-70B blocks: four,
+//     417 k, 361 / 379, where the narrow kernel's shared activations win);
+//   * 9 .. 16 rows: what fits the low-latency shape (M = 16, r = 4: 4096 x 4096 22.2 / 11.5, 13003 x 5120 30.7 / 22.0; beyond it 28672 x 8192
+//     would be 41.7 / 49.9: every tile reads its activations from LDS anew).
+constexpr int64_t kRowStackTiles = 200000;
+inline bool use_row_kernels(int64_t M, int64_t row_blocks, int64_t tiles, bool single, size_t part_bytes) {
+    if (M <= kValuMaxM) return true;
+    if (M <= 8 && (single || tiles <= kRowStackTiles)) return true;
+    return M <= kQuadMaxM && low_latency_fits(row_blocks, tiles, M, part_bytes);
+}
 inline bool use_wide(int64_t M) { return M > kNarrowMaxM; }
 inline int wide_chunks(int64_t M) { return (int)((M + kWideCols - 1) / kWideCols); }
 inline int wide_passes(int64_t M) { return (wide_chunks(M) + kWideMaxChunks - 1) / kWideMaxChunks; }
@@ -59,13 +81,13 @@ struct LayerDesc {
     const _Float16 *x;
     _Float16 *y;
     const uint4 *xt;        // MFMA paths: activations re-ordered (narrow path: and scaled) by the prep kernel
-    const void *x_bf16;     // vector-ALU path with kFlagXBf16: the caller's bf16 activations (x then points to their fp16 copy)
+    const void *x_bf16;     // row kernels with kFlagXBf16: the caller's bf16 activations (x then points to their fp16 copy)
     int32_t N, K, G, RB;    // RB = row blocks = ceil(N/64); super row blocks on the matrix-core paths: ceil(N/512) narrow, ceil(N/256) wide
     int32_t r;
     int32_t cost;           // schedule cost of one (row block, group) tile
     int32_t cnt_off;        // index of this layer's first row-block counter (CB*RB counters)
     int32_t M;              // batch rows of x
-    int32_t CB;             // column chunks: 1 on the vector-ALU path, ceil(M/16) on the MFMA path; wide path: passes
+    int32_t CB;             // column chunks: 1, or the wide kernel's passes
     int32_t job_start;      // prep kernel: sum of CB*G over the preceding layers
     int32_t rs;             // 0, or: Wp is the 8-bit parent (r == 8) and Eq. 1 to rs bits is applied in registers
     int32_t flags;          // kFlagXBf16: x holds bf16 values; kFlagYBf16: y is written as bf16
@@ -109,16 +131,16 @@ struct StackParams {
     LayerDesc single;
 };
 
-// Schedule cost of a tile on the vector-ALU path: measured times of uniform stacks (12 Llama-3-70B blocks, units of
-// 10 us) per batch M = 1..4.  At M = 1 the kernel is HBM-bound and the cost close to a tile's bytes (4r + 2 lines of
+// Schedule cost of a tile under the row kernels: measured times of uniform stacks (Llama-3-70B blocks) per batch 1, 2, 3, 4, 5 .. 8.
+// Up to M = 4 the kernel is HBM-bound and the cost close to a tile's bytes (4r + 2 lines of
 // 256 bytes: 100 : 140 : 180 : 260 : 340), but the narrow widths run a little below the HBM rate of the wide ones, and
-// mixed stacks are 1.6-1.8 % faster with the measured ratios than with the byte-proportional ones.  From M = 2 on the M
-// accumulators per lane make the narrow widths ALU-bound and the cost much flatter than the bytes.
+// mixed stacks are 1.6-1.8 % faster with the measured ratios than with the byte-proportional ones.  (Four blocks, r = 2 .. 8, us:
+// M = 1 160 213 274 397 522, M = 2 160 225 280 402 518, M = 4 177 229 285 408 528, M = 8 298 337 326 445 545.)
 inline int valu_tile_cost(int r, int M) {
-    static const int t[4][5] = {{100, 122, 155, 222, 290}, {89, 96, 98, 138, 176}, {109, 118, 117, 148, 178},
-                                {134, 143, 138, 177, 187}};
+    static const int t[5][5] = {{100, 122, 155, 222, 290}, {90, 126, 157, 226, 290}, {97, 124, 157, 227, 293},
+                                {99, 128, 159, 228, 295}, {167, 188, 181, 247, 305}};
     const int ri = r == 2 ? 0 : r == 3 ? 1 : r == 4 ? 2 : r == 6 ? 3 : 4;
-    return t[(M < 1 ? 1 : M > 4 ? 4 : M) - 1][ri];
+    return t[(M < 1 ? 1 : M > 4 ? 5 : M) - 1][ri];
 }
 
 // Narrow MFMA path (kValuMaxM < M <= kNarrowMaxM): a tile's time there is set by instruction issue more than by its
@@ -187,13 +209,12 @@ hipError_t launch_gptq(float *W, int64_t ldw, int64_t N, int64_t K, const float 
 hipError_t launch_quant(const float *W, int64_t ldw, int64_t N, int64_t ncols, int64_t col0, const _Float16 *scales,
                         const _Float16 *zeros, int64_t G, const float *lambda, uint8_t *Q, int64_t ldq, bool vec4,
                         hipStream_t s);
-// bf16 activations of the layers that carry kFlagXBf16 -> fp16 in their LayerDesc::xt (ahead of a vector-ALU launch)
+// bf16 activations of the layers that carry kFlagXBf16 -> fp16 in their LayerDesc::xt (ahead of a launch of row kernels)
 hipError_t launch_xcvt(const StackParams &p, hipStream_t s);
-// Fills p.nwaves and launches (vector-ALU path, M <= kValuMaxM).  max_cost = largest tile cost in the stack.
+// Fills p.nwaves and launches (row kernels, M <= 8).  max_cost = largest tile cost in the stack.
 // from_parent: every layer has rs != 0 (the kernel variant that slices in registers).
 hipError_t launch_stack(StackParams p, int max_cost, bool from_parent, hipStream_t s);
 // Single layer, M <= kValuMaxM: one workgroup per (row block, K slice); see mq_linear.hip.
-bool linear_rb_fits(const LayerDesc &L, size_t part_bytes);
 hipError_t launch_linear_rb(const LayerDesc &L, float *part, int32_t *cnt, hipStream_t s);
 // The same shape for a small stack (M <= kValuMaxM): all layers' workgroups in one launch.  `table` is the host copy
 // of the descriptors; false = the stack is too big for it.

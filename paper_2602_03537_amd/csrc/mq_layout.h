@@ -144,6 +144,90 @@ template <int R> constexpr bool layout_ok() {
     }
     return true;
 }
+// Two fields with one key meet two activation pairs in a v_mfma_f32_4x4x4_16b_f16 (batches of 2 .. 4).  The list of such steps
+// for a block of BP pairs: fields (unit, op) a and b, and where in the block their pairs stand once activation pair p of 16 has been
+// moved to position pos(p), chosen so that the two are neighbours (but for the third bit of the 3-bit unit's last code).
+struct Step {
+    int ua, oa, ub, ob;  // unit within the block, op
+    int pa, pb;          // position of their pairs within the block
+};
+template <int R> struct Steps;
+template <> struct Steps<2> {
+    static constexpr int BP = 16, N = 8;
+    static constexpr Step at(int i) {
+        constexpr Step t[N] = {{0, 0, 0, 5, 0, 1}, {0, 1, 0, 6, 2, 3}, {1, 0, 1, 5, 4, 5}, {1, 1, 1, 6, 6, 7},
+                               {0, 2, 0, 7, 8, 9}, {1, 2, 1, 7, 10, 11}, {0, 3, 1, 3, 12, 13}, {0, 4, 1, 4, 14, 15}};
+        return t[i];
+    }
+};
+template <> struct Steps<3> {
+    static constexpr int BP = 32, N = 18;
+    static constexpr Step at(int i) {
+        constexpr Step t[N] = {{0, 0, 0, 3, 0, 1}, {0, 1, 0, 4, 2, 3}, {0, 5, 0, 8, 4, 5}, {0, 6, 0, 9, 6, 7},
+                               {0, 10, 0, 13, 8, 9}, {0, 11, 0, 14, 10, 11}, {0, 2, 0, 7, 12, 13}, {0, 12, 0, 15, 14, 15},
+                               {1, 0, 1, 3, 16, 17}, {1, 1, 1, 4, 18, 19}, {1, 5, 1, 8, 20, 21}, {1, 6, 1, 9, 22, 23},
+                               {1, 10, 1, 13, 24, 25}, {1, 11, 1, 14, 26, 27}, {1, 2, 1, 7, 28, 29}, {1, 12, 1, 15, 30, 31},
+                               {0, 16, 1, 16, 15, 31}, {0, 17, 1, 17, 15, 31}};
+        return t[i];
+    }
+};
+template <> struct Steps<4> {
+    static constexpr int BP = 16, N = 8;
+    static constexpr Step at(int i) { return {i / 2, i % 2, i / 2, i % 2 + 2, 2 * i, 2 * i + 1}; }
+};
+template <> struct Steps<6> {
+    static constexpr int BP = 16, N = 10;
+    static constexpr Step at(int i) {
+        const int u = i / 5, p = 8 * u;
+        constexpr int oa[5] = {0, 2, 4, 6, 7}, ob[5] = {1, 3, 5, 8, 9}, at[5] = {0, 2, 4, 6, 6};
+        return {u, oa[i % 5], u, ob[i % 5], p + at[i % 5], p + at[i % 5] + 1};
+    }
+};
+template <> struct Steps<8> {
+    static constexpr int BP = 16, N = 8;
+    static constexpr Step at(int i) { return {i, 0, i, 1, 2 * i, 2 * i + 1}; }
+};
+// position of pair p of a block of 16, from the list
+template <int R> constexpr int step_pos(int p) {
+    using T = Layout<R>;
+    for (int i = 0; i < Steps<R>::N; ++i) {
+        const Step s = Steps<R>::at(i);
+        if (s.ua * T::PPU + T::op(s.oa).pair == p) return s.pa;
+        if (s.ub * T::PPU + T::op(s.ob).pair == p) return s.pb;
+    }
+    return -1;
+}
+// ... of all 16, four bits each
+template <int R> constexpr uint64_t step_table() {
+    uint64_t t = 0;
+    for (int p = 0; p < 16; ++p) t |= (uint64_t)step_pos<R>(p) << (4 * p);
+    return t;
+}
+template <int R> constexpr bool steps_ok() {
+    using T = Layout<R>;
+    using S = Steps<R>;
+    constexpr int units = S::BP / T::PPU;
+    int used[8][18] = {};
+    for (int i = 0; i < S::N; ++i) {
+        const Step s = S::at(i);
+        if (s.ua >= units || s.ub >= units || key_index<R>(s.oa) != key_index<R>(s.ob)) return false;
+        ++used[s.ua][s.oa];
+        ++used[s.ub][s.ob];
+        // every field meets its own pair
+        if (s.pa != step_pos<R>(s.ua * T::PPU + T::op(s.oa).pair) || s.pb != step_pos<R>(s.ub * T::PPU + T::op(s.ob).pair)) return false;
+    }
+    for (int u = 0; u < units; ++u)
+        for (int o = 0; o < T::NOPS; ++o)
+            if (used[u][o] != 1) return false;  // every field once
+    int seen[32] = {};
+    for (int p = 0; p < S::BP; ++p) {
+        const int q = step_pos<R>(p);
+        if (q < 0 || q >= S::BP || seen[q]++) return false;          // a permutation ...
+        if (q != step_pos<R>(p % 16) + p / 16 * 16) return false;  // ... the same in every 16
+    }
+    return true;
+}
+static_assert(steps_ok<2>() && steps_ok<3>() && steps_ok<4>() && steps_ok<6>() && steps_ok<8>(), "inconsistent list of matrix-core steps");
 static_assert(layout_ok<2>() && layout_ok<3>() && layout_ok<4>() && layout_ok<6>() && layout_ok<8>(),
               "inconsistent packed layout table");
 

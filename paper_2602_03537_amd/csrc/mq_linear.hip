@@ -1,6 +1,6 @@
 // Sliced, group-dequantised linear layer  y = x * W_D^T  (Section 4 of the paper)
-// for batch sizes served by the vector ALUs (M <= 4), and the mixed-precision
-// stack of such layers (Section 3.3), as ONE persistent kernel.  Schedule and
+// for small batches: one row of x on the vector ALUs, 2 .. 16 by 4x4x4 matrix
+// instructions, and the mixed-precision stack of such layers (Section 3.3), as ONE persistent kernel.  Schedule and
 // split-K hand-off: mq_device.h.
 //
 // Arithmetic per tile and lane (one row, one group g):
@@ -12,18 +12,27 @@
 
 namespace mq {
 
-// How a wave gets the 64 activation pairs of a group (they are the same for every lane):
-//   kXScalar : scalar loads into SGPRs at the start of the tile's math (short latency while x
-//              sits in the scalar cache; exposed when it does not)
-//   kXLds    : each lane fetches ONE pair together with the tile (one tile ahead, like the
-//              weights), drops it into the wave's 256 bytes of LDS and all lanes read the
-//              pairs back with broadcast ds_read_b128: no scalar-cache dependence at all
-enum XPath { kXScalar = 0, kXLds = 1 };
+// How a wave gets the 64 activation pairs of a group (they are the same for every lane): each lane fetches ONE pair together with
+// the tile (one tile ahead, like the weights), drops it into the wave's 256 bytes of LDS per batch row and all lanes read the
+// pairs back with ds_read_b128.
+// From a batch of 2 on a tile is multiplied by the matrix core (tile_math_mfma), whose result has four rows per lane
+template <int M> constexpr bool kQuadRows = M >= 2;
+template <int M> constexpr int kQuads = (M + 3) / 4;                      // of batch rows
+template <int M> constexpr int kAcc = kQuadRows<M> ? 4 * kQuads<M> : 1;  // fp32 running sums per lane
+template <int M> constexpr int kRbWaves = M > 8 ? 4 : M > 4 ? 8 : 16;                 // most waves of a low-latency workgroup (registers)
+// Dwords from batch row to batch row in LDS: the four rows that a quad of lanes reads at one time lie in different banks (64 dwords
+// apart they shared them: 28672 x 8192, r = 4, M = 8: 37.0 us, now 30.8)
+template <int M> constexpr int kRowDwords = M > 1 ? 68 : 64;
+// M of a kernel is 1 .. 4, or 8 for a batch of 5 .. 8: there the rows of x that do not exist are read as the last one and not stored
+template <int M> __device__ __forceinline__ int row_count(const LayerDesc &L) { return M > 4 ? L.M : M; }
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));  // four fp16 at any address of one
+typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 template <int R, int M> struct TileRegs {
     uint32_t w[4 * R];
-    _Float16 s, z;
-    uint32_t xl[M];  // lane l's pair (x[2l], x[2l+1]) of the group: X_g, and the kXLds path
+    std::conditional_t<kQuadRows<M>, half4_t, _Float16> s, z;  // of the lane's rows
+    uint32_t xl[M];  // lane l's pair (x[2l], x[2l+1]) of the group
 };
 
 // weights, scale and zero-offset of tile u
@@ -38,11 +47,20 @@ __device__ __forceinline__ void load_tile_w(TileRegs<R, M> &t, const LayerDesc &
         const u32x4 v = __builtin_nontemporal_load(src + i * 64);
         t.w[4 * i] = v.x; t.w[4 * i + 1] = v.y; t.w[4 * i + 2] = v.z; t.w[4 * i + 3] = v.w;
     }
-    t.s = __builtin_nontemporal_load(gl(L.st) + (size_t)u * 64 + lane);
+    const size_t su = (size_t)u * 64, zu = (size_t)(u & L.zmask) * 64;
+    if constexpr (kQuadRows<M>) {
+        t.s = __builtin_bit_cast(half4_t, (u32x2)__builtin_nontemporal_load(reinterpret_cast<const u32x2_any MQ_GLOBAL *>(gl(L.st) + su + (lane & ~3))));
+    } else {
+        t.s = __builtin_nontemporal_load(gl(L.st) + su + lane);
+    }
     // A symmetric layer has no zero-offset array: its zt is a few lines of 64 x 128.0 inside the library and zmask
     // folds every tile onto them (cache hits, no HBM traffic).  The load is neither branched around nor selected -- either
     // costs the ALU-bound 2-bit tiles and the mixed Llama-3-70B stack 3-9 % -- and an asymmetric layer pays one scalar AND.
-    t.z = __builtin_nontemporal_load(gl(L.zt) + (size_t)(u & L.zmask) * 64 + lane);
+    if constexpr (kQuadRows<M>) {
+        t.z = __builtin_bit_cast(half4_t, (u32x2)__builtin_nontemporal_load(reinterpret_cast<const u32x2_any MQ_GLOBAL *>(gl(L.zt) + zu + (lane & ~3))));
+    } else {
+        t.z = __builtin_nontemporal_load(gl(L.zt) + zu + lane);
+    }
 }
 // the lane's activation pair of group g, per batch row.  fresh: x was written by other workgroups of this very launch
 // (a chained stack): the loads go to where the whole device sees memory, past whatever this compute die's caches hold.
@@ -50,7 +68,8 @@ template <int R, int M>
 __device__ __forceinline__ void load_tile_x(TileRegs<R, M> &t, const LayerDesc &L, int g, int lane, bool fresh = false) {
 #pragma unroll
     for (int m = 0; m < M; ++m) {
-        const uint32_t MQ_GLOBAL *src = gl(reinterpret_cast<const uint32_t *>(L.x + (size_t)m * L.K + (size_t)g * kGroup)) + lane;
+        const int row = M > 4 && m >= L.M ? L.M - 1 : m;
+        const uint32_t MQ_GLOBAL *src = gl(reinterpret_cast<const uint32_t *>(L.x + (size_t)row * L.K + (size_t)g * kGroup)) + lane;
         t.xl[m] = fresh ? __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *src;
     }
 }
@@ -78,39 +97,119 @@ __device__ __forceinline__ uint32_t slice_pair(uint32_t v, const SliceConst &c) 
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(t, c.cap2));
 }
 
-// xlds: this wave's M x 64 dwords of LDS (kXLds only)
-// SL (R == 8 only): the tile holds the unsliced parent; its codes are sliced to L.rs bits first.
-// XB: the activations are bf16 and are converted here
-template <int R, int M, int XP, bool SL = false, bool XB = false>
-__device__ __forceinline__ void tile_math(const TileRegs<R, M> &t, const LayerDesc &L, int g, int lane,
-                                          uint32_t *xlds, float (&yacc)[M]) {
+// A batch of 2 and more on the matrix core: v_mfma_f32_4x4x4_16b_f16 takes, from every lane, four weights of its row (two masked
+// dwords) and four activations of batch row lane % 4, and gives lane 4 b + m the sums of rows 4 b .. 4 b + 3 for batch row m.  The
+// operand layout is the tile's own, so a quad of activations is read from LDS once for four batch rows (by v_dot2 it was once for
+// each, which is what bound these kernels) and the multiplications leave the vector ALUs.  Two fields with one key make an operand;
+// Steps<R> lists them.  Lanes of batch rows that do not exist read some other row's and their sums are dropped.
+// By v_dot2 / now, us: 28672 x 8192 M = 4: r = 2 35.8 / 20.6, r = 4 35.4 / 27.3, r = 8 48 / 44.9; 4096 x 4096 r = 4 M = 2, 3, 4 7.3 / 6.9,
+// 7.9 / 7.2, 8.4 / 7.3; a decode step of four Llama-2-7B blocks 179 / 159, 205 / 169, 244 / 175; a mixed stack of 12 Llama-3-70B blocks
+// 968 / 948, 1179 / 923, 1009 (narrow kernel) / 934.
+// X_g per batch row: partial sums of the four rows change places over DPP steps until lane l holds those of row l % 4.
+template <int M, int Q> __device__ __forceinline__ float quad_sums(const uint32_t (&x)[M], int lane) {
+    constexpr int n = M - 4 * Q < 4 ? M - 4 * Q : 4;
+    float s[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) s[m] = m < n ? dot2(x[4 * Q + (m < n ? m : 0)], 0x3C003C00u, 0.f) : 0.f;  // (1.0, 1.0)
+    auto swap1 = [](float v) { return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xB1, 0xf, 0xf, true)); };
+    auto swap2 = [](float v) { return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x4E, 0xf, 0xf, true)); };
+    const bool odd = lane & 1, high = lane & 2;
+    const float a = (odd ? s[1] : s[0]) + swap1(odd ? s[0] : s[1]);
+    float t;
+    if constexpr (n > 2) {
+        const float b = (odd ? s[3] : s[2]) + swap1(odd ? s[2] : s[3]);
+        t = (high ? b : a) + swap2(high ? a : b);
+    } else {
+        t = a + swap2(a);
+    }
+    t = dpp_add<0x124>(t);  // row_ror:4
+    t = dpp_add<0x128>(t);  // row_ror:8
+    t += __shfl_xor(t, 16);
+    t += __shfl_xor(t, 32);
+    return t;
+}
+template <int R, int M, bool SL, bool XB>
+__device__ __forceinline__ void tile_math_mfma(const TileRegs<R, M> &t, const LayerDesc &L, int lane, uint32_t *xlds, float (&yacc)[kAcc<M>]) {
     using T = Layout<R>;
-    static_assert(!SL || R == kC, "slicing in registers starts from the 8-bit parent");
-    constexpr int NU = 4 * R / T::UD;
+    using S = Steps<R>;
+    constexpr int NQ = kQuads<M>;
     const SliceConst sc = slice_const(SL ? L.rs : kC);
-    float xg[M];
-    cptr32 xs[M];
+    uint32_t xl[M];
+    const int pos = (lane & ~15) | (int)((step_table<R>() >> (4 * (lane & 15))) & 15);
 #pragma unroll
     for (int m = 0; m < M; ++m) {
-        const uint32_t xl = XB ? bf16_pair_to_f16_pair(t.xl[m]) : t.xl[m];
-        xg[m] = wave_sum(dot2(xl, 0x3C003C00u, 0.f));  // (1.0, 1.0)
-        if constexpr (XP == kXLds)
-            xlds[m * 64 + lane] = xl;
-        else
-            xs[m] = as_const(L.x + (size_t)m * L.K + (size_t)g * kGroup);
+        xl[m] = XB ? bf16_pair_to_f16_pair(t.xl[m]) : t.xl[m];
+        xlds[m * kRowDwords<M> + pos] = xl[m];
     }
-    float acc[M][T::NKEYS];
+    float xg[NQ];
+    static_for<NQ>([&](auto q) { xg[q] = quad_sums<M, q>(xl, lane); });
+    const int m = lane & 3;
+    f32x4 acc[NQ][T::NKEYS];
 #pragma unroll
-    for (int m = 0; m < M; ++m)
+    for (int q = 0; q < NQ; ++q)
 #pragma unroll
-        for (int k = 0; k < T::NKEYS; ++k) acc[m][k] = 0.f;
+        for (int k = 0; k < T::NKEYS; ++k) acc[q][k] = f32x4{0.f, 0.f, 0.f, 0.f};
+    static_for<64 / S::BP>([&](auto bl) {
+        u32x4 x[NQ][S::BP / 4];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const u32x4 *xq = reinterpret_cast<const u32x4 *>(xlds + (4 * q + m < M ? 4 * q + m : 4 * q) * kRowDwords<M>);
+#pragma unroll
+            for (int i = 0; i < S::BP / 4; ++i) x[q][i] = xq[bl * (S::BP / 4) + i];
+        }
+        static_for<S::N>([&](auto si) {
+            constexpr Step st = S::at(si);
+            auto field = [&](auto uc, auto oc) {
+                constexpr Op o = T::op(oc);
+                uint32_t v = t.w[(bl * (S::BP / T::PPU) + uc) * T::UD + o.dw];
+                if constexpr (o.sh != 0) v >>= o.sh;
+                v &= (uint32_t)o.mask * 0x10001u;
+                if constexpr (SL) v = slice_pair(v, sc);
+                return v;
+            };
+            const u32x2 a = {field(IntC<st.ua>{}, IntC<st.oa>{}), field(IntC<st.ub>{}, IntC<st.ob>{})};
+            constexpr int key = key_index<R>(st.oa);
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const u32x2 b = {x[q][st.pa / 4][st.pa % 4], x[q][st.pb / 4][st.pb % 4]};
+                acc[q][key] = __builtin_amdgcn_mfma_f32_4x4x4f16(__builtin_bit_cast(half4_t, a), __builtin_bit_cast(half4_t, b), acc[q][key], 0, 0, 0);
+            }
+        });
+    });
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float s = (float)t.s[i], z = (float)t.z[i];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            float d = 0.f;
+            // field value = digit * 2^(key-24); back to code units, then Eq. 1's rescale 2^(8-r)
+            static_for<T::NKEYS>([&](auto k) { d = fmaf(acc[q][k][i], __builtin_ldexpf(1.f, 24 - T::key(k) + kC - R), d); });
+            yacc[4 * q + i] = fmaf(s, fmaf(-z, xg[q], d), yacc[4 * q + i]);
+        }
+    }
+}
 
-    if constexpr (XP == kXLds) {
+// xlds: this wave's M rows of LDS
+// SL (R == 8 only): the tile holds the unsliced parent; its codes are sliced to L.rs bits first.
+// XB: the activations are bf16 and are converted here
+template <int R, int M, bool SL = false, bool XB = false>
+__device__ __forceinline__ void tile_math(const TileRegs<R, M> &t, const LayerDesc &L, int lane, uint32_t *xlds, float (&yacc)[kAcc<M>]) {
+    using T = Layout<R>;
+    static_assert(!SL || R == kC, "slicing in registers starts from the 8-bit parent");
+    if constexpr (kQuadRows<M>) {
+        tile_math_mfma<R, M, SL, XB>(t, L, lane, xlds, yacc);
+    } else {
+        constexpr int NU = 4 * R / T::UD;
+        const SliceConst sc = slice_const(SL ? L.rs : kC);
+        const uint32_t xl = XB ? bf16_pair_to_f16_pair(t.xl[0]) : t.xl[0];
+        const float xg = wave_sum(dot2(xl, 0x3C003C00u, 0.f));  // (1.0, 1.0)
+        xlds[lane] = xl;
+        float acc[T::NKEYS];
+#pragma unroll
+        for (int k = 0; k < T::NKEYS; ++k) acc[k] = 0.f;
         // quad by quad of activation pairs: one broadcast 16-byte LDS read serves four pairs
         static_for<16>([&](auto qi) {
-            u32x4 xq[M];
-#pragma unroll
-            for (int m = 0; m < M; ++m) xq[m] = reinterpret_cast<const u32x4 *>(xlds + m * 64)[qi];
+            const u32x4 xq = reinterpret_cast<const u32x4 *>(xlds)[qi];
             static_for<NU>([&](auto un) {
                 static_for<T::NOPS>([&](auto oi) {
                     constexpr Op o = T::op(oi);
@@ -121,35 +220,40 @@ __device__ __forceinline__ void tile_math(const TileRegs<R, M> &t, const LayerDe
                         if constexpr (o.sh != 0) v >>= o.sh;
                         v &= (uint32_t)o.mask * 0x10001u;
                         if constexpr (SL) v = slice_pair(v, sc);
-#pragma unroll
-                        for (int m = 0; m < M; ++m) acc[m][key] = dot2(v, xq[m][pidx % 4], acc[m][key]);
+                        acc[key] = dot2(v, xq[pidx % 4], acc[key]);
                     }
                 });
             });
         });
-    } else {
-        static_for<NU>([&](auto un) {
-            static_for<T::NOPS>([&](auto oi) {
-                constexpr Op o = T::op(oi);
-                constexpr int key = key_index<R>(oi);
-                uint32_t v = t.w[un * T::UD + o.dw];
-                if constexpr (o.sh != 0) v >>= o.sh;
-                v &= (uint32_t)o.mask * 0x10001u;
-                if constexpr (SL) v = slice_pair(v, sc);
-#pragma unroll
-                for (int m = 0; m < M; ++m) acc[m][key] = dot2(v, xs[m][un * T::PPU + o.pair], acc[m][key]);
-            });
-        });
-    }
-    const float s = (float)t.s, z = (float)t.z;
-#pragma unroll
-    for (int m = 0; m < M; ++m) {
         float d = 0.f;
         static_for<T::NKEYS>([&](auto k) {
             // field value = digit * 2^(key-24); back to code units, then Eq. 1's rescale 2^(8-r)
-            d = fmaf(acc[m][k], __builtin_ldexpf(1.f, 24 - T::key(k) + kC - R), d);
+            d = fmaf(acc[k], __builtin_ldexpf(1.f, 24 - T::key(k) + kC - R), d);
         });
-        yacc[m] = fmaf(s, fmaf(-z, xg[m], d), yacc[m]);
+        yacc[0] = fmaf((float)t.s, fmaf(-(float)t.z, xg, d), yacc[0]);
+    }
+}
+
+// a wave's sums as one row per lane, in M rows of LDS of its own
+template <int M> __device__ __forceinline__ void put_rows(const float (&yacc)[kAcc<M>], uint32_t *room, int lane) {
+    if constexpr (kQuadRows<M>) {
+#pragma unroll
+        for (int q = 0; q < kQuads<M>; ++q) {
+            const f32x4 v = {yacc[4 * q], yacc[4 * q + 1], yacc[4 * q + 2], yacc[4 * q + 3]};
+            const int m = 4 * q + (lane & 3);
+            if (m < M) *reinterpret_cast<u32x4 *>(room + m * kRowDwords<M> + (lane & ~3)) = __builtin_bit_cast(u32x4, v);
+        }
+    } else {
+        room[lane] = __builtin_bit_cast(uint32_t, yacc[0]);
+    }
+}
+template <int M> __device__ __forceinline__ void rows_of(const float (&yacc)[kAcc<M>], uint32_t *xlds, int lane, float (&rows)[M]) {
+    if constexpr (kQuadRows<M>) {
+        put_rows<M>(yacc, xlds, lane);
+#pragma unroll
+        for (int m = 0; m < M; ++m) rows[m] = __builtin_bit_cast(float, xlds[m * kRowDwords<M> + lane]);
+    } else {
+        rows[0] = yacc[0];
     }
 }
 
@@ -157,21 +261,21 @@ __device__ __forceinline__ void tile_math(const TileRegs<R, M> &t, const LayerDe
 // in flight cannot pull more than tile_bytes / memory_latency (1.3 GB/s at r = 2), less than
 // its fair share of HBM once wider layers free bandwidth, so narrow tiles are fetched deeper:
 // about 8 KB per wave in flight at every width.
-template <int R> struct PrefetchDepth {
-    static constexpr int value = R <= 2 ? 4 : R == 3 ? 3 : R <= 6 ? 2 : 1;
+template <int R, int M> struct PrefetchDepth {
+    static constexpr int value = M > 4 ? (R <= 4 ? 2 : 1) : R <= 2 ? 4 : R == 3 ? 3 : R <= 6 ? 2 : 1;
 };
 
 // Tiles [u_begin, u_end) of one layer, owned by share `wave`.
-template <int R, int M, int XP, bool SL = false>
+template <int R, int M, bool SL = false>
 __device__ __forceinline__ void run_units(const LayerDesc &L, const StackParams &p, int u_begin, int u_end, int wave,
                                           int lane, uint32_t *xlds) {
-    constexpr int D = PrefetchDepth<R>::value, NB = D + 1;
+    constexpr int D = PrefetchDepth<R, M>::value, NB = D + 1;
     int rb = u_begin / L.G;
     int g = u_begin - rb * L.G;
     int ga = g;
-    float yacc[M];
+    float yacc[kAcc<M>];
 #pragma unroll
-    for (int m = 0; m < M; ++m) yacc[m] = 0.f;
+    for (int i = 0; i < kAcc<M>; ++i) yacc[i] = 0.f;
 
     // ring of NB tile buffers with compile-time indices (no register copies, which would wait
     // for the loads); past the end of the run the last tile is fetched again instead of
@@ -191,45 +295,47 @@ __device__ __forceinline__ void run_units(const LayerDesc &L, const StackParams 
         static_for<NB>([&](auto j) {
             if (u >= u_end) return;
             prefetch(buf[(j + D) % NB]);
-            tile_math<R, M, XP, SL>(buf[j], L, g, lane, xlds, yacc);
+            tile_math<R, M, SL>(buf[j], L, lane, xlds, yacc);
             ++g;
             ++u;
             if (g == L.G || u == u_end) {
                 const int row = rb * kRowBlock + lane;
+                float rows[M];
+                rows_of<M>(yacc, xlds, lane, rows);
                 finish_row_block<M>(L, p, p.cnt + L.cnt_off + rb, L.cost_start + (uint64_t)rb * L.G * L.cost, ga, g,
-                                    yacc, wave, lane, [&](const float(&tot)[M]) {
+                                    rows, wave, lane, [&](const float(&tot)[M]) {
 #pragma unroll
                                         for (int m = 0; m < M; ++m)
-                                            if (row < L.N) store_y(L.y, (size_t)m * L.N + row, tot[m], L.flags);
+                                            if (row < L.N && m < row_count<M>(L)) store_y(L.y, (size_t)m * L.N + row, tot[m], L.flags);
                                     });
                 ++rb;
                 g = 0;
                 ga = 0;
 #pragma unroll
-                for (int m = 0; m < M; ++m) yacc[m] = 0.f;
+                for (int i = 0; i < kAcc<M>; ++i) yacc[i] = 0.f;
             }
         });
     }
 }
 
 // SL: every layer of the stack is computed from its resident 8-bit parent (LayerDesc::rs).
-template <int M, int XP, bool SL = false> __global__ __launch_bounds__(256) void stack_kernel(const StackParams p) {
-    __shared__ __attribute__((aligned(16))) uint32_t xlds_all[XP == kXLds ? 4 * M * 64 : 4];
-    uint32_t *xlds = xlds_all + (XP == kXLds ? (threadIdx.x >> 6) * M * 64 : 0);
+template <int M, bool SL = false> __global__ __launch_bounds__(256, M > 4 ? 2 : 1) void stack_kernel(const StackParams p) {
+    __shared__ __attribute__((aligned(16))) uint32_t xlds_all[4 * M * kRowDwords<M>];
+    uint32_t *xlds = xlds_all + (threadIdx.x >> 6) * M * kRowDwords<M>;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6));
     if (wave >= p.nwaves) return;
     for (int worker = wave; worker < p.nworkers; worker += p.nwaves) {
         walk_tiles(p, worker, [&](const LayerDesc &L, int u_begin, int u_end) {
             if constexpr (SL) {
-                run_units<8, M, XP, true>(L, p, u_begin, u_end, worker, lane, xlds);
+                run_units<8, M, true>(L, p, u_begin, u_end, worker, lane, xlds);
             } else {
                 switch (L.r) {
-                    case 2: run_units<2, M, XP>(L, p, u_begin, u_end, worker, lane, xlds); break;
-                    case 3: run_units<3, M, XP>(L, p, u_begin, u_end, worker, lane, xlds); break;
-                    case 4: run_units<4, M, XP>(L, p, u_begin, u_end, worker, lane, xlds); break;
-                    case 6: run_units<6, M, XP>(L, p, u_begin, u_end, worker, lane, xlds); break;
-                    default: run_units<8, M, XP>(L, p, u_begin, u_end, worker, lane, xlds); break;
+                    case 2: run_units<2, M>(L, p, u_begin, u_end, worker, lane, xlds); break;
+                    case 3: run_units<3, M>(L, p, u_begin, u_end, worker, lane, xlds); break;
+                    case 4: run_units<4, M>(L, p, u_begin, u_end, worker, lane, xlds); break;
+                    case 6: run_units<6, M>(L, p, u_begin, u_end, worker, lane, xlds); break;
+                    default: run_units<8, M>(L, p, u_begin, u_end, worker, lane, xlds); break;
                 }
             }
         });
@@ -290,18 +396,18 @@ __device__ __forceinline__ void chain_announce(const ChainCtl &c, int stage, int
 }
 
 // CH: the launch is a chained small stack (`chain` is live); the plain variants carry none of its code
-template <int R, int M, int XP, bool SL, bool CH = false, bool XB = false>
+template <int R, int M, bool SL, bool CH = false, bool XB = false>
 __device__ __forceinline__ void linear_rb_body(const LayerDesc &L, const int KS, const int blk, const int slot0,
-                                               float *part, int32_t *cnt, float (*red)[M][64], uint32_t *xlds_all,
+                                               float *part, int32_t *cnt, uint32_t (*red)[M][kRowDwords<M>], uint32_t *xlds_all,
                                                const ChainCtl chain = ChainCtl{nullptr, nullptr, 0}) {
-    uint32_t *xlds = xlds_all + (XP == kXLds ? (threadIdx.x >> 6) * M * 64 : 0);
+    uint32_t *xlds = xlds_all + (threadIdx.x >> 6) * M * kRowDwords<M>;
     const int lane = threadIdx.x & 63;
     const int w = threadIdx.x >> 6, W = blockDim.x >> 6;
     const int rb = blk / KS, ks = blk - rb * KS;
     const int g_lo = (int)((int64_t)ks * L.G / KS), g_hi = (int)((int64_t)(ks + 1) * L.G / KS);
-    float yacc[M];
+    float yacc[kAcc<M>];
 #pragma unroll
-    for (int m = 0; m < M; ++m) yacc[m] = 0.f;
+    for (int i = 0; i < kAcc<M>; ++i) yacc[i] = 0.f;
     int g = g_lo + w;
     const bool waits = CH && (L.chain & kChainWaits);
     TileRegs<R, M> cur, nxt;
@@ -327,21 +433,20 @@ __device__ __forceinline__ void linear_rb_body(const LayerDesc &L, const int KS,
                 have_nxt = false;
                 load_tile_x<R, M>(nxt, L, g2, lane, waits);
             }
-            tile_math<R, M, XP, SL, XB>(cur, L, g, lane, xlds, yacc);
+            tile_math<R, M, SL, XB>(cur, L, lane, xlds, yacc);
             if (g2 >= g_hi) break;
             cur = nxt;
             g = g2;
         }
     }
-#pragma unroll
-    for (int m = 0; m < M; ++m) red[w][m][lane] = yacc[m];
+    put_rows<M>(yacc, &red[w][0][0], lane);
     __syncthreads();
     if (w != 0) return;
     float tot[M];
 #pragma unroll
     for (int m = 0; m < M; ++m) {
-        tot[m] = red[0][m][lane];
-        for (int i = 1; i < W; ++i) tot[m] += red[i][m][lane];
+        tot[m] = __builtin_bit_cast(float, red[0][m][lane]);
+        for (int i = 1; i < W; ++i) tot[m] += __builtin_bit_cast(float, red[i][m][lane]);
     }
     const int row = rb * kRowBlock + lane;
     if (KS > 1) {
@@ -384,18 +489,17 @@ __device__ __forceinline__ void linear_rb_body(const LayerDesc &L, const int KS,
     }
 #pragma unroll
     for (int m = 0; m < M; ++m)
-        if (row < L.N) store_y(L.y, (size_t)m * L.N + row, tot[m], L.flags);
+        if (row < L.N && m < row_count<M>(L)) store_y(L.y, (size_t)m * L.N + row, tot[m], L.flags);
 }
 
 // XB: L.x holds bf16 activations.  One variant per kind, because this launch is short: converting ahead of it costs a launch of
 // its own (13003 x 5120, r = 6, M = 3: 22.4 us with it, 20.3 without), while in the tile loop it is four operations per lane,
 // row and tile.
-template <int R, int M, int XP, bool SL = false, bool XB = false>
-__global__ __launch_bounds__(1024) void linear_rb_kernel(const LayerDesc L, const int KS, float *part, int32_t *cnt) {
-    static_assert(XP == kXLds || !XB, "converted activations reach the lanes through LDS");
-    __shared__ float red[16][M][64];
-    __shared__ __attribute__((aligned(16))) uint32_t xlds_all[XP == kXLds ? 16 * M * 64 : 4];
-    linear_rb_body<R, M, XP, SL, false, XB>(L, KS, (int)blockIdx.x, 0, part, cnt, red, xlds_all);
+template <int R, int M, bool SL = false, bool XB = false>
+__global__ __launch_bounds__(64 * kRbWaves<M>) void linear_rb_kernel(const LayerDesc L, const int KS, float *part, int32_t *cnt) {
+    __shared__ __attribute__((aligned(16))) uint32_t red[kRbWaves<M>][M][kRowDwords<M>];
+    __shared__ __attribute__((aligned(16))) uint32_t xlds_all[kRbWaves<M> * M * kRowDwords<M>];
+    linear_rb_body<R, M, SL, false, XB>(L, KS, (int)blockIdx.x, 0, part, cnt, red, xlds_all);
 }
 
 // Launch shape, from sweeps on Llama-2-7B / Llama-3-70B shapes (cold weights): enough K slices
@@ -420,6 +524,8 @@ __host__ __device__ static inline int stack_k_slices(const LayerDesc &L, int ks_
 // groups on, e.g. 4096 x 11008 in four slices of 21-22 groups: 8.3 / 9.6 / 12.9 -> 7.9 / 9.1 / 11.8 us)
 static int rb_waves(const LayerDesc &L, int KS) {
     const int per_block = (L.G + KS - 1) / KS;
+    if (L.M > 8) return 4;
+    if (L.M > 4) return per_block >= 6 ? 8 : 4;
     return (per_block >= 16 || (KS == 1 && per_block >= 12)) ? 16 : per_block >= 6 ? 8 : 4;
 }
 
@@ -431,15 +537,17 @@ static hipError_t launch_linear_rb_rm(const LayerDesc &L, float *part, int32_t *
         if (L.x_bf16) {
             LayerDesc B = L;
             B.x = static_cast<const _Float16 *>(L.x_bf16);
-            return launch((linear_rb_kernel<R, M, kXLds, false, true>), dim3((unsigned)(L.RB * KS)), dim3(64 * W), 0, s, B, KS, part,
+            return launch((linear_rb_kernel<R, M, false, true>), dim3((unsigned)(L.RB * KS)), dim3(64 * W), 0, s, B, KS, part,
                           cnt);
         }
     }
-    return launch((linear_rb_kernel<R, M, kXLds, SL>), dim3((unsigned)(L.RB * KS)), dim3(64 * W), 0, s, L, KS, part,
+    return launch((linear_rb_kernel<R, M, SL>), dim3((unsigned)(L.RB * KS)), dim3(64 * W), 0, s, L, KS, part,
                        cnt);
 }
 template <int M> static hipError_t launch_linear_rb_m(const LayerDesc &L, float *part, int32_t *cnt, hipStream_t s) {
-    if (L.rs) return launch_linear_rb_rm<8, M, true>(L, part, cnt, s);
+    if constexpr (M <= kValuMaxM) {
+        if (L.rs) return launch_linear_rb_rm<8, M, true>(L, part, cnt, s);
+    }
     switch (L.r) {
         case 2: return launch_linear_rb_rm<2, M>(L, part, cnt, s);
         case 3: return launch_linear_rb_rm<3, M>(L, part, cnt, s);
@@ -449,28 +557,22 @@ template <int M> static hipError_t launch_linear_rb_m(const LayerDesc &L, float 
     }
     return hipErrorInvalidValue;
 }
-// The low-latency shape pays off while a wave owns few tiles; big layers stream better under
-// the persistent schedule.  Slots needed: RB * KS * M * 64 floats (KS <= 8).
-bool linear_rb_fits(const LayerDesc &L, size_t part_bytes) {
-    if ((int64_t)L.RB * L.G > 12288) return false;
-    return (size_t)L.RB * 8 * (size_t)L.M * 64 * sizeof(float) <= part_bytes;
-}
 hipError_t launch_linear_rb(const LayerDesc &L, float *part, int32_t *cnt, hipStream_t s) {
     switch (L.M) {
         case 1: return launch_linear_rb_m<1>(L, part, cnt, s);
         case 2: return launch_linear_rb_m<2>(L, part, cnt, s);
         case 3: return launch_linear_rb_m<3>(L, part, cnt, s);
         case 4: return launch_linear_rb_m<4>(L, part, cnt, s);
+        default: return L.M <= 8 ? launch_linear_rb_m<8>(L, part, cnt, s) : L.M <= kQuadMaxM ? launch_linear_rb_m<16>(L, part, cnt, s) : hipErrorInvalidValue;
     }
-    return hipErrorInvalidValue;
 }
 
 // The same shape for a SMALL stack (the linears of a decoder block that share their input, say): the workgroups of all
 // layers in one launch; a workgroup finds its layer and its descriptor in the kernel arguments (at most 16 layers).
-template <int M, int XP, bool SL, bool CH = false>
-__global__ __launch_bounds__(1024) void linear_rb_stack_kernel(const StackParams p, const SmallTable t) {
-    __shared__ float red[16][M][64];
-    __shared__ __attribute__((aligned(16))) uint32_t xlds_all[XP == kXLds ? 16 * M * 64 : 4];
+template <int M, bool SL, bool CH = false>
+__global__ __launch_bounds__(64 * kRbWaves<M>) void linear_rb_stack_kernel(const StackParams p, const SmallTable t) {
+    __shared__ __attribute__((aligned(16))) uint32_t red[kRbWaves<M>][M][kRowDwords<M>];
+    __shared__ __attribute__((aligned(16))) uint32_t xlds_all[kRbWaves<M> * M * kRowDwords<M>];
     // the grid holds exactly sum(RB * KS) workgroups; each layer's first one and the descriptors come with the kernel
     // arguments, so a workgroup reads nothing from device memory before its tiles (a walk along the table there was a
     // chain of dependent loads, 0.5 us each and 1.2 us for the first)
@@ -484,14 +586,14 @@ __global__ __launch_bounds__(1024) void linear_rb_stack_kernel(const StackParams
     int32_t *cnt = p.cnt + L.cnt_off;
     const ChainCtl chain{CH ? p.cnt + p.chain_off : nullptr, p.stage_rb, p.chain_total};
     if constexpr (SL) {
-        linear_rb_body<8, M, XP, true, CH>(L, KS, blk, slot0, p.part, cnt, red, xlds_all, chain);
+        linear_rb_body<8, M, true, CH>(L, KS, blk, slot0, p.part, cnt, red, xlds_all, chain);
     } else {
         switch (L.r) {
-            case 2: linear_rb_body<2, M, XP, false, CH>(L, KS, blk, slot0, p.part, cnt, red, xlds_all, chain); break;
-            case 3: linear_rb_body<3, M, XP, false, CH>(L, KS, blk, slot0, p.part, cnt, red, xlds_all, chain); break;
-            case 4: linear_rb_body<4, M, XP, false, CH>(L, KS, blk, slot0, p.part, cnt, red, xlds_all, chain); break;
-            case 6: linear_rb_body<6, M, XP, false, CH>(L, KS, blk, slot0, p.part, cnt, red, xlds_all, chain); break;
-            default: linear_rb_body<8, M, XP, false, CH>(L, KS, blk, slot0, p.part, cnt, red, xlds_all, chain); break;
+            case 2: linear_rb_body<2, M, false, CH>(L, KS, blk, slot0, p.part, cnt, red, xlds_all, chain); break;
+            case 3: linear_rb_body<3, M, false, CH>(L, KS, blk, slot0, p.part, cnt, red, xlds_all, chain); break;
+            case 4: linear_rb_body<4, M, false, CH>(L, KS, blk, slot0, p.part, cnt, red, xlds_all, chain); break;
+            case 6: linear_rb_body<6, M, false, CH>(L, KS, blk, slot0, p.part, cnt, red, xlds_all, chain); break;
+            default: linear_rb_body<8, M, false, CH>(L, KS, blk, slot0, p.part, cnt, red, xlds_all, chain); break;
         }
     }
 }
@@ -504,7 +606,7 @@ template <int M, bool SL, bool CH = false> static int rb_stack_resident(int wave
     int dev = 0, cus = 0, b = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, linear_rb_stack_kernel<M, kXLds, SL, CH>, 64 * waves, 0) != hipSuccess)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, linear_rb_stack_kernel<M, SL, CH>, 64 * waves, 0) != hipSuccess)
         return 0;
     cached[slot] = cus * (b < 1 ? 1 : b);
     return cached[slot];
@@ -521,7 +623,8 @@ static int rb_stack_resident_m(int M, bool from_parent, bool chained, int waves)
         case 1: return rb_stack_resident_v<1>(from_parent, chained, waves);
         case 2: return rb_stack_resident_v<2>(from_parent, chained, waves);
         case 3: return rb_stack_resident_v<3>(from_parent, chained, waves);
-        default: return rb_stack_resident_v<4>(from_parent, false, waves);
+        case 4: return rb_stack_resident_v<4>(from_parent, false, waves);
+        default: return M <= 8 ? rb_stack_resident<8, false>(waves) : rb_stack_resident<16, false>(waves);
     }
 }
 
@@ -532,13 +635,13 @@ static int rb_stack_resident_m(int M, bool from_parent, bool chained, int waves)
 // fit).  Then first the waves per workgroup are halved (a wave takes more tiles), then the K slices.
 bool linear_rb_stack_shape(const LayerDesc *table, int n_layers, size_t part_bytes, bool from_parent, bool chained,
                            int *blocks, int *waves, int *ks_cap, int32_t *ll_start, bool *all_resident) {
-    if (n_layers > kSmallStackLayers || table[0].M > kValuMaxM) return false;
-    int64_t tiles = 0, slots = 0;
+    if (n_layers > kSmallStackLayers || table[0].M > kQuadMaxM) return false;
+    int64_t tiles = 0, row_blocks = 0;
     for (int i = 0; i < n_layers; ++i) {
         tiles += (int64_t)table[i].RB * table[i].G;
-        slots += (int64_t)table[i].RB * 8;
+        row_blocks += table[i].RB;
     }
-    if (tiles > 12288 || (size_t)slots * (size_t)table[0].M * 64 * sizeof(float) > part_bytes) return false;
+    if (!low_latency_fits(row_blocks, tiles, table[0].M, part_bytes)) return false;
     auto shape = [&](int cap, int *nb, int *W) {
         *nb = 0;
         *W = 4;
@@ -580,14 +683,16 @@ template <int M> static hipError_t launch_linear_rb_stack_m(const StackParams &p
     if constexpr (M <= kChainMaxM) {
         if (p.chain_total) {
             if (from_parent)
-                return launch((linear_rb_stack_kernel<M, kXLds, true, true>), dim3((unsigned)blocks), dim3(64 * waves), 0, s, p, t);
-            return launch((linear_rb_stack_kernel<M, kXLds, false, true>), dim3((unsigned)blocks), dim3(64 * waves), 0, s, p, t);
+                return launch((linear_rb_stack_kernel<M, true, true>), dim3((unsigned)blocks), dim3(64 * waves), 0, s, p, t);
+            return launch((linear_rb_stack_kernel<M, false, true>), dim3((unsigned)blocks), dim3(64 * waves), 0, s, p, t);
         }
     }
     if (p.chain_total) return hipErrorInvalidValue;  // refused when the stack was planned
-    if (from_parent)
-        return launch((linear_rb_stack_kernel<M, kXLds, true>), dim3((unsigned)blocks), dim3(64 * waves), 0, s, p, t);
-    return launch((linear_rb_stack_kernel<M, kXLds, false>), dim3((unsigned)blocks), dim3(64 * waves), 0, s, p, t);
+    if constexpr (M <= kValuMaxM) {
+        if (from_parent)
+            return launch((linear_rb_stack_kernel<M, true>), dim3((unsigned)blocks), dim3(64 * waves), 0, s, p, t);
+    }
+    return launch((linear_rb_stack_kernel<M, false>), dim3((unsigned)blocks), dim3(64 * waves), 0, s, p, t);
 }
 hipError_t launch_linear_rb_stack(const StackParams &p, const SmallTable &t, int blocks, int waves, bool from_parent,
                                   hipStream_t s) {
@@ -596,18 +701,20 @@ hipError_t launch_linear_rb_stack(const StackParams &p, const SmallTable &t, int
         case 2: return launch_linear_rb_stack_m<2>(p, t, blocks, waves, from_parent, s);
         case 3: return launch_linear_rb_stack_m<3>(p, t, blocks, waves, from_parent, s);
         case 4: return launch_linear_rb_stack_m<4>(p, t, blocks, waves, from_parent, s);
+        default:
+            if (p.M > kQuadMaxM || from_parent) return hipErrorInvalidValue;
+            return p.M <= 8 ? launch_linear_rb_stack_m<8>(p, t, blocks, waves, false, s) : launch_linear_rb_stack_m<16>(p, t, blocks, waves, false, s);
     }
-    return hipErrorInvalidValue;
 }
 
 // blocks (of 4 waves) the device keeps resident per compute unit, and the number of units
-template <int M, int XP, bool SL> static bool residency(int &cus, int &blocks) {
+template <int M, bool SL> static bool residency(int &cus, int &blocks) {
     static int c_cus = 0, c_blocks = 0;
     if (!c_cus) {
         int dev = 0, a = 0, b = 0;
         if (hipGetDevice(&dev) != hipSuccess) return false;
         if (hipDeviceGetAttribute(&a, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return false;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, stack_kernel<M, XP, SL>, 256, 0) != hipSuccess) return false;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, stack_kernel<M, SL>, 256, 0) != hipSuccess) return false;
         if (b < 1) b = 1;
         while (a * b * 4 > kMaxWaves) --b;
         c_cus = a;
@@ -618,9 +725,9 @@ template <int M, int XP, bool SL> static bool residency(int &cus, int &blocks) {
     return true;
 }
 
-template <int M, int XP, bool SL> static hipError_t launch_stack_mx(StackParams p, int max_cost, hipStream_t s) {
+template <int M, bool SL> static hipError_t launch_stack_mx(StackParams p, int max_cost, hipStream_t s) {
     int cus = 0, blocks = 0;
-    if (!residency<M, XP, SL>(cus, blocks)) return hipErrorUnknown;
+    if (!residency<M, SL>(cus, blocks)) return hipErrorUnknown;
     int hw = cus * blocks * 4;
     if (p.worker_cap && hw > p.worker_cap) hw = p.worker_cap;
     const uint64_t max_workers = p.worker_cap ? (uint64_t)p.worker_cap : (uint64_t)max_workers_valu(M);
@@ -632,7 +739,7 @@ template <int M, int XP, bool SL> static hipError_t launch_stack_mx(StackParams 
     // A single big layer at batch 1 is over in 25-50 us: with every resident wave a share is only a few tiles
     // long and each row block is handed over many times.  A quarter of the waves still saturates HBM for that
     // long (each keeps its 8 KB in flight) and takes 10-25 % off the call (measured on the Llama-3-70B MLP shapes).
-    if (!p.table && M == 1 && p.nwaves > 2048) p.nwaves = 2048;
+    if (!p.table && p.nwaves > 2048) p.nwaves = 2048;
     // Several interleaved shares per wave even out layers of different width (a wave serves
     // shares w, w + nwaves, ...), but every share ends with up to two hand-overs of a few
     // microseconds, so shares stay at least ~128 tiles long (measured: Llama-2-7B stacks are
@@ -643,11 +750,10 @@ template <int M, int XP, bool SL> static hipError_t launch_stack_mx(StackParams 
     if (spw < 1) spw = 1;
     p.nworkers = (int)(spw * (uint64_t)p.nwaves);
     const unsigned nblocks = (unsigned)((p.nwaves + 3) / 4);
-    return launch((stack_kernel<M, XP, SL>), dim3(nblocks), dim3(256), 0, s, p);
+    return launch((stack_kernel<M, SL>), dim3(nblocks), dim3(256), 0, s, p);
 }
 template <int M> static hipError_t launch_stack_m(StackParams p, int max_cost, bool from_parent, hipStream_t s) {
-    // kXLds: measured 1-3 % (stack) to 20 % (single calls) faster than kXScalar
-    return from_parent ? launch_stack_mx<M, kXLds, true>(p, max_cost, s) : launch_stack_mx<M, kXLds, false>(p, max_cost, s);
+    return from_parent ? launch_stack_mx<M, true>(p, max_cost, s) : launch_stack_mx<M, false>(p, max_cost, s);
 }
 
 hipError_t launch_stack(StackParams p, int max_cost, bool from_parent, hipStream_t s) {
@@ -656,12 +762,13 @@ hipError_t launch_stack(StackParams p, int max_cost, bool from_parent, hipStream
         case 2: return launch_stack_m<2>(p, max_cost, from_parent, s);
         case 3: return launch_stack_m<3>(p, max_cost, from_parent, s);
         case 4: return launch_stack_m<4>(p, max_cost, from_parent, s);
+        default:
+            return p.M <= 8 && !from_parent ? launch_stack_mx<8, false>(p, max_cost, s) : hipErrorInvalidValue;
     }
-    return hipErrorInvalidValue;
 }
 
 // ------------------------------------------------------------------ bf16 activations for the kernels above
-// One small launch ahead of a vector-ALU launch whose layers (some of them) take bf16 activations (but for a single packed
+// One small launch ahead of a row kernel whose layers (some of them) take bf16 activations (but for a single packed
 // layer in the low-latency shape, which converts them itself): those layers'
 // activations (LayerDesc::x_bf16) go, as fp16, to the room the workspace keeps for them, which is where LayerDesc::x of
 // such a layer points: the kernels above never see the difference.  32 workgroups per layer; layers without the flag

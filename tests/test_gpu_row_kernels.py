@@ -1,0 +1,92 @@
+"""Batches of 2 .. 16 where one kernel takes over from another: the row kernels by 4x4x4 matrix instructions (built for 2, 3, 4, 8 and 16
+rows), the narrow kernel behind them, single layers, small stacks, stacks of more layers than travel with a launch, and bf16."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2602_03537_amd as mq
+from paper_2602_03537_amd import synth
+from gpu_util import C, DEV, WIDTHS, check_layer, check_y, dev, run_linear
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+BATCHES = (2, 3, 4, 5, 7, 8, 9, 12, 13, 16)
+
+
+@pytest.mark.parametrize("r", WIDTHS)
+@pytest.mark.parametrize("M", BATCHES)
+@pytest.mark.parametrize("shape", [(65, 128), (200, 1152), (1000, 2176)])   # one group; fewer and more groups than waves; K slices
+def test_single_layers(r, M, shape):
+    L = synth.make_random_codes_layer(*shape, M=M, seed=[501, M, *shape])
+    check_layer(run_linear(L, r), L, r, f"{shape} M={M} r={r}")
+
+
+def _put(L, r, M, flags=0):
+    lay = mq.prepare_layer(dev(L["parent"]), dev(L["scales"]), None if L["zeros"] is None else dev(L["zeros"]), r)
+    N = L["parent"].shape[0]
+    return dict(lay, x=dev(L["x"]), y=torch.full((M, N), float("nan"), dtype=torch.float16, device=DEV))
+
+
+# 3 layers: one launch in the low-latency shape; 17: the persistent row kernel up to 8 rows, the narrow kernel above
+@pytest.mark.parametrize("M", BATCHES)
+@pytest.mark.parametrize("n", [3, 17])
+def test_stacks(M, n):
+    shapes = [(65 + 61 * (i % 5), 128 * (1 + i % 4)) for i in range(n)]
+    widths = [WIDTHS[(i + M) % 5] for i in range(n)]
+    host = [synth.make_layer(N, K, M=M, seed=[502, M, i]) for i, (N, K) in enumerate(shapes)]
+    layers = [_put(L, r, M) for L, r in zip(host, widths)]
+    plan = mq.mq_stack_plan(layers, M, device=DEV)
+    outs = []
+    for _ in range(2):
+        mq.mq_linear_stack(plan)
+        torch.cuda.synchronize()
+        outs.append([lay["y"].clone() for lay in layers])
+    for i, (L, r) in enumerate(zip(host, widths)):
+        check_layer(outs[0][i], L, r, f"layer {i} of {n} M={M} r={r}")
+        assert torch.equal(outs[0][i], outs[1][i])          # fixed summation order
+
+
+@pytest.mark.parametrize("M", (2, 4, 5, 8, 11, 16))
+def test_bf16_is_the_same_arithmetic(M):
+    # sums that are exact in any order: the bf16 result is the rounding of the exact value
+    N, K = 300, 1280
+    rng = np.random.default_rng([503, M])
+    parent = rng.integers(0, 256, (N, K), dtype=np.uint8)
+    s = np.exp2(-rng.integers(7, 9, (N, K // 128)).astype(np.float64)).astype(np.float16)
+    z = rng.integers(0, 256, (N, K // 128)).astype(np.float16)
+    x = torch.from_numpy(rng.integers(-8, 9, (M, K)) / 4.0).to(torch.bfloat16)
+    for r in WIDTHS:
+        lay = mq.prepare_layer(dev(parent), dev(s), dev(z), r)
+        y = mq.mq_linear_bf16(x.to(DEV), lay["packed_W"], lay["scales_t"], lay["zeros_t"], N, K, r, 128, mq.new_workspace(M, N, K, r))
+        ref = oracle.linear(x.to(torch.float16).numpy(), parent, s, z, C, r, 128)
+        assert torch.equal(y.cpu(), torch.from_numpy(ref).to(torch.float32).to(torch.bfloat16)), r
+
+
+@pytest.mark.parametrize("M", (2, 3, 5, 8, 9, 16))
+def test_infinities_stay_in_their_batch_row(M):
+    N, K = 200, 768
+    L = synth.make_layer(N, K, M=M, seed=[504, M])
+    for m in (0, M - 1):
+        for v in (np.inf, -np.inf, np.nan):
+            x = L["x"].copy()
+            x[m, 5 + m] = v
+            for r in WIDTHS:
+                y = run_linear(dict(L, x=x), r).cpu()
+                assert not y[m].isfinite().any() and y[[i for i in range(M) if i != m]].isfinite().all(), (m, v, r)
+
+
+def test_layers_beyond_the_low_latency_shape_sampled_rows():
+    # 12 416 tiles: the persistent row kernel up to 8 rows, the narrow kernel above
+    N, K = 12401, 8192
+    L = synth.make_layer(N, K, M=16, seed=[505])
+    rows = np.unique(np.concatenate([[0, 63, 64, N - 2, N - 1], np.random.default_rng(506).integers(0, N, 90)]))
+    rt = torch.from_numpy(rows).to(DEV)
+    p, s, z = dev(L["parent"]), dev(L["scales"]), dev(L["zeros"])
+    for r in WIDTHS:
+        lay = mq.prepare_layer(p, s, z, r)
+        for M in (2, 3, 4, 5, 8, 9, 16):
+            y = mq.mq_linear(dev(L["x"][:M]), lay["packed_W"], lay["scales_t"], lay["zeros_t"], N, K, r, 128, mq.new_workspace(M, N, K, r))
+            torch.cuda.synchronize()
+            assert torch.isfinite(y).all()
+            check_y(y[:, rt], oracle.linear_rows(L["x"][:M], L["parent"], L["scales"], L["zeros"], C, r, 128, rows), f"M={M} r={r}")
