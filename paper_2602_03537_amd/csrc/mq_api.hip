@@ -149,14 +149,14 @@ LayerDesc make_desc(const mq_layer &l, int64_t M, int64_t Mp, bool rows, uint64_
         d.RB = (d.RB + kNarrowRowBlocks - 1) / kNarrowRowBlocks;
         d.cost = mfma_tile_cost(l.r);
     }
-    if (use_wide(Mp)) {  // scheduled in super-tiles of four row blocks
+    if (!rows && use_wide(Mp)) {  // scheduled in super-tiles of four row blocks
         d.RB = (d.RB + 3) / 4;
         d.cost = wide_tile_cost(l.r, wide_chunks_per_pass(Mp));
     }
     d.flags = l.flags & (MQ_X_BF16 | MQ_Y_BF16);
     d.cnt_off = cnt_off;
     d.M = (int32_t)M;
-    d.CB = (int32_t)chunks(Mp);
+    d.CB = rows ? 1 : (int32_t)chunks(Mp);
     d.job_start = job_start;
     d.cost_start = cost_start;
     return d;
@@ -286,7 +286,7 @@ mq_status run_single(const mq_layer &l, int64_t M, void *ws, size_t ws_bytes, mq
         if (launch_xcvt(p, (hipStream_t)stream) != hipSuccess) return MQ_ERR_HIP;
         p.single.x_bf16 = nullptr;  // from here on x is the fp16 copy
     }
-    if (use_wide(M))
+    if (use_wide(M) && !rows)
         e = launch_stack_wide(p, p.single.cost, (hipStream_t)stream);
     else if (!rows)
         e = launch_stack_mfma(p, p.single.cost, (hipStream_t)stream);
@@ -556,7 +556,7 @@ mq_status mq_stack_plan(const mq_layer *layers, int n_layers, int64_t M, void *p
         tiles += pad_rows(layers[i].N) / kRowBlock * (layers[i].K / kGroup);
     }
     // (more than kSmallStackLayers layers never have the low-latency shape)
-    const bool rows = use_row_kernels(M, row_blocks, n_layers > kSmallStackLayers && M > 8 ? INT64_MAX : tiles, false, partial_bytes(Mp));
+    const bool rows = use_row_kernels(M, row_blocks, (n_layers > kSmallStackLayers && M > 8) || M > 16 ? INT64_MAX : tiles, false, partial_bytes(Mp));
     char *base_dev = static_cast<char *>(plan_ws);
     int64_t counters = 0, jobs = 0;
     uint64_t cost = 0;

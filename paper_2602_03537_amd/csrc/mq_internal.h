@@ -38,7 +38,7 @@ constexpr int kCounterBytesAlign = 256;
 // activations.  "Wide" (mq_wide.hip): 32 columns per chunk, four waves per super-tile of 256 rows and up to kWideMaxChunks chunks
 // against one unpacked tile.  Workspaces are laid out by the batch alone: up to kValuMaxM, up to kNarrowMaxM, larger.
 constexpr int kValuMaxM = 4;
-constexpr int kQuadMaxM = 16;  // batch that a row kernel exists for
+constexpr int kQuadMaxM = 128;  // largest batch of the row kernels: a row block's counter has four bits for each chunk of 16
 constexpr int kChunkCols = 16;
 constexpr int kNarrowMaxM = 16;
 constexpr int kWideCols = 32;
@@ -47,16 +47,28 @@ constexpr int kWideXtBlockBytes = 8 * 1024;  // prepared activations of one (gro
 // batch rows that the row kernel serving a batch of M is built for (its partial sums have as many)
 inline int vector_rows(int64_t M) { return M <= 4 ? (int)M : M <= 8 ? 8 : 16; }
 // The low-latency shape pays off while a wave owns few tiles; larger layers stream better under the persistent schedule.
-// A row block has up to eight partial-sum slots.
+// Batches above 16 run in it as chunks of 16 rows (single layers only), each with the layer's tiles to itself; the wide kernel takes over
+// the earlier the more row blocks there are, as it gains from them and loses by cutting K.  us, wide / row kernel, r = 4, tiles times
+// chunks in brackets: 1500 x 8192 M = 128 [12 k] 44.5 / 34.3; 2048 x 14336 M = 64 [14 k] 38.4 / 27.1, M = 128 [29 k] 58.2 / 43.5; 4096 x 4096
+// M = 32 [4 k] 22.1 / 14.4, M = 128 [16 k] 37.7 / 25.9; 4096 x 11008 M = 64 [22 k] 38.2 / 35.1, M = 128 [44 k] 57.9 / 58.6; 8192 x 4096 M = 32
+// [8 k] 23.0 / 18.9, M = 48 [12 k] 27.8 / 26.5; 6000 x 6016 M = 48 [13 k] 33.4 / 35.4; 13003 x 2048 M = 32 [6.5 k] 21.0 / 16.6, M = 48 [10 k]
+// 25.6 / 24.6, M = 64 [13 k] 25.5 / 29.6; 28672 x 1024 M = 32 [7 k] 18.6 / 20.0.
+// A row block has up to eight partial-sum slots per chunk.
+inline int64_t low_latency_tiles(int64_t row_blocks, int64_t M) {
+    if (M <= 16) return 12288;
+    return row_blocks <= 32 ? 28672 : row_blocks <= 64 ? 16384 : row_blocks <= 128 ? 11008 : row_blocks <= 256 ? 8192 : 4096;
+}
 inline bool low_latency_fits(int64_t row_blocks, int64_t tiles, int64_t M, size_t part_bytes) {
-    return tiles <= 12288 && (size_t)row_blocks * 8 * (size_t)vector_rows(M) * 64 * sizeof(float) <= part_bytes;
+    const int64_t chunks = (M + 15) / 16;
+    return tiles <= low_latency_tiles(row_blocks, M) / chunks &&
+           (size_t)(row_blocks * chunks) * 8 * (size_t)vector_rows(M) * 64 * sizeof(float) <= part_bytes;
 }
 // Row kernels serve
 //   * every batch up to kValuMaxM;
 //   * 5 .. 8 rows: every single layer (us, narrow kernel / row kernel: 4096 x 4096 20.8 / 8.9, 28672 x 8192 40 / 31 at r = 4, 59.5 / 47.5 at
 //     r = 8), and stacks up to kRowStackTiles tiles (Llama-2-7B blocks at M = 8: four of them, 99 k tiles, 102 / 90; Llama-3-70B blocks: four,
 //     417 k, 361 / 379, where the narrow kernel's shared activations win);
-//   * 9 .. 16 rows: what fits the low-latency shape (M = 16, r = 4: 4096 x 4096 22.2 / 11.5, 13003 x 5120 30.7 / 22.0; beyond it 28672 x 8192
+//   * 9 .. kQuadMaxM rows: what fits the low-latency shape (M = 16, r = 4: 4096 x 4096 22.2 / 11.5, 13003 x 5120 30.7 / 22.0; beyond it 28672 x 8192
 //     would be 41.7 / 49.9: every tile reads its activations from LDS anew).
 constexpr int64_t kRowStackTiles = 200000;
 inline bool use_row_kernels(int64_t M, int64_t row_blocks, int64_t tiles, bool single, size_t part_bytes) {

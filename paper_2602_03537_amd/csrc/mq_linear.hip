@@ -399,7 +399,7 @@ __device__ __forceinline__ void chain_announce(const ChainCtl &c, int stage, int
 template <int R, int M, bool SL, bool CH = false, bool XB = false>
 __device__ __forceinline__ void linear_rb_body(const LayerDesc &L, const int KS, const int blk, const int slot0,
                                                float *part, int32_t *cnt, uint32_t (*red)[M][kRowDwords<M>], uint32_t *xlds_all,
-                                               const ChainCtl chain = ChainCtl{nullptr, nullptr, 0}) {
+                                               const ChainCtl chain = ChainCtl{nullptr, nullptr, 0}, const int chunk = 0) {
     uint32_t *xlds = xlds_all + (threadIdx.x >> 6) * M * kRowDwords<M>;
     const int lane = threadIdx.x & 63;
     const int w = threadIdx.x >> 6, W = blockDim.x >> 6;
@@ -457,9 +457,11 @@ __device__ __forceinline__ void linear_rb_body(const LayerDesc &L, const int KS,
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         int old = 0;
-        if (lane == 0) old = __hip_atomic_fetch_add(gl(cnt + rb), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // (a counter serves up to eight chunks of batch rows, four bits each)
+        const int shift = M > 8 ? 4 * chunk : 0;
+        if (lane == 0) old = __hip_atomic_fetch_add(gl(cnt + rb), (int)(1u << shift), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         old = __builtin_amdgcn_readfirstlane(old);
-        if (old != KS - 1) return;
+        if ((M > 8 ? (int)((uint32_t)old >> shift & 15u) : old) != KS - 1) return;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
         const float MQ_GLOBAL *src = gl(part + ((size_t)(slot0 + rb * KS) * M) * 64 + lane);
         float v[8][M];
@@ -476,7 +478,10 @@ __device__ __forceinline__ void linear_rb_body(const LayerDesc &L, const int KS,
             for (int i = 1; i < 8; ++i)
                 if (i < KS) tot[m] += v[i][m];
         }
-        if (lane == 0) __hip_atomic_store(gl(cnt + rb), 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (lane == 0) {
+            if constexpr (M > 8) __hip_atomic_fetch_add(gl(cnt + rb), (int)-((uint32_t)KS << shift), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else __hip_atomic_store(gl(cnt + rb), 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     }
     if constexpr (CH) {
 #pragma unroll
@@ -499,13 +504,34 @@ template <int R, int M, bool SL = false, bool XB = false>
 __global__ __launch_bounds__(64 * kRbWaves<M>) void linear_rb_kernel(const LayerDesc L, const int KS, float *part, int32_t *cnt) {
     __shared__ __attribute__((aligned(16))) uint32_t red[kRbWaves<M>][M][kRowDwords<M>];
     __shared__ __attribute__((aligned(16))) uint32_t xlds_all[kRbWaves<M> * M * kRowDwords<M>];
-    linear_rb_body<R, M, SL, false, XB>(L, KS, (int)blockIdx.x, 0, part, cnt, red, xlds_all);
+    if constexpr (M <= 8) {
+        linear_rb_body<R, M, SL, false, XB>(L, KS, (int)blockIdx.x, 0, part, cnt, red, xlds_all);
+    } else {
+        // 16 batch rows per workgroup; the workgroups that share a tile's weights have numbers 8 apart: one compute die's, one L2's
+        const int nc = (L.M + 15) / 16, units = L.RB * KS;
+        const int t = (int)blockIdx.x / (8 * nc), v = (int)blockIdx.x % (8 * nc), chunk = v / 8, blk = 8 * t + v % 8;
+        if (blk >= units) return;
+        LayerDesc C = L;
+        C.x += (size_t)(16 * chunk) * L.K;
+        C.y += (size_t)(16 * chunk) * L.N;
+        C.M = L.M - 16 * chunk < 16 ? L.M - 16 * chunk : 16;
+        linear_rb_body<R, M, SL, false, XB>(C, KS, blk, chunk * units, part, cnt, red, xlds_all, ChainCtl{nullptr, nullptr, 0}, chunk);
+    }
 }
 
 // Launch shape, from sweeps on Llama-2-7B / Llama-3-70B shapes (cold weights): enough K slices
 // that (a) there are >= 256 workgroups when there are few row blocks and (b) no wave owns more
 // than about two tiles; at most 8 slices, each at least 4 groups long.
 __host__ __device__ static inline int pick_k_slices(const LayerDesc &L) {
+    if (L.M > 8) {
+        // The device holds 512 workgroups (four waves of up to 256 registers): as many slices as keep all of them resident at one time
+        // (4096 x 4096, r = 4, us, with up to 512 / 1024 workgroups: M = 32 14.3 / 18.9, M = 64 19.0 / 25.3)
+        const int wgs = L.RB * ((L.M + 15) / 16);
+        int ks = 512 / wgs;
+        if (ks > 8) ks = 8;
+        while (ks > 1 && L.G / ks < 4) --ks;
+        return ks < 1 ? 1 : ks;
+    }
     const int cover = L.RB >= 128 ? 1 : (256 + L.RB - 1) / L.RB;
     const int depth = (L.G + 31) / 32;
     int ks = cover > depth ? cover : depth;
@@ -533,15 +559,16 @@ template <int R, int M, bool SL = false>
 static hipError_t launch_linear_rb_rm(const LayerDesc &L, float *part, int32_t *cnt, hipStream_t s) {
     const int KS = pick_k_slices(L);
     const int W = rb_waves(L, KS);
+    const unsigned blocks = M > 8 ? (unsigned)((L.RB * KS + 7) / 8 * 8 * ((L.M + 15) / 16)) : (unsigned)(L.RB * KS);
     if constexpr (!SL) {  // a single from-parent call takes fp16 activations
         if (L.x_bf16) {
             LayerDesc B = L;
             B.x = static_cast<const _Float16 *>(L.x_bf16);
-            return launch((linear_rb_kernel<R, M, false, true>), dim3((unsigned)(L.RB * KS)), dim3(64 * W), 0, s, B, KS, part,
+            return launch((linear_rb_kernel<R, M, false, true>), dim3(blocks), dim3(64 * W), 0, s, B, KS, part,
                           cnt);
         }
     }
-    return launch((linear_rb_kernel<R, M, SL>), dim3((unsigned)(L.RB * KS)), dim3(64 * W), 0, s, L, KS, part,
+    return launch((linear_rb_kernel<R, M, SL>), dim3(blocks), dim3(64 * W), 0, s, L, KS, part,
                        cnt);
 }
 template <int M> static hipError_t launch_linear_rb_m(const LayerDesc &L, float *part, int32_t *cnt, hipStream_t s) {
@@ -635,7 +662,7 @@ static int rb_stack_resident_m(int M, bool from_parent, bool chained, int waves)
 // fit).  Then first the waves per workgroup are halved (a wave takes more tiles), then the K slices.
 bool linear_rb_stack_shape(const LayerDesc *table, int n_layers, size_t part_bytes, bool from_parent, bool chained,
                            int *blocks, int *waves, int *ks_cap, int32_t *ll_start, bool *all_resident) {
-    if (n_layers > kSmallStackLayers || table[0].M > kQuadMaxM) return false;
+    if (n_layers > kSmallStackLayers || table[0].M > 16) return false;
     int64_t tiles = 0, row_blocks = 0;
     for (int i = 0; i < n_layers; ++i) {
         tiles += (int64_t)table[i].RB * table[i].G;
@@ -702,7 +729,7 @@ hipError_t launch_linear_rb_stack(const StackParams &p, const SmallTable &t, int
         case 3: return launch_linear_rb_stack_m<3>(p, t, blocks, waves, from_parent, s);
         case 4: return launch_linear_rb_stack_m<4>(p, t, blocks, waves, from_parent, s);
         default:
-            if (p.M > kQuadMaxM || from_parent) return hipErrorInvalidValue;
+            if (p.M > 16 || from_parent) return hipErrorInvalidValue;
             return p.M <= 8 ? launch_linear_rb_stack_m<8>(p, t, blocks, waves, false, s) : launch_linear_rb_stack_m<16>(p, t, blocks, waves, false, s);
     }
 }

@@ -1,4 +1,4 @@
-"""Batches of 2 .. 16 where one kernel takes over from another: the row kernels by 4x4x4 matrix instructions (built for 2, 3, 4, 8 and 16
+"""Batches of 2 .. 128 where one kernel takes over from another: the row kernels by 4x4x4 matrix instructions (built for 2, 3, 4, 8 and 16
 rows), the narrow kernel behind them, single layers, small stacks, stacks of more layers than travel with a launch, and bf16."""
 import numpy as np
 import pytest
@@ -22,7 +22,40 @@ def test_single_layers(r, M, shape):
     check_layer(run_linear(L, r), L, r, f"{shape} M={M} r={r}")
 
 
-def _put(L, r, M, flags=0):
+@pytest.mark.parametrize("r", WIDTHS)
+@pytest.mark.parametrize("M", (17, 33, 100, 128))
+@pytest.mark.parametrize("shape", [(65, 128), (200, 1152), (1000, 2176), (4100, 640)])
+def test_single_layers_in_chunks_of_16_rows(r, M, shape):
+    # (row blocks with a last chunk of 1 and 4 rows; not, one, and several times cut along K; one counter for all chunks of a row block)
+    N, K = shape
+    L = synth.make_random_codes_layer(N, K, M=M, seed=[507, M, N, K])
+    lay = mq.prepare_layer(dev(L["parent"]), dev(L["scales"]), dev(L["zeros"]), r)
+    ws, x = mq.new_workspace(M, N, K, r), dev(L["x"])
+    buf = torch.full((M * N + 128,), float("nan"), dtype=torch.float16, device=DEV)
+    outs = []
+    for _ in range(2):
+        y = buf[64:64 + M * N].view(M, N).fill_(float("nan"))
+        mq.mq_linear(x, lay["packed_W"], lay["scales_t"], lay["zeros_t"], N, K, r, 128, ws, y)
+        torch.cuda.synchronize()
+        outs.append(y.clone())
+    check_layer(outs[0], L, r, f"{shape} M={M} r={r}")
+    assert torch.equal(outs[0], outs[1])                # counters left at zero, fixed summation order
+    assert torch.isnan(buf[:64]).all() and torch.isnan(buf[64 + M * N:]).all()
+
+
+@pytest.mark.parametrize("M", (20, 64, 65, 128))        # one to four chunks of the wide kernel, where it still serves single layers
+def test_many_rows_keep_the_wide_kernel_sampled_rows(M):
+    N, K = 16500, 1152
+    L = synth.make_layer(N, K, M=M, seed=[508, M])
+    rows = np.unique(np.concatenate([[0, 63, 64, 255, 256, N - 2, N - 1], np.random.default_rng(509).integers(0, N, 60)]))
+    for r in WIDTHS:
+        y = run_linear(L, r)
+        assert torch.isfinite(y).all()
+        check_y(y[:, torch.from_numpy(rows).to(DEV)], oracle.linear_rows(L["x"], L["parent"], L["scales"], L["zeros"], C, r, 128, rows),
+                f"M={M} r={r}")
+
+
+def _put(L, r, M):
     lay = mq.prepare_layer(dev(L["parent"]), dev(L["scales"]), None if L["zeros"] is None else dev(L["zeros"]), r)
     N = L["parent"].shape[0]
     return dict(lay, x=dev(L["x"]), y=torch.full((M, N), float("nan"), dtype=torch.float16, device=DEV))
@@ -47,7 +80,7 @@ def test_stacks(M, n):
         assert torch.equal(outs[0][i], outs[1][i])          # fixed summation order
 
 
-@pytest.mark.parametrize("M", (2, 4, 5, 8, 11, 16))
+@pytest.mark.parametrize("M", (2, 4, 5, 8, 11, 16, 40))
 def test_bf16_is_the_same_arithmetic(M):
     # sums that are exact in any order: the bf16 result is the rounding of the exact value
     N, K = 300, 1280
