@@ -52,11 +52,12 @@ inline int vector_rows(int64_t M) { return M <= 4 ? (int)M : M <= 8 ? 8 : 16; }
 // chunks in brackets: 1500 x 8192 M = 128 [12 k] 44.5 / 34.3; 2048 x 14336 M = 64 [14 k] 38.4 / 27.1, M = 128 [29 k] 58.2 / 43.5; 4096 x 4096
 // M = 32 [4 k] 22.1 / 14.4, M = 128 [16 k] 37.7 / 25.9; 4096 x 11008 M = 64 [22 k] 38.2 / 35.1, M = 128 [44 k] 57.9 / 58.6; 8192 x 4096 M = 32
 // [8 k] 23.0 / 18.9, M = 48 [12 k] 27.8 / 26.5; 6000 x 6016 M = 48 [13 k] 33.4 / 35.4; 13003 x 2048 M = 32 [6.5 k] 21.0 / 16.6, M = 48 [10 k]
-// 25.6 / 24.6, M = 64 [13 k] 25.5 / 29.6; 28672 x 1024 M = 32 [7 k] 18.6 / 20.0.
+// 25.6 / 24.6, M = 64 [13 k] 25.5 / 29.6; 13003 x 1280 M = 72 [10 k] 33.4 / 27.8, M = 128 [16 k] 38.8 / 38.9; 7849 x 1920 M = 103 [13 k] 39.1 / 28.4;
+// 8192 x 3072 M = 96 [18 k] 32.3 / 33.2; 28672 x 1024 M = 32 [7 k] 18.6 / 20.0.
 // A row block has up to eight partial-sum slots per chunk.
 inline int64_t low_latency_tiles(int64_t row_blocks, int64_t M) {
     if (M <= 16) return 12288;
-    return row_blocks <= 32 ? 28672 : row_blocks <= 64 ? 16384 : row_blocks <= 128 ? 11008 : row_blocks <= 256 ? 8192 : 4096;
+    return row_blocks <= 32 ? 28672 : row_blocks <= 64 ? 16384 : row_blocks <= 128 ? 13000 : row_blocks <= 256 ? (M <= 64 ? 9600 : 12288) : 4096;
 }
 inline bool low_latency_fits(int64_t row_blocks, int64_t tiles, int64_t M, size_t part_bytes) {
     const int64_t chunks = (M + 15) / 16;
