@@ -132,6 +132,7 @@ struct StackParams {
     int32_t M;
     int32_t slot_floats;     // floats per partial-sum slot (64*M; a workgroup's 8 x 64*16 on the narrow matrix-core path)
     int32_t n_jobs;          // prep kernel jobs (MFMA path)
+    int32_t finish_apart;    // wide kernel: row blocks that several shares worked on are finished by a launch of its own
     int32_t worker_cap;      // 0, or: `part` holds slots for this many schedule shares only (a small workspace)
     int32_t ks_cap;          // low-latency launch of a small stack: most K slices per row block (0: as one layer would choose)
     int32_t ll_start[16];    // ... and the first workgroup of each layer (a workgroup finds its layer without reading the table)

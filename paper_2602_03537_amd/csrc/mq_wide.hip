@@ -293,6 +293,7 @@ __device__ __forceinline__ void finish_row_block_blocked(const LayerDesc &L, con
         for (int i = 0; i < BLK; ++i)
             __hip_atomic_store(mine + (b * BLK + i) * 64, v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     });
+    if (p.finish_apart) return;  // wide_finish_kernel adds the slots up
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     int old = 0;
@@ -658,6 +659,48 @@ template <int C, bool TWO = false> __global__ __launch_bounds__(256, TWO ? 2 : 1
     });
 }
 
+// The row blocks of a single layer that several shares worked on: their slots added up in share order, and y.  A launch of its
+// own (3 us): inside the kernel above, the last contributor of a row block adds up to eight slots of 16 KB a wave, with most of the chip
+// idle, after a store, a counter and a load one behind the other; here every 4 values of a lane have a wave.
+// One workgroup per (pass, row block, 16 values), a wave for four of them.
+template <int C> __global__ __launch_bounds__(256) void wide_finish_kernel(const StackParams p) {
+    const LayerDesc &L = p.single;
+    const int lane = threadIdx.x & 63, quarter = (int)(threadIdx.x >> 6);
+    const int rb_real = (L.N + kRowBlock - 1) / kRowBlock;
+    const int b = (int)(blockIdx.x % (2 * C)), unit = (int)(blockIdx.x / (2 * C));
+    const int pass = unit / rb_real, rb = unit - pass * rb_real, srb = rb / 4, wv = rb % 4;
+    const uint64_t a = ((uint64_t)pass * L.RB * L.G + (uint64_t)srb * L.G) * L.cost;
+    const int w_lo = wave_of(a, p.nworkers, p.cost_total);
+    const int w_hi = wave_of(a + (uint64_t)(L.G - 1) * L.cost, p.nworkers, p.cost_total);
+    if (w_lo == w_hi) return;  // one share did it all and has stored y
+    const float MQ_GLOBAL *part = gl(p.part) + (size_t)wv * (C * 32 * 64) + (b * 16 + quarter * 4) * 64 + lane;
+    float tot[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) tot[v] = part[(size_t)(w_lo * 2 + 1) * p.slot_floats + v * 64];
+    constexpr int kBatch = 8;
+    for (int w0 = w_lo + 1; w0 <= w_hi; w0 += kBatch) {
+        float t[kBatch][4];
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+            const float MQ_GLOBAL *src = part + (size_t)((w0 + j <= w_hi ? w0 + j : w_hi) * 2) * p.slot_floats;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) t[j][v] = src[v * 64];
+        }
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j)
+            if (w0 + j <= w_hi) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) tot[v] += t[j][v];
+            }
+    }
+    const int row = rb * kRowBlock + 32 * (b % 2) + (lane & 31);
+    const int col = (pass * C + b / 2) * kWideCols + 8 * quarter + 4 * (lane >> 5);
+    if (row >= L.N) return;
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+        if (col + v < L.M) store_y(L.y, (size_t)(col + v) * L.N + row, tot[v], L.flags);
+}
+
 // workgroups the device keeps resident for a launch with lds_bytes of LDS per workgroup
 template <int C, bool TWO> static int wide_resident_groups(int lds_bytes) {
     static int cached_bytes[2] = {0, 0}, cached[2] = {0, 0};
@@ -695,17 +738,33 @@ template <int C, bool TWO> static hipError_t launch_wide_c(StackParams p, int ma
     }
     const int hw = wide_resident_groups<C, TWO>(lds_bytes);
     if (hw <= 0) return hipErrorUnknown;
-    // shares of at least eight super-tiles: a small layer cut into more shares spends more on handing its row blocks
-    // over than it gains in parallelism (Llama-2-7B shapes at M = 128: 52 -> 40 us per call)
-    uint64_t cap = p.cost_total / ((uint64_t)max_cost * 8);
-    if (cap < 1) cap = 1;
-    p.nworkers = (int)(cap < (uint64_t)hw ? cap : (uint64_t)hw);
+    // Shares of at least eight super-tiles: a small layer cut into more shares spends more on handing its row blocks
+    // over than it gains in parallelism (Llama-2-7B shapes at M = 128: 52 -> 40 us per call); of four where the slots are added up by
+    // a launch of its own, which takes over for a single layer where three and more shares meet in a row block, or slots are large
+    // (three or four chunks).  us with the last contributor adding up / now, r = 4: 8192 x 28672 M = 61 63.9 / 58.4, M = 128 98.3 / 81.8; 8192 x
+    // 8192 M = 64 34.4 / 29.3; 4096 x 11008 M = 128 59.4 / 35.5, M = 256 67.1 / 46.1; 13003 x 5120 M = 128 51.5 / 39.3.  Two to three shares
+    // and one or two chunks lose: 28672 x 8192 M = 24 48.7 / 49.3, M = 64 60.5 / 61.7.
+    auto workers = [&](uint64_t least) {
+        uint64_t cap = p.cost_total / ((uint64_t)max_cost * least);
+        if (cap < 1) cap = 1;
+        return (int)(cap < (uint64_t)hw ? cap : (uint64_t)hw);
+    };
+    p.nworkers = workers(8);
+    p.finish_apart = 0;
+    const int64_t tiles = p.table ? 0 : (int64_t)p.single.CB * p.single.RB * p.single.G;
+    if (!p.table) {
+        const int more = workers(4);
+        if (C >= 3 || p.single.G * more >= 3 * tiles) {
+            p.finish_apart = 1;
+            p.nworkers = more;
+        }
+    }
     if (!p.table && p.nworkers == hw) {
         // Single layer: every workgroup re-reads the activations of a group for each of its row blocks, which
         // only stays cheap while the workgroups of a chip walk the SAME groups at the same time (then one
         // fetch serves them all from the L2).  Equal shares do that when a share is a whole number of row
         // blocks, or a whole fraction of one: give up a few compute units for such a share length.
-        const int64_t G = p.single.G, T = (int64_t)p.single.CB * p.single.RB * G;
+        const int64_t G = p.single.G, T = tiles;
         for (int w = hw; w >= hw - hw / 4; --w) {
             if (T % w) continue;
             const int64_t len = T / w;
@@ -719,7 +778,11 @@ template <int C, bool TWO> static hipError_t launch_wide_c(StackParams p, int ma
     p.slot_floats = 4 * C * 32 * 64;
     const hipError_t e = launch(xprep_wide_kernel, dim3((unsigned)p.n_jobs), dim3(256), 0, s, p);
     if (e != hipSuccess) return e;
-    return launch(wide_stack_kernel<C, TWO>, dim3((unsigned)p.nworkers), dim3(256), (unsigned)lds_bytes, s, p);
+    const hipError_t e2 = launch(wide_stack_kernel<C, TWO>, dim3((unsigned)p.nworkers), dim3(256), (unsigned)lds_bytes, s, p);
+    if (e2 != hipSuccess || !p.finish_apart) return e2;
+    if (tiles % p.nworkers == 0 && tiles / p.nworkers % p.single.G == 0) return e2;  // whole row blocks only
+    const unsigned units = (unsigned)(p.single.CB * ((p.single.N + kRowBlock - 1) / kRowBlock));
+    return launch(wide_finish_kernel<C>, dim3(units * 2 * C), dim3(256), 0, s, p);
 }
 
 hipError_t launch_stack_wide(StackParams p, int max_cost, hipStream_t s) {

@@ -1,4 +1,4 @@
-"""Batches of 2 .. 128 where one kernel takes over from another: the row kernels by 4x4x4 matrix instructions (built for 2, 3, 4, 8 and 16
+"""Batches where one kernel takes over from another, 2 .. 256 rows: the row kernels by 4x4x4 matrix instructions (built for 2, 3, 4, 8 and 16
 rows), the narrow kernel behind them, single layers, small stacks, stacks of more layers than travel with a launch, and bf16."""
 import numpy as np
 import pytest
@@ -49,6 +49,29 @@ def test_many_rows_keep_the_wide_kernel_sampled_rows(M):
     L = synth.make_layer(N, K, M=M, seed=[508, M])
     rows = np.unique(np.concatenate([[0, 63, 64, 255, 256, N - 2, N - 1], np.random.default_rng(509).integers(0, N, 60)]))
     for r in WIDTHS:
+        y = run_linear(L, r)
+        assert torch.isfinite(y).all()
+        check_y(y[:, torch.from_numpy(rows).to(DEV)], oracle.linear_rows(L["x"], L["parent"], L["scales"], L["zeros"], C, r, 128, rows),
+                f"M={M} r={r}")
+
+
+@pytest.mark.parametrize("M", (129, 200, 256))          # three and four chunks, two passes
+@pytest.mark.parametrize("shape", [(65, 2176), (300, 4096), (1000, 640)])
+def test_wide_row_blocks_finished_by_a_launch_of_their_own(M, shape):
+    N, K = shape
+    L = synth.make_layer(N, K, M=M, seed=[510, M, N, K])
+    for r in WIDTHS:
+        y = run_linear(L, r)
+        check_layer(y, L, r, f"{shape} M={M} r={r}")
+        assert torch.equal(y, run_linear(L, r))
+
+
+@pytest.mark.parametrize("M", (20, 64))                 # one and two chunks, long sums: many shares in a row block
+def test_wide_many_shares_in_a_row_block_sampled_rows(M):
+    N, K = 4200, 12672
+    L = synth.make_layer(N, K, M=M, seed=[511, M])
+    rows = np.unique(np.concatenate([[0, 63, 64, 4159, 4160, N - 1], np.random.default_rng(512).integers(0, N, 60)]))
+    for r in (3, 6):
         y = run_linear(L, r)
         assert torch.isfinite(y).all()
         check_y(y[:, torch.from_numpy(rows).to(DEV)], oracle.linear_rows(L["x"], L["parent"], L["scales"], L["zeros"], C, r, 128, rows),
