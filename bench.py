@@ -13,7 +13,7 @@ streams from HBM.
 Prints ONE JSON line: effective HBM GB/s over the step (algorithmic bytes:
 r/8 per weight + fp16 scale and zero per group + activations in and out), the
 per-r microseconds and GB/s, the roofline object of the dominant kernel
-(mq::stack_kernel<1, 1, false>, HBM-bound) measured with events on the launch stream, and
+(mq::stack_kernel<1, false>, HBM-bound) measured with events on the launch stream, and
 the CPU oracle timed on the host cores on a bounded sample.
 """
 from __future__ import annotations
@@ -31,7 +31,7 @@ if ROOT not in sys.path:
 HBM_PEAK_GBPS = 8000.0
 WIDTHS = (2, 3, 4, 6, 8)
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "stack_kernel_llama2_7b_m1_hbm_traffic.txt")
-# the sources that define mq::stack_kernel<1, 1, false>: a traffic figure is quoted only while they are the ones profiled
+# the sources that define mq::stack_kernel<1, false>: a traffic figure is quoted only while they are the ones profiled
 KERNEL_SOURCES = ("mq_linear.hip", "mq_device.h", "mq_layout.h", "mq_internal.h", "mq_static_for.h")
 
 
@@ -204,12 +204,12 @@ def main() -> int:
                          "frac_of_8TBps": round(gbps / HBM_PEAK_GBPS, 4), "algorithmic_MB": round(stacks[r]["bytes"] / 1e6, 1)}
     value = step_bytes / (ms_per_step * 1e-3) / 1e9
 
-    # roofline of the dominant kernel (mq::stack_kernel<1, 1, false>): algorithmic bytes per launch / mean launch duration
+    # roofline of the dominant kernel (mq::stack_kernel<1, false>): algorithmic bytes per launch / mean launch duration
     launches = [u for r in WIDTHS for u in per_r_us[r]]
     avg_launch_us = float(np.mean(launches))
     bytes_per_launch = step_bytes / len(WIDTHS)
     achieved = bytes_per_launch / avg_launch_us / 1e3
-    roofline = {"bound": "hbm", "kernel": "mq::stack_kernel<1, 1, false>", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS,
+    roofline = {"bound": "hbm", "kernel": "mq::stack_kernel<1, false>", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4),
                 "avg_launch_us": round(avg_launch_us, 1), "algorithmic_bytes_per_launch": int(bytes_per_launch)}
     traffic, traffic_src = traffic_from_profile() if args.layers == 32 else (None, "not the profiled workload")
@@ -431,7 +431,7 @@ def measure_mixed_stack(mq, synth, torch, np, dev, big, n_blocks, M, steps, warm
     torch.cuda.synchronize()
     ms = (time.perf_counter() - t0) * 1e3 / steps
     us = [evs[k].elapsed_time(evs[k + 1]) * 1e3 for k in range(steps)]
-    kernel = ("mq::stack_kernel<%d, 1, false>" % M if M <= 3 else "mq::gemm_stack_kernel" if M <= 16
+    kernel = ("mq::stack_kernel<%d, false>" % M if M <= 4 else "mq::gemm_stack_kernel" if M <= 16
               else "mq::wide_stack_kernel")
     return {"ms_wall": ms, "us": us, "bytes": nbytes, "mean_bits": mean, "n_linears": len(layers), "n_blocks": n_blocks,
             "kernel": kernel, "weights": weights}
@@ -500,7 +500,7 @@ def bench_resident_parent(args, mq, synth, torch, np, dev):
     ach = nbytes / float(np.mean(us)) / 1e3
     out["stack_us_median"] = round(float(np.median(us)), 1)
     out["frac_of_hbm_peak"] = round(value / HBM_PEAK_GBPS, 4)
-    out["roofline"] = {"bound": "hbm", "kernel": "mq::stack_kernel<%d, 1, true>" % M, "achieved": round(ach, 1),
+    out["roofline"] = {"bound": "hbm", "kernel": "mq::stack_kernel<%d, true>" % M, "achieved": round(ach, 1),
                        "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBPS, 4),
                        "avg_launch_us": round(float(np.mean(us)), 1), "algorithmic_bytes_per_launch": int(nbytes),
                        "traffic": None}
@@ -807,7 +807,7 @@ def bench_decode_fusions(args, mq, synth, torch, np, dev):
                      t_f * 1e3, f"Llama-2-7B decoder blocks x{n_blocks}, M={M}, per-layer r by seed (mean {mean:.3f} bits): "
                      "q/k/v and gate/up as one mq_linear_stack launch each, o and down as mq_linear", {"M": M})
     out["table"] = res
-    out["roofline"] = {"bound": "hbm", "kernel": "mq::stack_kernel<%d, 1, false> + mq::linear_rb_kernel" % M,
+    out["roofline"] = {"bound": "hbm", "kernel": "mq::stack_kernel<%d, false> + mq::linear_rb_kernel" % M,
                        "achieved": res["fused_qkv_and_gate_up"]["GBps"], "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                        "frac": round(res["fused_qkv_and_gate_up"]["GBps"] / HBM_PEAK_GBPS, 4), "avg_launch_us": None,
                        "algorithmic_bytes_per_launch": None, "traffic": None}

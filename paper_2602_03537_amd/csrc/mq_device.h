@@ -139,7 +139,8 @@ template <class F> __device__ __forceinline__ void walk_tiles(const StackParams 
 //   a       : cost position of the row block's first tile
 // Partial sums travel through agent-scope atomic stores/loads (write-through, cache
 // bypassing), so no whole-L2 write-back or invalidate is needed to publish them.
-template <int NV, class Final>
+// APART: where p.finish_apart says so, a later launch adds the slots up instead (nothing is counted).
+template <int NV, bool APART = false, class Final>
 __device__ __forceinline__ void finish_row_block(const LayerDesc &L, const StackParams &p, int32_t *cnt, uint64_t a,
                                                  int ga, int gb, float (&acc)[NV], int worker, int lane, Final &&final) {
     if (ga == 0 && gb == L.G) {
@@ -151,6 +152,7 @@ __device__ __forceinline__ void finish_row_block(const LayerDesc &L, const Stack
     float MQ_GLOBAL *mine = gl(p.part + (size_t)(worker * 2 + slot) * slot_floats + lane);
 #pragma unroll
     for (int v = 0; v < NV; ++v) __hip_atomic_store(mine + v * 64, acc[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (APART && p.finish_apart) return;
     // the write-through stores must have been acknowledged before the counter moves
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -187,6 +189,30 @@ __device__ __forceinline__ void finish_row_block(const LayerDesc &L, const Stack
     }
     final(tot);
     if (lane == 0) __hip_atomic_store(gl(cnt), 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Four values of a row block's lanes, added up over the slots of shares w_lo .. w_hi in share order (launches that finish row
+// blocks apart).  part: the first value in slot 0 of share 0.
+__device__ __forceinline__ void sum_slots(const float *part0, int w_lo, int w_hi, size_t slot_floats, float (&tot)[4]) {
+    const float MQ_GLOBAL *part = gl(part0);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) tot[v] = part[(size_t)(w_lo * 2 + 1) * slot_floats + v * 64];
+    constexpr int kBatch = 8;
+    for (int w0 = w_lo + 1; w0 <= w_hi; w0 += kBatch) {
+        float t[kBatch][4];
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+            const float MQ_GLOBAL *src = part + (size_t)((w0 + j <= w_hi ? w0 + j : w_hi) * 2) * slot_floats;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) t[j][v] = src[v * 64];
+        }
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j)
+            if (w0 + j <= w_hi) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) tot[v] += t[j][v];
+            }
+    }
 }
 
 }  // namespace mq

@@ -386,7 +386,7 @@ __device__ __forceinline__ void run_narrow_units(const LayerDesc &L, const Stack
                 const int row0 = rb * kRowBlock + lm.rowbase;
                 const int col = lm.col;
                 const bool fast_store = (L.N & 3) == 0 && (reinterpret_cast<uintptr_t>(L.y) & 7) == 0;
-                finish_row_block<16>(L, pw, p.cnt + L.cnt_off + rb, a, ga, g, yacc, worker, lane,
+                finish_row_block<16, true>(L, pw, p.cnt + L.cnt_off + rb, a, ga, g, yacc, worker, lane,
                                      [&](const float(&tot)[16]) {
                                          if (col >= L.M) return;
                                          uint16_t MQ_GLOBAL *yrow = gl(reinterpret_cast<uint16_t *>(L.y) + (size_t)col * L.N);
@@ -437,6 +437,26 @@ __global__ __launch_bounds__(64 * kNarrowWaves, 1) void gemm_stack_kernel(const 
     });
 }
 
+// The row blocks of a single layer that several shares worked on: their slots added up in share order, and y.  One workgroup per
+// row block, a wave for four values of a lane.
+__global__ __launch_bounds__(256) void narrow_finish_kernel(const StackParams p) {
+    const LayerDesc &L = p.single;
+    const int lane = threadIdx.x & 63, quarter = (int)(threadIdx.x >> 6);
+    const int rb = (int)blockIdx.x, srb = rb / kNarrowRowBlocks, wv = rb % kNarrowRowBlocks;
+    const uint64_t a = (uint64_t)srb * L.G * L.cost;
+    const int w_lo = wave_of(a, p.nworkers, p.cost_total);
+    const int w_hi = wave_of(a + (uint64_t)(L.G - 1) * L.cost, p.nworkers, p.cost_total);
+    if (w_lo == w_hi) return;  // one share did it all and has stored y
+    float tot[4];
+    sum_slots(p.part + (size_t)wv * (16 * 64) + quarter * 4 * 64 + lane, w_lo, w_hi, (size_t)p.slot_floats, tot);
+    const LaneMap lm = lane_map(lane);
+    if (lm.col >= L.M) return;
+    const int row = rb * kRowBlock + lm.rowbase + 8 * quarter;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (row + e < L.N) store_y(L.y, (size_t)lm.col * L.N + row + e, tot[e], L.flags);
+}
+
 // workgroups the device keeps resident for a launch with lds_bytes of LDS per workgroup
 static int narrow_resident_groups(int lds_bytes) {
     static int cached_bytes[2] = {0, 0}, cached[2] = {0, 0};
@@ -485,7 +505,14 @@ hipError_t launch_stack_mfma(StackParams p, int max_cost, hipStream_t s) {
     p.slot_floats = kNarrowWaves * 16 * 64;
     const hipError_t e = launch(xprep_kernel, dim3((unsigned)((p.n_jobs + 3) / 4)), dim3(256), 0, s, p);
     if (e != hipSuccess) return e;
-    return launch(gemm_stack_kernel, dim3((unsigned)p.nworkers), dim3(64 * kNarrowWaves), (unsigned)lds_bytes, s, p);
+    const int64_t tiles = p.table ? 0 : (int64_t)p.single.RB * p.single.G;
+    // Where eight and more shares meet in a row block of a single layer, a launch of its own adds their slots up: the last of them did,
+    // with most of the chip idle.  us, M = 16, r = 4, before / now: 8192 x 28672 (16 shares a row block) 43.1 / 39.2, 8192 x 14336 (16) 33.9 / 30.4,
+    // 13003 x 8192 (10) 34.6 / 29.6, 4096 x 28672 (32) 42.8 / 31.9; below, nothing: 28672 x 8192 (4.6) 40.8 / 40.6, 20000 x 6016 (6.4) 30.7 / 31.0.
+    p.finish_apart = !p.table && p.single.G * p.nworkers >= 8 * tiles;
+    const hipError_t e2 = launch(gemm_stack_kernel, dim3((unsigned)p.nworkers), dim3(64 * kNarrowWaves), (unsigned)lds_bytes, s, p);
+    if (e2 != hipSuccess || !p.finish_apart) return e2;
+    return launch(narrow_finish_kernel, dim3((unsigned)((p.single.N + kRowBlock - 1) / kRowBlock)), dim3(256), 0, s, p);
 }
 
 }  // namespace mq

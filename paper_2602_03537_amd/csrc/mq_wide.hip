@@ -673,26 +673,8 @@ template <int C> __global__ __launch_bounds__(256) void wide_finish_kernel(const
     const int w_lo = wave_of(a, p.nworkers, p.cost_total);
     const int w_hi = wave_of(a + (uint64_t)(L.G - 1) * L.cost, p.nworkers, p.cost_total);
     if (w_lo == w_hi) return;  // one share did it all and has stored y
-    const float MQ_GLOBAL *part = gl(p.part) + (size_t)wv * (C * 32 * 64) + (b * 16 + quarter * 4) * 64 + lane;
     float tot[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) tot[v] = part[(size_t)(w_lo * 2 + 1) * p.slot_floats + v * 64];
-    constexpr int kBatch = 8;
-    for (int w0 = w_lo + 1; w0 <= w_hi; w0 += kBatch) {
-        float t[kBatch][4];
-#pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-            const float MQ_GLOBAL *src = part + (size_t)((w0 + j <= w_hi ? w0 + j : w_hi) * 2) * p.slot_floats;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) t[j][v] = src[v * 64];
-        }
-#pragma unroll
-        for (int j = 0; j < kBatch; ++j)
-            if (w0 + j <= w_hi) {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) tot[v] += t[j][v];
-            }
-    }
+    sum_slots(p.part + (size_t)wv * (C * 32 * 64) + (b * 16 + quarter * 4) * 64 + lane, w_lo, w_hi, (size_t)p.slot_floats, tot);
     const int row = rb * kRowBlock + 32 * (b % 2) + (lane & 31);
     const int col = (pass * C + b / 2) * kWideCols + 8 * quarter + 4 * (lane >> 5);
     if (row >= L.N) return;
