@@ -308,7 +308,7 @@ mq_status mq_linear_plain(const mq_half *x, int64_t M, const void *packed_W, con
  * two agree to rounding, not bit for bit.
  *   packed_parent : device, 16-byte aligned, mq_pack(parent, 8, 8)
  *   ws            : as for mq_linear, ws_bytes >= mq_workspace_bytes(M,N,K,8)
- * 1 <= M <= 4 (the vector-ALU path); larger M returns MQ_ERR_UNSUPPORTED: re-slice
+ * 1 <= M <= 4; larger M returns MQ_ERR_UNSUPPORTED: re-slice
  * with mq_reslice and call mq_linear.  Other arguments and errors as mq_linear. */
 mq_status mq_linear_from_parent(const mq_half *x, int64_t M, const void *packed_parent,
                                 const mq_half *scales_t, const mq_half *zeros_t, int64_t N,
@@ -337,8 +337,10 @@ typedef struct {
 
 /* bf16 activations and outputs, per layer.
  *   MQ_X_BF16 : x points to bfloat16 values.  They are converted to fp16 before they are multiplied
- *               (M <= 4: by a small launch of its own ahead of the layer's, into the workspace, or in
- *               registers where a single packed layer is launched for latency; M > 4: inside the activation preparation), which is exact for every value whose magnitude is within the fp16 range
+ *               (by a small launch of its own ahead of the layer's, into the workspace; in registers
+ *               where a single packed layer is launched for latency; or inside the activation
+ *               preparation, where the kernel has one), which is exact for every value whose magnitude
+ *               is within the fp16 range
  *               (2^-14 <= |x| <= 65504, and 0): results are then those of the same values given as
  *               fp16, bit for bit.  Larger magnitudes become infinities, smaller ones keep what
  *               fp16 subnormals hold (absolute error <= 2^-25).
@@ -364,10 +366,9 @@ typedef struct {
  * this launch: the flag is for layers that really feed each other. */
 #define MQ_X_AFTER_EARLIER 4
 
-/* Kernels by batch: as mq_linear, except that a stack of packed layers already runs on the matrix
- * cores at M = 4 (scales_t / zeros_t 16-byte aligned from M = 4 on for a stack); stacks computed
- * from the parent stay on the vector ALUs (M <= 4).  A small stack (at most 16 layers and 12288
- * tiles of 64 rows x 128 columns in all, M <= 4: the q/k/v or gate/up linears of a decoder block,
+/* scales_t / zeros_t are 16-byte aligned from M = 4 on for a stack of packed layers that is not
+ * small; stacks computed from the parent take M <= 4.  A small stack (at most 16 layers and 12288
+ * tiles of 64 rows x 128 columns in all, M <= 16: the q/k/v or gate/up linears of a decoder block,
  * which may share one x) is launched for latency, one workgroup per (layer, row block, K slice);
  * larger ones as one persistent stream-K launch.
  *
