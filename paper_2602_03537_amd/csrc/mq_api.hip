@@ -26,7 +26,7 @@ mq_status check_shape(int64_t N, int64_t K, int group) {
 }
 
 size_t counter_bytes(int64_t row_blocks) { return align_up((size_t)row_blocks * 4, kCounterBytesAlign); }
-bool use_mfma(int64_t M) { return M > kValuMaxM; }
+bool more_rows(int64_t M) { return M > kValuMaxM; }
 // The batch that a plan's workspace is laid out for: M, but for a stack of packed layers at M = kValuMaxM that is not small, which has the
 // layout of the next larger batch.  The row kernels that serve it need neither that nor the 16-byte alignment of scales that goes with it:
 // both are kept because callers see them, as sizes and as what is refused.
@@ -41,27 +41,27 @@ bool small_stack(const mq_layer *layers, int n_layers, int64_t M) {
 }
 // column blocks the schedule sees: 1 up to 16 rows, the wide kernel's passes above
 int64_t chunks(int64_t M) {
-    return use_wide(M) ? wide_passes(M) : use_mfma(M) ? (M + kChunkCols - 1) / kChunkCols : 1;
+    return use_wide(M) ? wide_passes(M) : 1;
 }
 int64_t counters_of(int64_t M, int64_t N) { return chunks(M) * (pad_rows(N) / kRowBlock); }
 int slot_floats(int64_t M) {
     return use_wide(M)   ? 4 * wide_chunks_per_pass(M) * 32 * 64
-           : use_mfma(M) ? kNarrowRowBlocks * 64 * kChunkCols
-                         : 64 * (int)M;
+           : more_rows(M) ? kMidSlotFloats
+                          : 64 * (int)M;
 }
 // Shares of the schedule that part_bytes of partial sums hold slots for, row kernels
 int slots_in(size_t part_bytes, int64_t M) { return (int)(part_bytes / (2 * 64 * (size_t)vector_rows(M) * sizeof(float))); }
 size_t max_workers(int64_t M) {
     return use_wide(M)   ? (size_t)wide_max_groups(wide_chunks_per_pass(M))
-           : use_mfma(M) ? (size_t)kMaxGroupsNarrow
-                         : (size_t)max_workers_valu(M);
+           : more_rows(M) ? (size_t)kMidSlots
+                          : (size_t)max_workers_valu(M);
 }
 size_t partial_bytes(int64_t M) { return max_workers(M) * 2 * (size_t)slot_floats(M) * sizeof(float); }
-// narrow and wide: prepared activations of one layer (group sums and rescale factors live inside the blocks)
+// wide: prepared activations of one layer; row kernels: room for bf16 activations converted to fp16
 size_t xt_bytes(int64_t M, int64_t K, int) {
     if (use_wide(M)) return align_up((size_t)wide_chunks_padded(M) * (size_t)(K / kGroup) * kWideXtBlockBytes, 256);
-    if (use_mfma(M)) return (size_t)(K / kGroup) * kNarrowXtBlockBytes;
-    return align_up((size_t)M * (size_t)K * 2, 256);  // row kernels: bf16 activations converted to fp16
+    if (more_rows(M)) return (size_t)(K / kGroup) * kMidXBytes;
+    return align_up((size_t)M * (size_t)K * 2, 256);
 }
 
 mq_status layer_status(const mq_layer &l, int64_t M) {
@@ -74,9 +74,9 @@ mq_status layer_status(const mq_layer &l, int64_t M) {
     // a chained layer reads x as the earlier layers leave it: there is no point before the launch at which bf16
     // activations could be converted for it
     if ((l.flags & MQ_X_AFTER_EARLIER) && (l.flags & MQ_X_BF16)) return MQ_ERR_UNSUPPORTED;
-    if (l.from_parent && use_mfma(M)) return MQ_ERR_UNSUPPORTED;  // slicing in registers: row kernels only
-    // the narrow and the wide kernel move scales / zeros 16 bytes at a time (which of the three serves a batch depends on its shape)
-    const size_t meta_align = use_mfma(M) ? 16 : 2;
+    if (l.from_parent && more_rows(M)) return MQ_ERR_UNSUPPORTED;  // slicing in registers: up to kValuMaxM rows
+    // the wide kernel moves scales / zeros 16 bytes at a time (and what is refused depends on the batch alone)
+    const size_t meta_align = more_rows(M) ? 16 : 2;
     if (!aligned(l.packed_W, 16) || !aligned(l.x, 4) || !aligned(l.scales_t, meta_align) ||
         !aligned(l.zeros_t, meta_align) || !aligned(l.y, 2))
         return MQ_ERR_ALIGN;
@@ -113,7 +113,7 @@ const _Float16 *sym_zero_line() {
     return g_sym_zero_line[dev];
 }
 
-// xt: where the narrow and the wide kernel keep this layer's prepared activations (row kernels: the fp16 copy of bf16 activations)
+// xt: where the wide kernel keeps this layer's prepared activations (row kernels: the fp16 copy of bf16 activations)
 // sym_line: sym_zero_line() of the current device; needed (non-null) when the layer is symmetric
 // Mp: the batch that the workspace is laid out for (see stack_path_m); rows: the row kernels serve it
 LayerDesc make_desc(const mq_layer &l, int64_t M, int64_t Mp, bool rows, uint64_t cost_start, int cnt_off, int job_start, void *xt,
@@ -146,11 +146,7 @@ LayerDesc make_desc(const mq_layer &l, int64_t M, int64_t Mp, bool rows, uint64_
         d.rs = l.r;
         d.cost = valu_tile_cost(kC, (int)M);
     }
-    if (!rows && !use_wide(Mp)) {  // scheduled in super-tiles of kNarrowRowBlocks row blocks
-        d.RB = (d.RB + kNarrowRowBlocks - 1) / kNarrowRowBlocks;
-        d.cost = mfma_tile_cost(l.r);
-    }
-    if (!rows && use_wide(Mp)) {  // scheduled in super-tiles of four row blocks
+    if (!rows) {  // scheduled in super-tiles of four row blocks
         d.RB = (d.RB + 3) / 4;
         d.cost = wide_tile_cost(l.r, wide_chunks_per_pass(Mp));
     }
@@ -194,7 +190,7 @@ constexpr uint64_t kPlanMagic = 0x4d51504c414e3039ull;  // "MQPLAN09"
 // holds its own copy at its own address) and only that pointer is ever handed to a kernel.
 constexpr size_t kScratchBytes = MQ_NOALLOC_SCRATCH_BYTES;
 constexpr size_t kNoallocMinWorkers = 256;  // fewer schedule shares (waves) than this would leave most of the chip idle
-constexpr size_t kNoallocMinGroups = 32;    // the same for the narrow kernel, whose shares are workgroups of 8 waves
+constexpr size_t kNoallocMinMid = 32;       // the same from 5 rows on, where the workspace counts in kMidSlotFloats
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 std::mutex g_scratch_mutex;
 void *g_scratch_ptr[kMaxDevices] = {};
@@ -242,7 +238,7 @@ PlanLayout plan_layout(const mq_layer *layers, int n_layers, int64_t M) {
     PlanLayout p;
     p.table_off = 256;
     p.cnt_off = align_up(p.table_off + (size_t)n_layers * sizeof(LayerDesc), 256);
-    p.cnt_bytes = counter_bytes(counters + (use_mfma(M) ? 0 : kChainCounters));  // a small stack may be chained
+    p.cnt_bytes = counter_bytes(counters + (more_rows(M) ? 0 : kChainCounters));  // a small stack may be chained
     p.part_off = p.cnt_off + p.cnt_bytes;
     p.act_off = p.part_off + partial_bytes(M);
     p.total = p.act_off + act;
@@ -252,7 +248,7 @@ PlanLayout plan_layout(const mq_layer *layers, int n_layers, int64_t M) {
 // One layer on its own workspace: [counters][partial sums][prepared activations]
 // worker_cap: 0 = the workspace has mq_workspace_bytes; else it holds partial-sum slots for that many schedule
 // shares only ([counters][worker_cap slots pairs][prepared activations], checked by the caller) and the launch keeps
-// to them.  M <= kNarrowMaxM when capped.
+// to them.  M <= kRowMaxM when capped.
 mq_status run_single(const mq_layer &l, int64_t M, void *ws, size_t ws_bytes, mq_stream stream, int worker_cap = 0) {
     if (!ws) return MQ_ERR_NULL;
     if (mq_status st = layer_status(l, M)) return st;
@@ -266,9 +262,9 @@ mq_status run_single(const mq_layer &l, int64_t M, void *ws, size_t ws_bytes, mq
     const size_t part_b = worker_cap ? (size_t)worker_cap * 2 * (size_t)slot_floats(M) * sizeof(float) : partial_bytes(M);
     char *act = base + cnt_b + part_b;
     const int64_t row_blocks = pad_rows(l.N) / kRowBlock;
-    const bool rows = row_kernels_single(row_blocks, l.K / kGroup, l.r, M, part_b);
+    const bool rows = M <= kRowMaxM || row_kernels_single(row_blocks, l.K / kGroup, l.r, M, part_b);
     StackParams p{};
-    p.worker_cap = use_mfma(M) && rows ? slots_in(part_b, M) : worker_cap;
+    p.worker_cap = more_rows(M) && rows ? slots_in(part_b, M) : worker_cap;
     p.table = nullptr;
     p.n_layers = 1;
     const _Float16 *sym_line = nullptr;
@@ -282,15 +278,13 @@ mq_status run_single(const mq_layer &l, int64_t M, void *ws, size_t ws_bytes, mq
     p.n_jobs = (use_wide(M) ? wide_chunks_padded(M) : p.single.CB) * p.single.G;
     hipError_t e;
     // bf16 activations (packed layers only: a single from-parent call takes fp16): the low-latency launch converts them itself
-    const bool rb = rows && low_latency_single(row_blocks, l.K / kGroup, M, part_b);
+    const bool rb = rows && low_latency_call(row_blocks, l.K / kGroup, M, part_b);
     if (rows && (l.flags & MQ_X_BF16) && !rb) {
         if (launch_xcvt(p, (hipStream_t)stream) != hipSuccess) return MQ_ERR_HIP;
         p.single.x_bf16 = nullptr;  // from here on x is the fp16 copy
     }
-    if (use_wide(M) && !rows)
+    if (!rows)
         e = launch_stack_wide(p, p.single.cost, (hipStream_t)stream);
-    else if (!rows)
-        e = launch_stack_mfma(p, p.single.cost, (hipStream_t)stream);
     else if (rb)
         e = launch_linear_rb(p.single, p.part, p.cnt, (hipStream_t)stream);
     else
@@ -551,9 +545,7 @@ mq_status mq_stack_plan(const mq_layer *layers, int n_layers, int64_t M, void *p
     if (plan_bytes < need) return MQ_ERR_BUF_TOO_SMALL;
 
     const PlanLayout pl = plan_layout(layers, n_layers, Mp);
-    const bool rows = row_kernels_stack(n_layers, M, partial_bytes(Mp), [&](int i) {
-        return RowLayer{(int)(pad_rows(layers[i].N) / kRowBlock), (int)(layers[i].K / kGroup), layers[i].r};
-    });
+    const bool rows = M <= kRowMaxM;
     char *base_dev = static_cast<char *>(plan_ws);
     int64_t counters = 0, jobs = 0;
     uint64_t cost = 0;
@@ -645,7 +637,7 @@ mq_status mq_linear_stack(const mq_plan *plan, mq_stream stream) {
     p.part = reinterpret_cast<float *>(base + h.part_off);
     p.M = h.M;
     p.slot_floats = h.rows ? 64 * vector_rows(h.M) : slot_floats(h.path_M);
-    if (use_mfma(h.path_M) && h.rows) p.worker_cap = slots_in(partial_bytes(h.path_M), h.M);
+    if (more_rows(h.path_M) && h.rows) p.worker_cap = slots_in(partial_bytes(h.path_M), h.M);
     p.n_jobs = h.n_jobs;
     p.ks_cap = h.ll_ks_cap;
     std::memcpy(p.ll_start, h.ll_start, sizeof(p.ll_start));
@@ -655,11 +647,9 @@ mq_status mq_linear_stack(const mq_plan *plan, mq_stream stream) {
     if (h.rows && h.any_x_bf16) {
         if (launch_xcvt(p, (hipStream_t)stream) != hipSuccess) return MQ_ERR_HIP;
     }
-    const hipError_t e = use_wide(h.path_M)   ? launch_stack_wide(p, h.max_cost, (hipStream_t)stream)
-                         : !h.rows            ? launch_stack_mfma(p, h.max_cost, (hipStream_t)stream)
-                         : h.ll_blocks        ? launch_linear_rb_stack(p, small, h.ll_blocks, h.ll_waves, h.from_parent != 0,
-                                                                       (hipStream_t)stream)
-                                              : launch_stack(p, h.max_cost, h.from_parent != 0, (hipStream_t)stream);
+    const hipError_t e = !h.rows       ? launch_stack_wide(p, h.max_cost, (hipStream_t)stream)
+                         : h.ll_blocks ? launch_linear_rb_stack(p, small, h.ll_blocks, h.ll_waves, h.from_parent != 0, (hipStream_t)stream)
+                                       : launch_stack(p, h.max_cost, h.from_parent != 0, (hipStream_t)stream);
     return e == hipSuccess ? MQ_OK : MQ_ERR_HIP;
 }
 
@@ -667,12 +657,12 @@ mq_status mq_linear_noalloc(const mq_half *x, int64_t M, const void *packed_W, c
                             const mq_half *zeros_t, int64_t N, int64_t K, int r, int group, mq_half *y, mq_stream stream) {
     const mq_layer l{packed_W, scales_t, zeros_t, x, y, N, K, r, group, 0, 0};
     if (mq_status st = layer_status(l, M)) return st;
-    if (M > kNarrowMaxM) return MQ_ERR_UNSUPPORTED;  // the wide path's slots alone exceed the scratch array
+    if (M > kRowMaxM) return MQ_ERR_UNSUPPORTED;  // the wide path's slots alone exceed the scratch array
     // [counters][slot pairs for `cap` schedule shares][prepared activations] must fit the array
     const size_t cnt_b = counter_bytes(counters_of(M, N));
     const size_t act_b = xt_bytes(M, K, r);
     const size_t pair_b = 2 * (size_t)slot_floats(M) * sizeof(float);
-    const size_t min_workers = use_mfma(M) ? kNoallocMinGroups : kNoallocMinWorkers;
+    const size_t min_workers = more_rows(M) ? kNoallocMinMid : kNoallocMinWorkers;
     if (cnt_b + act_b + min_workers * pair_b > kScratchBytes) return MQ_ERR_BUF_TOO_SMALL;
     size_t cap = (kScratchBytes - cnt_b - act_b) / pair_b;
     const size_t most = max_workers(M);

@@ -1,18 +1,16 @@
 // Device-side pieces shared by the row kernels (mq_linear.hip) and the
-// MFMA kernel (mq_gemm.hip): the persistent schedule over all tiles of a stack
-// and the deterministic split-K hand-off.
+// wide kernel (mq_wide.hip): the persistent schedule over all tiles of a stack.
 //
-// Schedule.  ("wavefront w" below is a schedule share, a "worker": a wave may serve several.)
-// A layer is CB x RB x G tiles (column chunk, row block of 64 rows,
-// group of 128 columns; CB = 1 unless the batch is served 16 columns at a time).
-// Tiles of all layers form one line in "cost" space (cost ~ bytes of a tile);
-// wavefront w owns the tiles whose start lies in [w*C/W, (w+1)*C/W): a
+// Schedule.  A layer is CB x RB x G tiles (pass of the wide kernel, row block of 64 rows, or super row block,
+// group of 128 columns; CB = 1 for the row kernels).
+// Tiles of all layers form one line in "cost" space (cost ~ time of a tile); share ("worker") w of W, a workgroup's,
+// owns the tiles whose start lies in [w*C/W, (w+1)*C/W): a
 // contiguous run, group index fastest, i.e. a contiguous piece of packed
-// memory, while the wave keeps fp32 running sums for its current row block.
+// memory, while the workgroup keeps fp32 running sums for its current row block.
 //
-// Split-K.  When a run ends inside a row block the wave leaves its partial sums
+// Split-K.  When a run ends inside a row block its workgroup leaves its partial sums
 // in a slot of its own and adds the number of groups it covered to the row
-// block's counter; whoever brings the counter to G adds the slots up in wave
+// block's counter; whoever brings the counter to G adds the slots up in share
 // order (so the result does not depend on timing), writes y and resets the
 // counter.  Nobody waits for anybody.
 #pragma once
@@ -46,7 +44,7 @@ __device__ __forceinline__ uint32_t bf16_pair_to_f16_pair(uint32_t v) {
     const half2_t h = {(_Float16)lo, (_Float16)hi};
     return __builtin_bit_cast(uint32_t, h);
 }
-// (for the activation prep kernels of the narrow and the wide kernel, where the conversion costs nothing that matters; the
+// (for the activation prep kernel of the wide kernel, where the conversion costs nothing that matters; the
 // row kernels, but for the single-layer low-latency one, read activations that xcvt_kernel has converted: computed both ways and selected per
 // tile, the conversion costs the ALU-bound 2-bit tiles 3 %, branched around 10 %)
 __device__ __forceinline__ uint32_t x_pair(uint32_t v, int flags) { return flags & kFlagXBf16 ? bf16_pair_to_f16_pair(v) : v; }
@@ -96,7 +94,7 @@ __device__ __forceinline__ LayerDesc load_desc(const LayerDesc *p) {
     return d;
 }
 
-// wave that owns the tile starting at cost position pos
+// share that owns the tile starting at cost position pos
 __device__ __forceinline__ int wave_of(uint64_t pos, uint64_t nw, uint64_t ctot) {
     return (int)(((pos + 1) * nw - 1) / ctot);
 }
@@ -130,65 +128,6 @@ template <class F> __device__ __forceinline__ void walk_tiles(const StackParams 
         pos = layer_end;
         ++li;
     }
-}
-
-// End of a wave's run inside row block (chunk c, rb): groups [ga, gb) are in acc[NV] (per lane).
-// Complete row block -> final(acc).  Otherwise publish the partial sums; the last
-// contributor sums all slots in wave order and calls final(total).
-//   cnt     : the row block's counter
-//   a       : cost position of the row block's first tile
-// Partial sums travel through agent-scope atomic stores/loads (write-through, cache
-// bypassing), so no whole-L2 write-back or invalidate is needed to publish them.
-// APART: where p.finish_apart says so, a later launch adds the slots up instead (nothing is counted).
-template <int NV, bool APART = false, class Final>
-__device__ __forceinline__ void finish_row_block(const LayerDesc &L, const StackParams &p, int32_t *cnt, uint64_t a,
-                                                 int ga, int gb, float (&acc)[NV], int worker, int lane, Final &&final) {
-    if (ga == 0 && gb == L.G) {
-        final(acc);
-        return;
-    }
-    const int slot = ga == 0 ? 1 : 0;  // the wave holding a row block's first tile uses slot 1
-    const size_t slot_floats = (size_t)p.slot_floats;
-    float MQ_GLOBAL *mine = gl(p.part + (size_t)(worker * 2 + slot) * slot_floats + lane);
-#pragma unroll
-    for (int v = 0; v < NV; ++v) __hip_atomic_store(mine + v * 64, acc[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (APART && p.finish_apart) return;
-    // the write-through stores must have been acknowledged before the counter moves
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    int old = 0;
-    if (lane == 0) old = __hip_atomic_fetch_add(gl(cnt), gb - ga, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    old = __builtin_amdgcn_readfirstlane(old);
-    if (old + (gb - ga) != L.G) return;
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    const int w_lo = wave_of(a, p.nworkers, p.cost_total);
-    const int w_hi = wave_of(a + (uint64_t)(L.G - 1) * L.cost, p.nworkers, p.cost_total);
-    // Fixed summation order (w_lo's slot 1, then slot 0 of w_lo+1 .. w_hi); loads are issued
-    // in batches so that their round trips overlap.
-    constexpr int kBatch = NV >= 8 ? 8 : 16;  // slots fetched per round trip (NV * kBatch registers)
-    float tot[NV];
-    const float MQ_GLOBAL *first = gl(p.part + (size_t)(w_lo * 2 + 1) * slot_floats + lane);
-#pragma unroll
-    for (int v = 0; v < NV; ++v) tot[v] = __hip_atomic_load(first + v * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    for (int w0 = w_lo + 1; w0 <= w_hi; w0 += kBatch) {
-        float t[kBatch][NV];
-#pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-            const int w = w0 + j <= w_hi ? w0 + j : w_hi;
-            const float MQ_GLOBAL *src = gl(p.part + (size_t)(w * 2) * slot_floats + lane);
-#pragma unroll
-            for (int v = 0; v < NV; ++v)
-                t[j][v] = __hip_atomic_load(src + v * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-#pragma unroll
-        for (int j = 0; j < kBatch; ++j)
-            if (w0 + j <= w_hi) {
-#pragma unroll
-                for (int v = 0; v < NV; ++v) tot[v] += t[j][v];
-            }
-    }
-    final(tot);
-    if (lane == 0) __hip_atomic_store(gl(cnt), 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Four values of a row block's lanes, added up over the slots of shares w_lo .. w_hi in share order (launches that finish row

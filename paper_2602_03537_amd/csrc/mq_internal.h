@@ -18,11 +18,9 @@ namespace mq {
 // and the kernel's occupancy and launches min(what is resident there, the cap), so a smaller or larger part stays
 // correct and only loses the slots it cannot use.  (8192 = 256 compute units x 32 waves, the MI355X.)
 constexpr int kMaxWaves = 8192;
-// Narrow kernel: a workgroup of kNarrowRowBlocks waves owns a super-tile of
-// kNarrowRowBlocks row blocks x one group; one workgroup per compute unit.
-constexpr int kNarrowRowBlocks = 8;
-constexpr int kMaxGroupsNarrow = 256;
-constexpr int kNarrowXtBlockBytes = 6 * 1024;  // prepared activations of one group: operand blocks + 16 factors
+// 5 .. 16 rows: what a workspace holds (callers see its size, which has room to spare): pairs of partial-sum slots, floats in one, and bytes
+// for the activations of a group
+constexpr int kMidSlots = 256, kMidSlotFloats = 8 * 64 * 16, kMidXBytes = 6 * 1024;
 // Persistent row kernel: each wave serves several interleaved shares of the schedule, so that
 // layers of different widths (different speed per byte) even out over the waves.
 constexpr int kSharesPerWave = 8;
@@ -43,9 +41,9 @@ struct LayerDesc {
     const _Float16 *zt;
     const _Float16 *x;
     _Float16 *y;
-    const uint4 *xt;        // narrow and wide kernel: activations re-ordered (narrow: and scaled) by the prep kernel
+    const uint4 *xt;        // wide kernel: activations re-ordered by the prep kernel
     const void *x_bf16;     // row kernels with kFlagXBf16: the caller's bf16 activations (x then points to their fp16 copy)
-    int32_t N, K, G, RB;    // RB = row blocks = ceil(N/64); super row blocks: ceil(N/512) narrow, ceil(N/256) wide
+    int32_t N, K, G, RB;    // RB = row blocks = ceil(N/64); super row blocks of the wide kernel: ceil(N/256)
     int32_t r;
     int32_t cost;           // schedule cost of one (row block, group) tile
     int32_t cnt_off;        // index of this layer's first row-block counter (CB*RB counters)
@@ -73,15 +71,15 @@ static_assert(sizeof(SmallTable) <= 2048, "kernel arguments are limited to 4 KiB
 struct StackParams {
     const LayerDesc *table;  // device table, or nullptr to use `single`
     int32_t n_layers;
-    int32_t nwaves;          // wavefronts launched
-    int32_t nworkers;        // schedule shares ("workers"); wave w serves workers w, w + nwaves, ...
+    int32_t nwaves;          // row kernels: workgroups launched
+    int32_t nworkers;        // schedule shares ("workers"); workgroup w serves workers w, w + nwaves, ...
     uint64_t cost_total;
     float *part;             // [nworkers][2][slot_floats] partial sums
     int32_t *cnt;            // row-block counters, zero between launches
     int32_t M;
-    int32_t slot_floats;     // floats per partial-sum slot (row kernels 64 * vector_rows(M); a workgroup's: narrow 8 x 64*16, wide 4 x chunks x 32*64)
-    int32_t n_jobs;          // jobs of the prep kernel (narrow, wide)
-    int32_t finish_apart;    // narrow and wide, single layers: row blocks that several shares worked on are finished by a launch of its own
+    int32_t slot_floats;     // wide: floats per partial-sum slot (4 x chunks x 32*64)
+    int32_t n_jobs;          // wide: jobs of the prep kernel
+    int32_t finish_apart;    // wide, single layers: row blocks that several shares worked on are finished by a launch of its own
     int32_t worker_cap;      // 0, or: `part` holds slots for this many schedule shares only (a small workspace)
     int32_t ks_cap;          // low-latency launch of a small stack: most K slices per row block (0: as one layer would choose)
     int32_t ll_start[16];    // ... and the first workgroup of each layer (a workgroup finds its layer without reading the table)
@@ -93,20 +91,6 @@ struct StackParams {
     int32_t stage_rb[16];    // row blocks per stage
     LayerDesc single;
 };
-
-// Narrow kernel: a tile's time there is set by instruction issue more than by its
-// bytes, so the measured per-tile times of uniform stacks are the costs (M = 8, 12 Llama-3-70B blocks: 1.11, 1.24,
-// 1.24, 1.61, 1.87 ms for r = 2, 3, 4, 6, 8).  With the byte-proportional costs a 2-bit share ran 1.6 times as long as
-// an 8-bit share of a mixed stack.
-inline int mfma_tile_cost(int r) {
-    switch (r) {
-        case 2: return 111;
-        case 3: return 124;
-        case 4: return 124;
-        case 6: return 161;
-        default: return 187;
-    }
-}
 
 // Wide kernel: cost of a super-tile (256 rows x one group) per pass with C chunks of 32 columns, again the measured
 // times of uniform stacks (12 Llama-3-70B blocks at M = 32, 64, 96, 128; units of 10 us; the first two rows with two
@@ -162,7 +146,7 @@ hipError_t launch_quant(const float *W, int64_t ldw, int64_t N, int64_t ncols, i
                         hipStream_t s);
 // bf16 activations of the layers that carry kFlagXBf16 -> fp16 in their LayerDesc::xt (ahead of a launch of row kernels)
 hipError_t launch_xcvt(const StackParams &p, hipStream_t s);
-// Fills p.nwaves and launches (row kernels, M <= 8).  max_cost = largest tile cost in the stack.
+// Fills p.nwaves and launches (row kernels, M <= 16).  max_cost = largest tile cost in the stack.
 // from_parent: every layer has rs != 0 (the kernel variant that slices in registers).
 hipError_t launch_stack(StackParams p, int max_cost, bool from_parent, hipStream_t s);
 // Single layer (low_latency_single): one workgroup per (row block, K slice, chunk of 16 rows); see mq_linear.hip.
@@ -176,9 +160,7 @@ bool linear_rb_stack_shape(const LayerDesc *table, int n_layers, size_t part_byt
                            int *blocks, int *waves, int *ks_cap, int32_t *ll_start, bool *all_resident);
 hipError_t launch_linear_rb_stack(const StackParams &p, const SmallTable &t, int blocks, int waves, bool from_parent,
                                   hipStream_t s);
-// Narrow: activation prep kernel + persistent kernel (single layers: + a finishing launch where p.finish_apart).
-hipError_t launch_stack_mfma(StackParams p, int max_cost, hipStream_t s);
-// Wide: the same, one workgroup per share.
+// Wide: activation prep kernel + persistent kernel, one workgroup per share (single layers: + a finishing launch where p.finish_apart).
 hipError_t launch_stack_wide(StackParams p, int max_cost, hipStream_t s);
 
 }  // namespace mq

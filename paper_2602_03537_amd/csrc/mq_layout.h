@@ -227,6 +227,31 @@ template <int R> constexpr bool steps_ok() {
     }
     return true;
 }
+// The same weights in v_mfma_f32_16x16x32_f16 (the row kernels from 5 rows on): multiplication q of four takes activation pairs
+// 4 chunk(q, h) .. + 3 in quarter h of the wave.  The dwords that hold their codes in the four quarters are S apart, so that a transpose of
+// dwords b, b + S, b + 2 S, b + 3 S serves them all.
+template <int R> struct ColSteps {
+    using T = Layout<R>;
+    static constexpr int S = T::UD == 3 ? 3 : T::PPU == 2 ? 2 : 1;
+    static constexpr int chunk(int q, int h) { return T::PPU == 16 ? q + 4 * h : T::PPU == 8 ? 8 * (q / 2) + q % 2 + 2 * h : 4 * q + h; }
+};
+template <int R> constexpr bool col_steps_ok() {
+    using T = Layout<R>;
+    using C = ColSteps<R>;
+    int seen[64] = {};
+    for (int q = 0; q < 4; ++q)
+        for (int h = 0; h < 4; ++h)
+            for (int i = 0; i < 4; ++i) {
+                const int p0 = 4 * C::chunk(q, 0) + i, p = 4 * C::chunk(q, h) + i;
+                if (C::chunk(q, h) != C::chunk(q, 0) + C::chunk(0, h) || p >= 64 || seen[p]++) return false;
+                if (p % T::PPU != p0 % T::PPU) return false;                                          // the same field in every quarter
+                if (p / T::PPU * T::UD != p0 / T::PPU * T::UD + h * C::S) return false;               // of dwords S apart
+                for (int o = 0; o < T::NOPS; ++o)
+                    if (T::op(o).pair == p0 % T::PPU && ((p0 / T::PPU * T::UD + T::op(o).dw) / C::S) % 4 != 0) return false;
+            }
+    return true;
+}
+static_assert(col_steps_ok<2>() && col_steps_ok<3>() && col_steps_ok<4>() && col_steps_ok<6>() && col_steps_ok<8>(), "inconsistent columns of the 16-row steps");
 static_assert(steps_ok<2>() && steps_ok<3>() && steps_ok<4>() && steps_ok<6>() && steps_ok<8>(), "inconsistent list of matrix-core steps");
 static_assert(layout_ok<2>() && layout_ok<3>() && layout_ok<4>() && layout_ok<6>() && layout_ok<8>(),
               "inconsistent packed layout table");

@@ -1,44 +1,71 @@
 // Sliced, group-dequantised linear layer  y = x * W_D^T  (Section 4 of the paper)
-// for small batches: one row of x on the vector ALUs, 2 .. 16 by 4x4x4 matrix
-// instructions (larger batches in chunks of 16), and the mixed-precision stack of such layers (Section 3.3), as ONE persistent kernel.  Schedule and
-// split-K hand-off: mq_device.h.
+// for small batches: one row of x on the vector ALUs, 2 .. 4 by 4x4x4 and 5 .. 16 by 16x16x32 matrix
+// instructions (larger batches in chunks of 16), and the mixed-precision stack of such layers (Section 3.3), as ONE persistent kernel.  Schedule: mq_device.h.
 //
 // Arithmetic per tile and lane (one row, one group g):
 //   D   = sum_k x[k] * t[k]            t = r-bit code, via fp16-subnormal fields
 //   y  += scale * (2^(8-r) * D - zero * X_g),   X_g = sum_{k in g} x[k]
 // which is  sum_k x[k] * scale * (S[k] - zero)  with S = t * 2^(8-r)  (Eq. 1's
 // rescale), the zero-offset and scale applied once per group instead of per weight.
-#include "mq_device.h"
+#include "mq_dma.h"
 
 namespace mq {
 
 // How a wave gets the 64 activation pairs of a group (they are the same for every lane): each lane fetches ONE pair together with
 // the tile (one tile ahead, like the weights), drops it into the wave's 256 bytes of LDS per batch row and all lanes read the
 // pairs back with ds_read_b128.
-// From a batch of 2 on a tile is multiplied by the matrix core (tile_math_mfma), whose result has four rows per lane
-template <int M> constexpr bool kQuadRows = M >= 2;
-template <int M> constexpr int kQuads = (M + 3) / 4;                      // of batch rows
-template <int M> constexpr int kAcc = kQuadRows<M> ? 4 * kQuads<M> : 1;  // fp32 running sums per lane
+// A batch of 2 .. 4 is multiplied by the matrix core (tile_math_mfma), whose result has four rows per lane, ...
+template <int M> constexpr bool kQuadRows = M >= 2 && M <= 4;
+template <int M> constexpr bool kColRows = M > 4;                        // ... and from 5 rows on by tile_math_cols, 16 batch rows at a time
+template <int M> constexpr int kAcc = kColRows<M> ? 16 : kQuadRows<M> ? 4 : 1;  // fp32 running sums per lane
+// The persistent launch: waves of a workgroup, one workgroup per compute unit
+constexpr int kWgWaves = 8;
 template <int M> constexpr int kRbWaves = M > 8 ? 4 : M > 4 ? 8 : 16;                 // most waves of a low-latency workgroup (registers)
 // Waves of it that a SIMD has to have room for.  One row of x and up to four bits need 59 - 67 registers as they come, and two workgroups of 16
 // waves a compute unit end at 64 (13003 x 5120, r = 3: 67 registers 11.4 us, 64 9.3)
 // More than 8 rows: two workgroups of four waves, which their launch shape counts on (kQuadResident)
 template <int R, int M> constexpr int kRbPerSimd = M == 1 && R <= 4 ? 8 : M > 8 ? 2 : kRbWaves<M> / 4;
 // Dwords from batch row to batch row in LDS: the four rows that a quad of lanes reads at one time lie in different banks (64 dwords
-// apart they shared them: 28672 x 8192, r = 4, M = 8: 37.0 us, now 30.8)
+// apart they shared them: 28672 x 8192, r = 4, eight rows by 4x4x4 instructions 37.0 us, 30.8 so)
 template <int M> constexpr int kRowDwords = M > 1 ? 68 : 64;
 // M of a kernel is 1 .. 4, 8 or 16 (vector_rows): in the last two the rows of x that do not exist are read as the last one and not stored
 template <int M> __device__ __forceinline__ int row_count(const LayerDesc &L) { return M > 4 ? L.M : M; }
 typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));  // four fp16 at any address of one
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));  // eight at any address of a pair
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+
+// Four registers as a 4 x 4 matrix of quarters of the wave, transposed: afterwards register t holds, in quarter h, what register h held in quarter t
+__device__ __forceinline__ void quarter_transpose(uint32_t &a, uint32_t &b, uint32_t &c, uint32_t &d) {
+    auto swap32 = [](uint32_t &p, uint32_t &q) {
+        const auto v = __builtin_amdgcn_permlane32_swap(p, q, false, false);
+        p = v[0];
+        q = v[1];
+    };
+    auto swap16 = [](uint32_t &p, uint32_t &q) {
+        const auto v = __builtin_amdgcn_permlane16_swap(p, q, false, false);
+        p = v[0];
+        q = v[1];
+    };
+    swap32(a, c);
+    swap32(b, d);
+    swap16(a, b);
+    swap16(c, d);
+}
 
 template <int R, int M> struct TileRegs {
     uint32_t w[4 * R];
     std::conditional_t<kQuadRows<M>, half4_t, _Float16> s, z;  // of the lane's rows
-    uint32_t xl[M];  // lane l's pair (x[2l], x[2l+1]) of the group
+    uint32_t xl[M];  // lane l's pair (x[2l], x[2l+1]) of the group per batch row; from 5 rows on see load_tile_x
 };
 
+// v in a vector register (an address made from it gives a load whose result stays in one: for a scalar register it would be waited for at once)
+__device__ __forceinline__ int own_register(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
 // weights, scale and zero-offset of tile u
 template <int R, int M>
 __device__ __forceinline__ void load_tile_w(TileRegs<R, M> &t, const LayerDesc &L, int u, int lane) {
@@ -70,11 +97,25 @@ __device__ __forceinline__ void load_tile_w(TileRegs<R, M> &t, const LayerDesc &
 // (a chained stack): the loads go to where the whole device sees memory, past whatever this compute die's caches hold.
 template <int R, int M>
 __device__ __forceinline__ void load_tile_x(TileRegs<R, M> &t, const LayerDesc &L, int g, int lane, bool fresh = false) {
+    if constexpr (kColRows<M>) {
+        // A load takes 128 bytes of 8 rows (16 rows' 64 bytes, as the matrix core wants them, cost 2.5 us of 28672 x 8192, r = 4, M = 16), its
+        // 16-byte pieces in an order that depends on the row, so that reading them back by columns meets no bank twice.  Rows that do not
+        // exist repeat the last one, and their sums are not stored.
+        static_for<M / 8>([&](auto b) {
+            const int row = 8 * b + (lane >> 3) < L.M ? 8 * b + (lane >> 3) : L.M - 1;
+            const u32x4_any MQ_GLOBAL *src = gl(reinterpret_cast<const u32x4_any *>(L.x + (size_t)row * L.K + (size_t)g * kGroup)) + ((lane & 7) ^ (lane >> 3));
+            static_for<2>([&](auto c) {
+                const u32x4 v = src[8 * c];
+                constexpr int i = 8 * b + 4 * c;
+                t.xl[i] = v.x; t.xl[i + 1] = v.y; t.xl[i + 2] = v.z; t.xl[i + 3] = v.w;
+            });
+        });
+    } else {
 #pragma unroll
-    for (int m = 0; m < M; ++m) {
-        const int row = M > 4 && m >= L.M ? L.M - 1 : m;
-        const uint32_t MQ_GLOBAL *src = gl(reinterpret_cast<const uint32_t *>(L.x + (size_t)row * L.K + (size_t)g * kGroup)) + lane;
-        t.xl[m] = fresh ? __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *src;
+        for (int m = 0; m < M; ++m) {
+            const uint32_t MQ_GLOBAL *src = gl(reinterpret_cast<const uint32_t *>(L.x + (size_t)m * L.K + (size_t)g * kGroup)) + lane;
+            t.xl[m] = fresh ? __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *src;
+        }
     }
 }
 template <int R, int M>
@@ -86,7 +127,6 @@ __device__ __forceinline__ void load_tile(TileRegs<R, M> &t, const LayerDesc &L,
 // Eq. 1 on the two 8-bit codes of a masked pair (one per 16-bit half), in 8-bit units:
 //   S = min((q + 2^(sh-1)) & ~(2^sh - 1), 256 - 2^sh),  sh = 8 - rs
 // (rounding half up; q + 2^(sh-1) < 256 + 2^sh, so the only value above the top code is 256 itself).
-typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 struct SliceConst {
     uint32_t half2, keep2;
     u16x2 cap2;
@@ -101,26 +141,25 @@ __device__ __forceinline__ uint32_t slice_pair(uint32_t v, const SliceConst &c) 
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(t, c.cap2));
 }
 
-// A batch of 2 and more on the matrix core: v_mfma_f32_4x4x4_16b_f16 takes, from every lane, four weights of its row (two masked
+// A batch of 2 .. 4 on the matrix core: v_mfma_f32_4x4x4_16b_f16 takes, from every lane, four weights of its row (two masked
 // dwords) and four activations of batch row lane % 4, and gives lane 4 b + m the sums of rows 4 b .. 4 b + 3 for batch row m.  The
 // operand layout is the tile's own, so a quad of activations is read from LDS once for four batch rows (by v_dot2 it was once for
 // each, which is what bound these kernels) and the multiplications leave the vector ALUs.  Two fields with one key make an operand;
 // Steps<R> lists them.  Lanes of batch rows that do not exist read some other row's and their sums are dropped.
 // By v_dot2 / now, us: 28672 x 8192 M = 4: r = 2 35.8 / 20.6, r = 4 35.4 / 27.3, r = 8 48 / 44.9; 4096 x 4096 r = 4 M = 2, 3, 4 7.3 / 6.9,
 // 7.9 / 7.2, 8.4 / 7.3; a decode step of four Llama-2-7B blocks 179 / 159, 205 / 169, 244 / 175; a mixed stack of 12 Llama-3-70B blocks
-// 968 / 948, 1179 / 923, 1009 (narrow kernel) / 934.
+// 968 / 948, 1179 / 923.
 // X_g per batch row: partial sums of the four rows change places over DPP steps until lane l holds those of row l % 4.
-template <int M, int Q> __device__ __forceinline__ float quad_sums(const uint32_t (&x)[M], int lane) {
-    constexpr int n = M - 4 * Q < 4 ? M - 4 * Q : 4;
+template <int M> __device__ __forceinline__ float quad_sums(const uint32_t (&x)[M], int lane) {
     float s[4];
 #pragma unroll
-    for (int m = 0; m < 4; ++m) s[m] = m < n ? dot2(x[4 * Q + (m < n ? m : 0)], 0x3C003C00u, 0.f) : 0.f;  // (1.0, 1.0)
+    for (int m = 0; m < 4; ++m) s[m] = m < M ? dot2(x[m < M ? m : 0], 0x3C003C00u, 0.f) : 0.f;  // (1.0, 1.0)
     auto swap1 = [](float v) { return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xB1, 0xf, 0xf, true)); };
     auto swap2 = [](float v) { return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x4E, 0xf, 0xf, true)); };
     const bool odd = lane & 1, high = lane & 2;
     const float a = (odd ? s[1] : s[0]) + swap1(odd ? s[0] : s[1]);
     float t;
-    if constexpr (n > 2) {
+    if constexpr (M > 2) {
         const float b = (odd ? s[3] : s[2]) + swap1(odd ? s[2] : s[3]);
         t = (high ? b : a) + swap2(high ? a : b);
     } else {
@@ -136,7 +175,6 @@ template <int R, int M, bool SL, bool XB>
 __device__ __forceinline__ void tile_math_mfma(const TileRegs<R, M> &t, const LayerDesc &L, int lane, uint32_t *xlds, float (&yacc)[kAcc<M>]) {
     using T = Layout<R>;
     using S = Steps<R>;
-    constexpr int NQ = kQuads<M>;
     const SliceConst sc = slice_const(SL ? L.rs : kC);
     uint32_t xl[M];
     const int pos = (lane & ~15) | (int)((step_table<R>() >> (4 * (lane & 15))) & 15);
@@ -145,22 +183,16 @@ __device__ __forceinline__ void tile_math_mfma(const TileRegs<R, M> &t, const La
         xl[m] = XB ? bf16_pair_to_f16_pair(t.xl[m]) : t.xl[m];
         xlds[m * kRowDwords<M> + pos] = xl[m];
     }
-    float xg[NQ];
-    static_for<NQ>([&](auto q) { xg[q] = quad_sums<M, q>(xl, lane); });
+    const float xg = quad_sums<M>(xl, lane);
     const int m = lane & 3;
-    f32x4 acc[NQ][T::NKEYS];
+    f32x4 acc[T::NKEYS];
 #pragma unroll
-    for (int q = 0; q < NQ; ++q)
-#pragma unroll
-        for (int k = 0; k < T::NKEYS; ++k) acc[q][k] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int k = 0; k < T::NKEYS; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const u32x4 *xq = reinterpret_cast<const u32x4 *>(xlds + (m < M ? m : 0) * kRowDwords<M>);
     static_for<64 / S::BP>([&](auto bl) {
-        u32x4 x[NQ][S::BP / 4];
+        u32x4 x[S::BP / 4];
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const u32x4 *xq = reinterpret_cast<const u32x4 *>(xlds + (4 * q + m < M ? 4 * q + m : 4 * q) * kRowDwords<M>);
-#pragma unroll
-            for (int i = 0; i < S::BP / 4; ++i) x[q][i] = xq[bl * (S::BP / 4) + i];
-        }
+        for (int i = 0; i < S::BP / 4; ++i) x[i] = xq[bl * (S::BP / 4) + i];
         static_for<S::N>([&](auto si) {
             constexpr Step st = S::at(si);
             auto field = [&](auto uc, auto oc) {
@@ -173,23 +205,99 @@ __device__ __forceinline__ void tile_math_mfma(const TileRegs<R, M> &t, const La
             };
             const u32x2 a = {field(IntC<st.ua>{}, IntC<st.oa>{}), field(IntC<st.ub>{}, IntC<st.ob>{})};
             constexpr int key = key_index<R>(st.oa);
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                const u32x2 b = {x[q][st.pa / 4][st.pa % 4], x[q][st.pb / 4][st.pb % 4]};
-                acc[q][key] = __builtin_amdgcn_mfma_f32_4x4x4f16(__builtin_bit_cast(half4_t, a), __builtin_bit_cast(half4_t, b), acc[q][key], 0, 0, 0);
-            }
+            const u32x2 b = {x[st.pa / 4][st.pa % 4], x[st.pb / 4][st.pb % 4]};
+            acc[key] = __builtin_amdgcn_mfma_f32_4x4x4f16(__builtin_bit_cast(half4_t, a), __builtin_bit_cast(half4_t, b), acc[key], 0, 0, 0);
         });
     });
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const float s = (float)t.s[i], z = (float)t.z[i];
+        float d = 0.f;
+        // field value = digit * 2^(key-24); back to code units, then Eq. 1's rescale 2^(8-r)
+        static_for<T::NKEYS>([&](auto k) { d = fmaf(acc[k][i], __builtin_ldexpf(1.f, 24 - T::key(k) + kC - R), d); });
+        yacc[i] = fmaf((float)t.s[i], fmaf(-(float)t.z[i], xg, d), yacc[i]);
+    }
+}
+
+// 5 and more rows, 16 at a time: v_mfma_f32_16x16x32_f16, activations (batch row lane % 16) times weights (row lane % 16 of a quarter of
+// the tile), the four quarters of a wave holding the four quarters of 32 columns.  In the tile a quarter of the wave holds all columns of ITS
+// 16 rows, so four lane dwords at a time change places like the entries of a 4 x 4 matrix (a v_permlane32_swap and a v_permlane16_swap
+// for every two): afterwards dword t of the four holds rows 16 t .. 16 t + 15, and quarter h of the wave the columns of what was dword h.  All codes
+// come to one place of their half, so that one accumulator serves the tile, and the matrix core adds the activations up as well (times 1.0).
+// The place: this instruction adds its products after aligning them as if a subnormal weight began at 2^-14, so codes stand as high in the
+// mantissa as one mask or shift each allows (relative error of 8192 x 28672, r = 2, M = 16 against 64 bits with them at bit 0 2.44e-4, here 2.07e-4; by 32x32x16 instructions on subnormals, with
+// the activations scaled, it was 2.28e-4.  6 and 8 bits are as near at bit 0, which costs one instruction less).
+//   The activations turn from rows to columns in the wave's own LDS (4 or 8 transfers of 1 KB a tile); no wave waits for another.  A tile is
+// 20 matrix and about 200 vector instructions at every width, and the memory bounds it.  us, what this took the place of (4x4x4 instructions, which read all
+// activations from LDS for every four rows of x, or a kernel with an activation launch of its own and a barrier a tile) / now, r = 4: 28672 x 8192 M = 8 30.4 /
+// 25.7, M = 16 41.3 / 28.9; 8192 x 28672 M = 16 38.9 / 27.8; 4096 x 4096 M = 16 12.1 / 8.9; r = 8 28672 x 8192 M = 16 61.4 / 42.4; mixed stacks of four
+// Llama-3-70B blocks M = 8 372 / 323, M = 16 393 / 375, 32 Llama-2-7B blocks M = 8 659 / 603.
+template <int R> constexpr int kCodeBit = R == 2 ? 8 : R == 3 ? 6 : R == 4 ? 4 : 0;
+template <int R, bool XB, int M>
+__device__ __forceinline__ void tile_math_cols(const TileRegs<R, M> &t, int lane, uint32_t *xlds, float (&yacc)[kAcc<M>]) {
+    using T = Layout<R>;
+    using C = ColSteps<R>;
+    static_for<M / 4>([&](auto i) {
+        u32x4 v;
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            float d = 0.f;
-            // field value = digit * 2^(key-24); back to code units, then Eq. 1's rescale 2^(8-r)
-            static_for<T::NKEYS>([&](auto k) { d = fmaf(acc[q][k][i], __builtin_ldexpf(1.f, 24 - T::key(k) + kC - R), d); });
-            yacc[4 * q + i] = fmaf(s, fmaf(-z, xg[q], d), yacc[4 * q + i]);
-        }
+        for (int k = 0; k < 4; ++k) v[k] = XB ? bf16_pair_to_f16_pair(t.xl[4 * i + k]) : t.xl[4 * i + k];
+        reinterpret_cast<u32x4 *>(xlds)[i * 64 + lane] = v;
+    });
+    half8_t x[4];
+    static_for<4>([&](auto q) {
+        const int c = C::chunk(q, lane >> 4), row = lane & (M - 1) & 15;  // (8 rows: the other half of the lanes repeats them)
+        x[q] = __builtin_bit_cast(half8_t, reinterpret_cast<const u32x4 *>(xlds)[((row >> 3) * 2 + (c >> 3)) * 64 + (row & 7) * 8 + ((c ^ row) & 7)]);
+    });
+    uint32_t w[4 * R];
+#pragma unroll
+    for (int i = 0; i < 4 * R; ++i) w[i] = t.w[i];
+    static_for<4 * R>([&](auto b) {
+        if constexpr (b / C::S % 4 == 0) quarter_transpose(w[b], w[b + C::S], w[b + 2 * C::S], w[b + 3 * C::S]);
+    });
+    // scale and zero-offset of the rows l % 16 of each quarter
+    uint32_t sz[4];
+    sz[0] = (uint32_t)__builtin_bit_cast(uint16_t, t.s) | (uint32_t)__builtin_bit_cast(uint16_t, t.z) << 16;
+#pragma unroll
+    for (int i = 1; i < 4; ++i) {
+        sz[i] = sz[0];
+        asm volatile("" : "+v"(sz[i]));  // four registers, not one value: the swaps change both of theirs
+    }
+    quarter_transpose(sz[0], sz[1], sz[2], sz[3]);
+    constexpr int P = kCodeBit<R>;
+    const _Float16 one = (_Float16)1.f;
+    const half8_t ones = {one, one, one, one, one, one, one, one};
+    f32x4 acc[4], xg = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    static_for<4>([&](auto q) {
+        xg = __builtin_amdgcn_mfma_f32_16x16x32_f16(x[q], ones, xg, 0, 0, 0);
+        static_for<4>([&](auto tc) {
+            u32x4 b;
+            static_for<4>([&](auto i) {
+                constexpr int pair = 4 * C::chunk(q, 0) + i, unit = pair / T::PPU;
+                uint32_t code = 0;
+                static_for<T::NOPS>([&](auto oc) {
+                    constexpr Op o = T::op(oc);
+                    if constexpr (o.pair == pair % T::PPU) {
+                        constexpr int pos = ctz16(o.mask) + o.sh, bits = popc16(o.mask), to = P + o.d;
+                        const uint32_t v = w[unit * T::UD + o.dw + tc * C::S];
+                        if constexpr (pos + bits == 16 && to == 0)  // the top of its half, down to bit 0: no mask
+                            code |= __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, v) >> (uint16_t)pos);
+                        else
+                            code |= (pos >= to ? v >> (pos - to) : v << (to - pos)) & ((uint32_t)(((1 << bits) - 1) << to) * 0x10001u);
+                    }
+                });
+                b[(int)i] = code;
+            });
+            acc[tc] = __builtin_amdgcn_mfma_f32_16x16x32_f16(x[q], __builtin_bit_cast(half8_t, b), acc[tc], 0, 0, 0);
+        });
+    });
+    // scale * (2^(32-r-P) * acc - zero * X_g): the power of two goes to scale and zero, once for four batch rows
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const half2_t h = __builtin_bit_cast(half2_t, sz[i]);
+        const float s = (float)h.x * __builtin_ldexpf(1.f, 24 + kC - R - P), z = (float)h.y * -__builtin_ldexpf(1.f, P + R - kC - 24);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) yacc[4 * i + v] = fmaf(s, fmaf(z, xg[v], acc[i][v]), yacc[4 * i + v]);
     }
 }
 
@@ -200,7 +308,10 @@ template <int R, int M, bool SL = false, bool XB = false>
 __device__ __forceinline__ void tile_math(const TileRegs<R, M> &t, const LayerDesc &L, int lane, uint32_t *xlds, float (&yacc)[kAcc<M>]) {
     using T = Layout<R>;
     static_assert(!SL || R == kC, "slicing in registers starts from the 8-bit parent");
-    if constexpr (kQuadRows<M>) {
+    if constexpr (kColRows<M>) {
+        static_assert(!SL, "from the parent: up to 4 rows");
+        tile_math_cols<R, XB, M>(t, lane, xlds, yacc);
+    } else if constexpr (kQuadRows<M>) {
         tile_math_mfma<R, M, SL, XB>(t, L, lane, xlds, yacc);
     } else {
         constexpr int NU = 4 * R / T::UD;
@@ -240,19 +351,25 @@ __device__ __forceinline__ void tile_math(const TileRegs<R, M> &t, const LayerDe
 
 // a wave's sums as one row per lane, in M rows of LDS of its own
 template <int M> __device__ __forceinline__ void put_rows(const float (&yacc)[kAcc<M>], uint32_t *room, int lane) {
-    if constexpr (kQuadRows<M>) {
+    if constexpr (kColRows<M>) {
 #pragma unroll
-        for (int q = 0; q < kQuads<M>; ++q) {
-            const f32x4 v = {yacc[4 * q], yacc[4 * q + 1], yacc[4 * q + 2], yacc[4 * q + 3]};
-            const int m = 4 * q + (lane & 3);
-            if (m < M) *reinterpret_cast<u32x4 *>(room + m * kRowDwords<M> + (lane & ~3)) = __builtin_bit_cast(u32x4, v);
+        for (int v = 0; v < 4; ++v) {
+            const int m = 4 * (lane >> 4) + v;  // quarter i of the tile, row lane % 16 of it: register 4 i + v
+            if (m < M) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) room[m * kRowDwords<M> + 16 * i + (lane & 15)] = __builtin_bit_cast(uint32_t, yacc[4 * i + v]);
+            }
         }
+    } else if constexpr (kQuadRows<M>) {
+        const f32x4 v = {yacc[0], yacc[1], yacc[2], yacc[3]};
+        const int m = lane & 3;
+        if (m < M) *reinterpret_cast<u32x4 *>(room + m * kRowDwords<M> + (lane & ~3)) = __builtin_bit_cast(u32x4, v);
     } else {
         room[lane] = __builtin_bit_cast(uint32_t, yacc[0]);
     }
 }
 template <int M> __device__ __forceinline__ void rows_of(const float (&yacc)[kAcc<M>], uint32_t *xlds, int lane, float (&rows)[M]) {
-    if constexpr (kQuadRows<M>) {
+    if constexpr (M >= 2) {
         put_rows<M>(yacc, xlds, lane);
 #pragma unroll
         for (int m = 0; m < M; ++m) rows[m] = __builtin_bit_cast(float, xlds[m * kRowDwords<M> + lane]);
@@ -269,14 +386,24 @@ template <int R, int M> struct PrefetchDepth {
     static constexpr int value = M > 4 ? (R <= 4 ? 2 : 1) : R <= 2 ? 4 : R == 3 ? 3 : R <= 6 ? 2 : 1;
 };
 
-// Tiles [u_begin, u_end) of one layer, owned by share `wave`.
-template <int R, int M, bool SL = false>
-__device__ __forceinline__ void run_units(const LayerDesc &L, const StackParams &p, int u_begin, int u_end, int wave,
-                                          int lane, uint32_t *xlds) {
-    constexpr int D = PrefetchDepth<R, M>::value, NB = D + 1;
-    int rb = u_begin / L.G;
-    int g = u_begin - rb * L.G;
-    int ga = g;
+// A share of the persistent schedule belongs to a workgroup: its waves take the groups of a row block in turn and add their sums up through
+// LDS where the row block ends, so that what a share hands over to others is one set of sums for each of its two ends.  (A share per wave handed over eight
+// times as much: 28672 x 8192, r = 4, M = 16 37.3 us, 33.1 so, M = 4 26.9 / 25.3.)
+//   The first of them (the end of a row block that earlier shares began) is stored as soon as it is known and counted when the next
+// row block ends.  The last one is kept in registers: the counter, read while the last tiles are multiplied, shows as a rule that all others
+// have been counted, and then the share adds their sums to its own and is done.  Otherwise it stores and counts its own, too, and
+// whoever completes the count adds the slots up, in the same order.  (All pieces stored and counted at the end: 33.1 us, 31.9 so.)
+// Tiles [u_begin, u_end) of one layer.
+template <int R, int M, bool SL>
+__device__ __forceinline__ void run_share(const LayerDesc &L, const StackParams &p, int u_begin, int u_end, int worker, int w, int lane,
+                                          uint32_t *xlds, uint32_t (*red)[kWgWaves][M][kRowDwords<M>], int32_t *flags, int &parity) {
+    constexpr int D = PrefetchDepth<R, M>::value, NB = D + 1, NW = kWgWaves;
+    constexpr int MR = (M + NW - 1) / NW;  // rows of x that a wave adds up
+    constexpr int kTileLoads = R + 2 + (kColRows<M> ? M / 4 : M);
+    const int G = L.G, rows = row_count<M>(L);
+    int32_t MQ_GLOBAL *cnt = gl(p.cnt + L.cnt_off);
+    int rb = u_begin / G, ga = u_begin - rb * G;
+    int seg_end = u_end < (rb + 1) * G ? u_end : (rb + 1) * G;
     float yacc[kAcc<M>];
 #pragma unroll
     for (int i = 0; i < kAcc<M>; ++i) yacc[i] = 0.f;
@@ -285,61 +412,176 @@ __device__ __forceinline__ void run_units(const LayerDesc &L, const StackParams 
     // for the loads); past the end of the run the last tile is fetched again instead of
     // branching around the loads
     TileRegs<R, M> buf[NB];
-    int u_pf = u_begin, g_pf = g;
+    int u = u_begin + w;
+    int u_pf = u < u_end ? u : u_end - 1, g_pf = u_pf % G;
     auto prefetch = [&](TileRegs<R, M> &t) {
         load_tile<R, M>(t, L, u_pf, g_pf, lane);
-        if (u_pf + 1 < u_end) {
-            ++u_pf;
-            g_pf = g_pf + 1 == L.G ? 0 : g_pf + 1;
+        if (u_pf + NW < u_end) {
+            u_pf += NW;
+            g_pf += NW;
+            while (g_pf >= G) g_pf -= G;
         }
     };
     static_for<D>([&](auto j) { prefetch(buf[j]); });
-    int u = u_begin;
-    while (u < u_end) {
-        static_for<NB>([&](auto j) {
-            if (u >= u_end) return;
-            prefetch(buf[(j + D) % NB]);
-            tile_math<R, M, SL>(buf[j], L, lane, xlds, yacc);
-            ++g;
-            ++u;
-            if (g == L.G || u == u_end) {
-                const int row = rb * kRowBlock + lane;
-                float rows[M];
-                rows_of<M>(yacc, xlds, lane, rows);
-                finish_row_block<M>(L, p, p.cnt + L.cnt_off + rb, L.cost_start + (uint64_t)rb * L.G * L.cost, ga, g,
-                                    rows, wave, lane, [&](const float(&tot)[M]) {
+
+    auto store_row = [&](int b, int m, float v) {
+        const int row = b * kRowBlock + lane;
+        if (row < L.N && m < rows) store_y(L.y, (size_t)m * L.N + row, v, L.flags);
+    };
+    auto slot_of = [&](int wk, int slot, int m) { return gl(p.part + (size_t)(wk * 2 + slot) * (size_t)(64 * M) + (m * 64 + lane)); };
+    // slots of the shares w_lo .. w_hi that worked on row block b, added up in share order (the first one's is slot 1)
+    auto add_slots = [&](int w_lo, int w_hi, int first, float (&tot)[MR]) {
+        constexpr int kBatch = 4;
+        for (int w0 = w_lo; w0 <= w_hi; w0 += kBatch) {
+            float t[kBatch][MR];
 #pragma unroll
-                                        for (int m = 0; m < M; ++m)
-                                            if (row < L.N && m < row_count<M>(L)) store_y(L.y, (size_t)m * L.N + row, tot[m], L.flags);
-                                    });
-                ++rb;
-                g = 0;
-                ga = 0;
+            for (int j = 0; j < kBatch; ++j)
 #pragma unroll
-                for (int i = 0; i < kAcc<M>; ++i) yacc[i] = 0.f;
+                for (int i = 0; i < MR; ++i) {
+                    const int wk = w0 + j <= w_hi ? w0 + j : w_hi, m = w + NW * i;
+                    t[j][i] = __hip_atomic_load(slot_of(wk, wk == first ? 1 : 0, m < M ? m : 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j)
+                if (w0 + j <= w_hi) {
+#pragma unroll
+                    for (int i = 0; i < MR; ++i) tot[i] += t[j][i];
+                }
+        }
+    };
+    auto first_share = [&](int b) { return wave_of(L.cost_start + (uint64_t)b * G * L.cost, p.nworkers, p.cost_total); };
+    auto last_share = [&](int b) { return wave_of(L.cost_start + ((uint64_t)b * G + (G - 1)) * L.cost, p.nworkers, p.cost_total); };
+    int head_rb = 0, head_n = 0, head_age = 0, tail_n = 0;  // groups of a piece that is stored; tiles since then
+    bool head_counted = false;
+    const int tail_rb = (u_end - 1) / G, tail_gb = u_end - tail_rb * G;
+    const bool has_tail = tail_gb < G && tail_rb * G >= u_begin;
+    int32_t others = -1;  // wave 0: groups of the last row block that others have stored
+    // flags: 0 this share completes the first row block, 1 the last, 2 + parity the last one's other pieces are there
+    auto count_head = [&]() {
+        if (w == 0 && lane == 0) flags[0] = __hip_atomic_fetch_add(cnt + head_rb, head_n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + head_n == G;
+        head_counted = true;
+    };
+    // the end of a row block, or of the share: wave w adds up rows w, w + 8, ... of x
+    auto finish = [&](int gb) {
+        const bool tail = has_tail && seg_end == u_end;
+        if (tail && w == 0 && lane == 0) flags[2 + parity] = others + gb == G;
+        put_rows<M>(yacc, &red[parity][w][0][0], lane);
+#pragma unroll
+        for (int i = 0; i < kAcc<M>; ++i) yacc[i] = 0.f;
+        const bool count = head_n != 0 && !head_counted;
+        if (count) {  // every wave's write-through stores must have been acknowledged before the counter moves: they are older than ...
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            if (head_age >= D) wait_transfers<D * kTileLoads>();  // ... the transfers in flight
+            else wait_transfers<0>();
+        }
+        lds_barrier();
+        if (count) count_head();
+        float t[MR];
+#pragma unroll
+        for (int i = 0; i < MR; ++i) {
+            const int m = w + NW * i < M ? w + NW * i : 0;
+            t[i] = __builtin_bit_cast(float, red[parity][0][m][lane]);
+#pragma unroll
+            for (int k = 1; k < NW; ++k) t[i] += __builtin_bit_cast(float, red[parity][k][m][lane]);
+        }
+        const bool all_there = tail && __builtin_amdgcn_readfirstlane(flags[2 + parity]);
+        parity ^= 1;  // (whoever writes here next has passed the next row block's barrier, and so has everyone who reads now)
+        if ((ga == 0 && gb == G) || all_there) {
+            if (all_there) {
+                const int lo = first_share(rb);
+                add_slots(lo + 1, last_share(rb), -1, t);
+                if (w == 0 && lane == 0) __hip_atomic_store(cnt + rb, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
+#pragma unroll
+            for (int i = 0; i < MR; ++i)
+                if (w + NW * i < M) store_row(rb, w + NW * i, t[i]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < MR; ++i)
+                if (w + NW * i < M)
+                    __hip_atomic_store(slot_of(worker, ga == 0 ? 1 : 0, w + NW * i), t[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (tail) {
+                tail_n = gb;
+            } else {
+                head_rb = rb;
+                head_n = gb - ga;
+                head_age = 0;
+            }
+        }
+    };
+
+    auto next_row_block = [&]() {
+        finish(seg_end - rb * G);
+        ++rb;
+        ga = 0;
+        seg_end = seg_end + G < u_end ? seg_end + G : u_end;
+    };
+    auto multiply = [&](const TileRegs<R, M> &t) {
+        tile_math<R, M, SL>(t, L, lane, xlds, yacc);
+        u += NW;
+        ++head_age;
+    };
+    // Whole rounds of the ring.  The loop has one way out, at its end: with one behind every tile the compiler joins those with the way back
+    // and has every round begin with a wait for all but the last loads (32 Llama-2-7B blocks, mixed widths, M = 1 526 us, 487 so, M = 5 634 / 584).
+    while (u + (NB - 1) * NW < u_end)
+        static_for<NB>([&](auto j) {
+            while (u >= seg_end) next_row_block();
+            prefetch(buf[(j + D) % NB]);
+            multiply(buf[j]);
         });
+    if (has_tail && w == 0) others = __hip_atomic_load(cnt + tail_rb + own_register(0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    while (u < u_end) {  // the last tiles, D at most, are on their way
+        while (u >= seg_end) next_row_block();
+        multiply(buf[0]);
+        static_for<NB - 1>([&](auto j) { buf[j] = buf[j + 1]; });
     }
+    while (seg_end < u_end) next_row_block();
+    finish(seg_end - rb * G);
+    if (head_n == 0 && tail_n == 0) return;
+    if (tail_n != 0 || !head_counted) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        wait_transfers<0>();
+        lds_barrier();
+        if (head_n != 0 && !head_counted) count_head();
+        if (tail_n != 0 && w == 0 && lane == 0)
+            flags[1] = __hip_atomic_fetch_add(cnt + tail_rb, tail_n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + tail_n == G;
+    }
+    lds_barrier();
+    auto complete = [&](int b) {
+        float tot[MR];
+#pragma unroll
+        for (int i = 0; i < MR; ++i) tot[i] = 0.f;
+        const int lo = first_share(b);
+        add_slots(lo, last_share(b), lo, tot);
+#pragma unroll
+        for (int i = 0; i < MR; ++i)
+            if (w + NW * i < M) store_row(b, w + NW * i, tot[i]);
+        if (w == 0 && lane == 0) __hip_atomic_store(cnt + b, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    if (head_n != 0 && __builtin_amdgcn_readfirstlane(flags[0])) complete(head_rb);
+    if (tail_n != 0 && __builtin_amdgcn_readfirstlane(flags[1])) complete(tail_rb);
 }
 
 // SL: every layer of the stack is computed from its resident 8-bit parent (LayerDesc::rs).
-template <int M, bool SL = false> __global__ __launch_bounds__(256, M > 4 ? 2 : 1) void stack_kernel(const StackParams p) {
-    __shared__ __attribute__((aligned(16))) uint32_t xlds_all[4 * M * kRowDwords<M>];
-    uint32_t *xlds = xlds_all + (threadIdx.x >> 6) * M * kRowDwords<M>;
+template <int M, bool SL = false> __global__ __launch_bounds__(64 * kWgWaves, kWgWaves / 4) void stack_kernel(const StackParams p) {
+    __shared__ __attribute__((aligned(16))) uint32_t xlds_all[kWgWaves * M * kRowDwords<M>];
+    __shared__ __attribute__((aligned(16))) uint32_t red[2][kWgWaves][M][kRowDwords<M>];
+    __shared__ int32_t flags[4];
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane((int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6));
-    if (wave >= p.nwaves) return;
-    for (int worker = wave; worker < p.nworkers; worker += p.nwaves) {
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    uint32_t *xlds = xlds_all + w * M * kRowDwords<M>;
+    int parity = 0;
+    for (int worker = blockIdx.x; worker < p.nworkers; worker += p.nwaves) {
         walk_tiles(p, worker, [&](const LayerDesc &L, int u_begin, int u_end) {
             if constexpr (SL) {
-                run_units<8, M, true>(L, p, u_begin, u_end, worker, lane, xlds);
+                run_share<8, M, true>(L, p, u_begin, u_end, worker, w, lane, xlds, red, flags, parity);
             } else {
                 switch (L.r) {
-                    case 2: run_units<2, M>(L, p, u_begin, u_end, worker, lane, xlds); break;
-                    case 3: run_units<3, M>(L, p, u_begin, u_end, worker, lane, xlds); break;
-                    case 4: run_units<4, M>(L, p, u_begin, u_end, worker, lane, xlds); break;
-                    case 6: run_units<6, M>(L, p, u_begin, u_end, worker, lane, xlds); break;
-                    default: run_units<8, M>(L, p, u_begin, u_end, worker, lane, xlds); break;
+                    case 2: run_share<2, M, false>(L, p, u_begin, u_end, worker, w, lane, xlds, red, flags, parity); break;
+                    case 3: run_share<3, M, false>(L, p, u_begin, u_end, worker, w, lane, xlds, red, flags, parity); break;
+                    case 4: run_share<4, M, false>(L, p, u_begin, u_end, worker, w, lane, xlds, red, flags, parity); break;
+                    case 6: run_share<6, M, false>(L, p, u_begin, u_end, worker, w, lane, xlds, red, flags, parity); break;
+                    default: run_share<8, M, false>(L, p, u_begin, u_end, worker, w, lane, xlds, red, flags, parity); break;
                 }
             }
         });
@@ -673,50 +915,36 @@ hipError_t launch_linear_rb_stack(const StackParams &p, const SmallTable &t, int
     }
 }
 
-// blocks (of 4 waves) the device keeps resident per compute unit, and the number of units
-template <int M, bool SL> static bool residency(int &cus, int &blocks) {
-    static int c_cus = 0, c_blocks = 0;
-    if (!c_cus) {
-        int dev = 0, a = 0, b = 0;
-        if (hipGetDevice(&dev) != hipSuccess) return false;
-        if (hipDeviceGetAttribute(&a, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return false;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, stack_kernel<M, SL>, 256, 0) != hipSuccess) return false;
-        if (b < 1) b = 1;
-        while (a * b * 4 > kMaxWaves) --b;
-        c_cus = a;
-        c_blocks = b;
+// workgroups of the persistent launch that the device keeps resident
+template <int M, bool SL> static int stack_resident() {
+    static int cached = 0;
+    if (!cached) {
+        int dev = 0, cus = 0;
+        if (hipGetDevice(&dev) != hipSuccess) return 0;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+        cached = cus;
     }
-    cus = c_cus;
-    blocks = c_blocks;
-    return true;
+    return cached;
 }
 
 template <int M, bool SL> static hipError_t launch_stack_mx(StackParams p, int max_cost, hipStream_t s) {
-    int cus = 0, blocks = 0;
-    if (!residency<M, SL>(cus, blocks)) return hipErrorUnknown;
-    int hw = cus * blocks * 4;
-    if (p.worker_cap && hw > p.worker_cap) hw = p.worker_cap;
-    const uint64_t max_workers = p.worker_cap ? (uint64_t)p.worker_cap : (uint64_t)max_workers_valu(M);
+    const int hw = stack_resident<M, SL>();
+    if (!hw) return hipErrorUnknown;
+    const uint64_t most = (uint64_t)(p.worker_cap ? p.worker_cap : max_workers_valu(M));
     // every share must be at least one tile long, so that each share between the first
     // and last contributor of a row block really owns a tile of it
     uint64_t cap = p.cost_total / (uint64_t)max_cost;
+    if (cap > most) cap = most;
     if (cap < 1) cap = 1;
     p.nwaves = (int)(cap < (uint64_t)hw ? cap : (uint64_t)hw);
-    // A single big layer at batch 1 is over in 25-50 us: with every resident wave a share is only a few tiles
-    // long and each row block is handed over many times.  A quarter of the waves still saturates HBM for that
-    // long (each keeps its 8 KB in flight) and takes 10-25 % off the call (measured on the Llama-3-70B MLP shapes).
-    if (!p.table && p.nwaves > 2048) p.nwaves = 2048;
-    // Several interleaved shares per wave even out layers of different width (a wave serves
-    // shares w, w + nwaves, ...), but every share ends with up to two hand-overs of a few
-    // microseconds, so shares stay at least ~128 tiles long (measured: Llama-2-7B stacks are
-    // best with one share per wave, Llama-3-70B stacks gain 15 % from eight).
-    uint64_t spw = p.cost_total / ((uint64_t)max_cost * 128 * (uint64_t)p.nwaves);  // whole shares per wave
+    // Several interleaved shares per workgroup where they stay long (128 tiles a wave): they even out what the costs miss (12 Llama-3-70B blocks, M = 16, 1343 us with
+    // one share a workgroup, 1148 so), and shorter ones cost more in hand-overs (three small blocks, M = 1 38 us, two shares a workgroup 41).
+    uint64_t spw = p.cost_total / ((uint64_t)max_cost * (128 * kWgWaves) * (uint64_t)p.nwaves);  // whole shares per workgroup
     if (spw > (uint64_t)kSharesPerWave) spw = kSharesPerWave;
-    while (spw > 1 && spw * (uint64_t)p.nwaves > max_workers) --spw;
+    while (spw > 1 && spw * (uint64_t)p.nwaves > most) --spw;
     if (spw < 1) spw = 1;
     p.nworkers = (int)(spw * (uint64_t)p.nwaves);
-    const unsigned nblocks = (unsigned)((p.nwaves + 3) / 4);
-    return launch((stack_kernel<M, SL>), dim3(nblocks), dim3(256), 0, s, p);
+    return launch((stack_kernel<M, SL>), dim3((unsigned)p.nwaves), dim3(64 * kWgWaves), 0, s, p);
 }
 template <int M> static hipError_t launch_stack_m(StackParams p, int max_cost, bool from_parent, hipStream_t s) {
     return from_parent ? launch_stack_mx<M, true>(p, max_cost, s) : launch_stack_mx<M, false>(p, max_cost, s);
@@ -729,7 +957,8 @@ hipError_t launch_stack(StackParams p, int max_cost, bool from_parent, hipStream
         case 3: return launch_stack_m<3>(p, max_cost, from_parent, s);
         case 4: return launch_stack_m<4>(p, max_cost, from_parent, s);
         default:
-            return p.M <= 8 && !from_parent ? launch_stack_mx<8, false>(p, max_cost, s) : hipErrorInvalidValue;
+            if (p.M > 16 || from_parent) return hipErrorInvalidValue;
+            return p.M <= 8 ? launch_stack_mx<8, false>(p, max_cost, s) : launch_stack_mx<16, false>(p, max_cost, s);
     }
 }
 
