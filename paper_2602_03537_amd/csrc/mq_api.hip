@@ -278,7 +278,7 @@ mq_status run_single(const mq_layer &l, int64_t M, void *ws, size_t ws_bytes, mq
     p.n_jobs = (use_wide(M) ? wide_chunks_padded(M) : p.single.CB) * p.single.G;
     hipError_t e;
     // bf16 activations (packed layers only: a single from-parent call takes fp16): the low-latency launch converts them itself
-    const bool rb = rows && low_latency_call(row_blocks, l.K / kGroup, M, part_b);
+    const bool rb = rows && low_latency_call(row_blocks, l.K / kGroup, r_ws, M, part_b);
     if (rows && (l.flags & MQ_X_BF16) && !rb) {
         if (launch_xcvt(p, (hipStream_t)stream) != hipSuccess) return MQ_ERR_HIP;
         p.single.x_bf16 = nullptr;  // from here on x is the fp16 copy

@@ -767,8 +767,8 @@ __global__ __launch_bounds__(64 * kRbWaves<M>, (kRbPerSimd<R, M>)) void linear_r
 
 template <int R, int M, bool SL = false>
 static hipError_t launch_linear_rb_rm(const LayerDesc &L, float *part, int32_t *cnt, hipStream_t s) {
-    const int KS = pick_k_slices(L.RB, L.G, L.M);
-    const int W = rb_waves(L.G, L.M, KS);
+    const RowShape shape = single_row_shape(L.RB, L.G, L.r, L.M);
+    const int KS = shape.KS, W = shape.W;
     const unsigned blocks = M > 8 ? (unsigned)((L.RB * KS + 7) / 8 * 8 * ((L.M + 15) / 16)) : (unsigned)(L.RB * KS);
     if constexpr (!SL) {  // a single from-parent call takes fp16 activations
         if (L.x_bf16) {
