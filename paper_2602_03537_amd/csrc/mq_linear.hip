@@ -806,8 +806,10 @@ hipError_t launch_linear_rb(const LayerDesc &L, float *part, int32_t *cnt, hipSt
 
 // The same shape for a SMALL stack (the linears of a decoder block that share their input, say): the workgroups of all
 // layers in one launch; a workgroup finds its layer and its descriptor in the kernel arguments (at most 16 layers).
-template <int M, bool SL, bool CH = false>
-__global__ __launch_bounds__(64 * kRbWaves<M>, (kRbPerSimd<8, M>)) void linear_rb_stack_kernel(const StackParams p, const SmallTable t) {
+// MAXR: the widest layer it serves.  One row and up to four bits keep to 64 registers, as alone, so that two workgroups of 16 waves share a compute unit (at
+// 100, for all widths, one): two 11008 x 4096 layers, r = 2 11.0 -> 9.8 us, r = 3 12.8 -> 11.6, r = 4 14.2 -> 13.4.  All widths at 64 registers spill.
+template <int M, bool SL, bool CH = false, int MAXR = 8>
+__global__ __launch_bounds__(64 * kRbWaves<M>, (kRbPerSimd<MAXR, M>)) void linear_rb_stack_kernel(const StackParams p, const SmallTable t) {
     __shared__ __attribute__((aligned(16))) uint32_t red[kRbWaves<M>][M][kRowDwords<M>];
     __shared__ __attribute__((aligned(16))) uint32_t xlds_all[kRbWaves<M> * M * kRowDwords<M>];
     // the grid holds exactly sum(RB * KS) workgroups; each layer's first one and the descriptors come with the kernel
@@ -829,21 +831,32 @@ __global__ __launch_bounds__(64 * kRbWaves<M>, (kRbPerSimd<8, M>)) void linear_r
             case 2: linear_rb_body<2, M, false, CH>(L, KS, blk, slot0, p.part, cnt, red, xlds_all, chain); break;
             case 3: linear_rb_body<3, M, false, CH>(L, KS, blk, slot0, p.part, cnt, red, xlds_all, chain); break;
             case 4: linear_rb_body<4, M, false, CH>(L, KS, blk, slot0, p.part, cnt, red, xlds_all, chain); break;
-            case 6: linear_rb_body<6, M, false, CH>(L, KS, blk, slot0, p.part, cnt, red, xlds_all, chain); break;
-            default: linear_rb_body<8, M, false, CH>(L, KS, blk, slot0, p.part, cnt, red, xlds_all, chain); break;
+            case 6:
+                if constexpr (MAXR >= 6) linear_rb_body<6, M, false, CH>(L, KS, blk, slot0, p.part, cnt, red, xlds_all, chain);
+                break;
+            case 8:
+                if constexpr (MAXR >= 8) linear_rb_body<8, M, false, CH>(L, KS, blk, slot0, p.part, cnt, red, xlds_all, chain);
+                break;
         }
     }
 }
 
+// The stacks of the kernel with MAXR = 4
+template <class Layer> static bool rb_stack_low_widths(int n_layers, int M, bool from_parent, bool chained, Layer &&layer) {
+    if (M != 1 || from_parent || chained) return false;
+    for (int i = 0; i < n_layers; ++i)
+        if (layer(i).r > 4) return false;
+    return true;
+}
 // workgroups of `waves` waves of the small-stack kernel that the device holds at one time
-template <int M, bool SL, bool CH = false> static int rb_stack_resident(int waves) {
+template <int M, bool SL, bool CH = false, int MAXR = 8> static int rb_stack_resident(int waves) {
     static int cached[3] = {0, 0, 0};
     const int slot = waves == 16 ? 0 : waves == 8 ? 1 : 2;
     if (cached[slot]) return cached[slot];
     int dev = 0, cus = 0, b = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, linear_rb_stack_kernel<M, SL, CH>, 64 * waves, 0) != hipSuccess)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, (linear_rb_stack_kernel<M, SL, CH, MAXR>), 64 * waves, 0) != hipSuccess)
         return 0;
     cached[slot] = cus * (b < 1 ? 1 : b);
     return cached[slot];
@@ -855,9 +868,11 @@ template <int M> static int rb_stack_resident_v(bool from_parent, bool chained, 
     return from_parent ? rb_stack_resident<M, true>(waves) : rb_stack_resident<M, false>(waves);
 }
 // chained: the variant of the kernel whose layers may wait for each other (it is the one whose residency matters then)
-static int rb_stack_resident_m(int M, bool from_parent, bool chained, int waves) {
+static int rb_stack_resident_m(int M, bool from_parent, bool chained, bool low_widths, int waves) {
     switch (M) {
-        case 1: return rb_stack_resident_v<1>(from_parent, chained, waves);
+        case 1:
+            if (low_widths) return rb_stack_resident<1, false, false, 4>(waves);
+            return rb_stack_resident_v<1>(from_parent, chained, waves);
         case 2: return rb_stack_resident_v<2>(from_parent, chained, waves);
         case 3: return rb_stack_resident_v<3>(from_parent, chained, waves);
         case 4: return rb_stack_resident_v<4>(from_parent, false, waves);
@@ -870,10 +885,11 @@ bool linear_rb_stack_shape(const LayerDesc *table, int n_layers, size_t part_byt
     const int M = table[0].M;
     auto layer = [&](int i) { return RowLayer{table[i].RB, table[i].G, table[i].r}; };
     if (!low_latency_stack(n_layers, M, part_bytes, layer)) return false;
+    const bool low_widths = rb_stack_low_widths(n_layers, M, from_parent, chained, layer);
     // A chained stack is a chain of dependent steps: what counts is the length of one step, and a row block that is
     // not cut along K needs no hand-over through device memory (three round trips) before its y can be announced.
     const RowStackShape s = row_stack_shape(n_layers, M, chained, layer,
-                                            [&](int W) { return rb_stack_resident_m(M, from_parent, chained, W); });
+                                            [&](int W) { return rb_stack_resident_m(M, from_parent, chained, low_widths, W); });
     *blocks = s.blocks;
     *waves = s.waves;
     *ks_cap = s.ks_cap;
@@ -896,6 +912,10 @@ template <int M> static hipError_t launch_linear_rb_stack_m(const StackParams &p
         }
     }
     if (p.chain_total) return hipErrorInvalidValue;  // refused when the stack was planned
+    if constexpr (M == 1) {
+        if (rb_stack_low_widths(p.n_layers, M, from_parent, false, [&](int i) { return RowLayer{t.d[i].RB, t.d[i].G, t.d[i].r}; }))
+            return launch((linear_rb_stack_kernel<M, false, false, 4>), dim3((unsigned)blocks), dim3(64 * waves), 0, s, p, t);
+    }
     if constexpr (M <= kValuMaxM) {
         if (from_parent)
             return launch((linear_rb_stack_kernel<M, true>), dim3((unsigned)blocks), dim3(64 * waves), 0, s, p, t);
