@@ -346,7 +346,7 @@ def main() -> int:
         del m
         torch.cuda.empty_cache()
         # a cut of the batched workload: the first 16 blocks of the Llama-3-70B-shaped stack (widths drawn for those blocks), at the
-        # batch sizes of the three kernel families (row, narrow and wide kernels)
+        # batch sizes of the kernel families (row kernels by their instructions, wide kernel)
         cut70 = {}
         for Mb in (1, 8, 64):
             m = measure_mixed_stack(mq, synth, torch, np, dev, True, 16, Mb, max(4, args.steps // 4), 2)
@@ -431,11 +431,7 @@ def measure_mixed_stack(mq, synth, torch, np, dev, big, n_blocks, M, steps, warm
     torch.cuda.synchronize()
     ms = (time.perf_counter() - t0) * 1e3 / steps
     us = [evs[k].elapsed_time(evs[k + 1]) * 1e3 for k in range(steps)]
-    # the line of the row kernels, csrc/mq_routes.h: 5 .. 8 rows up to 200000 tiles of 64 x 128, fewer of 2 and 3 bits
-    tiles = [(N + 63) // 64 * (K // 128) for (_, _, N, K) in shapes]
-    gain = sum(t * {2: 20, 3: 14}.get(int(r), -3) for t, r in zip(tiles, widths))
-    kernel = ("mq::stack_kernel<%d, false>" % (M if M <= 4 else 8) if M <= 4 or (M <= 8 and sum(tiles) <= 200000 and gain <= 20 * 98000)
-              else "mq::gemm_stack_kernel" if M <= 16 else "mq::wide_stack_kernel")
+    kernel = "mq::stack_kernel<%d, false>" % (M if M <= 4 else 8 if M <= 8 else 16) if M <= 16 else "mq::wide_stack_kernel"
     return {"ms_wall": ms, "us": us, "bytes": nbytes, "mean_bits": mean, "n_linears": len(layers), "n_blocks": n_blocks,
             "kernel": kernel, "weights": weights}
 
