@@ -1,5 +1,5 @@
-"""Small stacks and single layers of up to 4 rows whose layers are not cut along K, on either side of each line of that rule, and the one-row stacks of up
-to four bits, which have a kernel of their own: one tile a wave, several, none for some waves, row blocks with rows that do not exist."""
+"""Small stacks and single layers whose layers are not cut along K, or in fewer slices than alone, on either side of each line of those rules, and the one-row
+stacks of up to four bits, which have a kernel of their own: one tile a wave, several, none for some waves, row blocks with rows that do not exist."""
 import pytest
 
 import paper_2602_03537_amd as mq
@@ -18,12 +18,16 @@ STACKS = {
     "33_groups_160": [(64 * 100, 33), (64 * 60 - 3, 33)],
     "49_groups_192": [(64 * 190, 49), (100, 49)],
     "256_blocks": [(64 * 200, 5), (64 * 56, 16)],
+    "40_groups_208": [(64 * 150, 40), (64 * 58, 7)],
+    "cut_in_2": [(64 * 32, 31), (64 * 32 - 5, 24)],
+    "cut_in_4": [(64 * 20, 32), (64 * 28, 48)],
+    "cut_in_2_of_128": [(64 * 100, 33), (64 * 28, 64)],
     "257_blocks": [(64 * 200, 5), (64 * 57, 16)],
 }
 
 
 @pytest.mark.parametrize("name", STACKS)
-@pytest.mark.parametrize("M,widths", [(1, (2, 3)), (1, (4, 3)), (1, (4, 6)), (1, (8, 2)), (2, (3, 6)), (3, (8, 4)), (4, (2, 4))])
+@pytest.mark.parametrize("M,widths", [(1, (2, 3)), (1, (4, 3)), (1, (4, 6)), (1, (8, 2)), (2, (3, 6)), (3, (8, 4)), (4, (2, 4)), (6, (3, 4)), (8, (8, 2)), (13, (4, 6))])
 def test_small_stacks(name, M, widths):
     host = [synth.make_layer(N, 128 * G, M=M, seed=[901, M, N, G]) for N, G in STACKS[name]]
     layers = []

@@ -16,6 +16,11 @@ extern "C" void shape(int RB, int G, int r, int M, int *out) {
     out[0] = s.KS;
     out[1] = s.W;
 }
+extern "C" void stack(int n, int RB, int G, int r, int M, int *out) {
+    const RowStackShape s = row_stack_shape(n, M, false, [&](int) { return RowLayer{RB, G, r}; }, [](int waves) { return waves > 8 ? 256 : 512; });
+    out[0] = s.ks_cap;
+    out[1] = s.waves;
+}
 extern "C" int low_latency(int64_t RB, int64_t G, int r, int64_t M) { return low_latency_call(RB, G, r, M, (size_t)1 << 24); }
 """
 
@@ -59,3 +64,15 @@ def test_measured_shapes(lib, RB, G, r, M, shape):
     (20000, 2048, 4, 16, 12.5, 13.2), (8192, 8192, 4, 16, 15.3, 14.2)])
 def test_single_layers_take_the_faster_launch(lib, N, K, r, M, low, persistent):
     assert bool(lib.low_latency(ctypes.c_int64(-(-N // 64)), ctypes.c_int64(K // 128), r, ctypes.c_int64(M))) == (low < persistent)
+
+
+# layers, row blocks of each, groups, r, M: most slices and waves on the faster side (None: cut is faster)
+@pytest.mark.parametrize("n,RB,G,r,M,shape", [
+    (3, 64, 32, 4, 1, (1, 16)), (2, 88, 16, 4, 1, (1, 16)), (2, 64, 40, 4, 1, (2, 16)), (2, 96, 40, 4, 1, (1, 16)), (2, 48, 32, 6, 1, (2, 16)), (2, 4, 8, 8, 3, (1, 8)),
+    (2, 24, 32, 4, 1, (4, 8)), (2, 56, 32, 8, 1, (2, 16)), (2, 24, 8, 4, 6, (1, 4)), (2, 112, 16, 4, 16, (1, 4)), (2, 80, 32, 4, 6, None), (2, 112, 32, 4, 6, (1, 8)),
+    (2, 112, 32, 4, 16, None)],
+    ids=["9.7/8.4", "7.5/5.8", "9.1/9.4", "11.2/10.2", "9.1/9.1", "5.2/5.2", "6.3/6.0", "10.6/9.5", "7.1/6.7", "12.3/11.3", "11.6/12.5", "14.2/13.1", "16.5/17.1"])
+def test_measured_stack_shapes(lib, n, RB, G, r, M, shape):
+    out = (ctypes.c_int * 2)()
+    lib.stack(n, RB, G, r, M, out)
+    assert (out[0], out[1]) == shape if shape else out[0] != 1
