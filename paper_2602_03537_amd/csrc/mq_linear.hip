@@ -8,6 +8,7 @@
 // which is  sum_k x[k] * scale * (S[k] - zero)  with S = t * 2^(8-r)  (Eq. 1's
 // rescale), the zero-offset and scale applied once per group instead of per weight.
 #include "mq_dma.h"
+#include "mq_share_walk.h"
 
 namespace mq {
 
@@ -402,27 +403,11 @@ __device__ __forceinline__ void run_share(const LayerDesc &L, const StackParams 
     constexpr int kTileLoads = R + 2 + (kColRows<M> ? M / 4 : M);
     const int G = L.G, rows = row_count<M>(L);
     int32_t MQ_GLOBAL *cnt = gl(p.cnt + L.cnt_off);
-    int rb = u_begin / G, ga = u_begin - rb * G;
-    int seg_end = u_end < (rb + 1) * G ? u_end : (rb + 1) * G;
+    ShareWalk walk(G, u_begin, u_end);
     float yacc[kAcc<M>];
 #pragma unroll
     for (int i = 0; i < kAcc<M>; ++i) yacc[i] = 0.f;
-
-    // ring of NB tile buffers with compile-time indices (no register copies, which would wait
-    // for the loads); past the end of the run the last tile is fetched again instead of
-    // branching around the loads
-    TileRegs<R, M> buf[NB];
-    int u = u_begin + w;
-    int u_pf = u < u_end ? u : u_end - 1, g_pf = u_pf % G;
-    auto prefetch = [&](TileRegs<R, M> &t) {
-        load_tile<R, M>(t, L, u_pf, g_pf, lane);
-        if (u_pf + NW < u_end) {
-            u_pf += NW;
-            g_pf += NW;
-            while (g_pf >= G) g_pf -= G;
-        }
-    };
-    static_for<D>([&](auto j) { prefetch(buf[j]); });
+    TileRegs<R, M> buf[NB];  // a ring with compile-time indices: copies of registers would wait for the loads
 
     auto store_row = [&](int b, int m, float v) {
         const int row = b * kRowBlock + lane;
@@ -451,27 +436,28 @@ __device__ __forceinline__ void run_share(const LayerDesc &L, const StackParams 
     };
     auto first_share = [&](int b) { return wave_of(L.cost_start + (uint64_t)b * G * L.cost, p.nworkers, p.cost_total); };
     auto last_share = [&](int b) { return wave_of(L.cost_start + ((uint64_t)b * G + (G - 1)) * L.cost, p.nworkers, p.cost_total); };
-    int head_rb = 0, head_n = 0, head_age = 0, tail_n = 0;  // groups of a piece that is stored; tiles since then
-    bool head_counted = false;
+    StoredPiece head;
+    int tail_n = 0;  // groups of the last piece once it is stored
     const int tail_rb = (u_end - 1) / G, tail_gb = u_end - tail_rb * G;
     const bool has_tail = tail_gb < G && tail_rb * G >= u_begin;
     int32_t others = -1;  // wave 0: groups of the last row block that others have stored
     // flags: 0 this share completes the first row block, 1 the last, 2 + parity the last one's other pieces are there
     auto count_head = [&]() {
-        if (w == 0 && lane == 0) flags[0] = __hip_atomic_fetch_add(cnt + head_rb, head_n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + head_n == G;
-        head_counted = true;
+        if (w == 0 && lane == 0) flags[0] = __hip_atomic_fetch_add(cnt + head.rb, head.n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + head.n == G;
+        head.counted = true;
     };
     // the end of a row block, or of the share: wave w adds up rows w, w + 8, ... of x
     auto finish = [&](int gb) {
-        const bool tail = has_tail && seg_end == u_end;
+        const int rb = walk.rb, ga = walk.ga;
+        const bool tail = has_tail && walk.seg_end == u_end;
         if (tail && w == 0 && lane == 0) flags[2 + parity] = others + gb == G;
         put_rows<M>(yacc, &red[parity][w][0][0], lane);
 #pragma unroll
         for (int i = 0; i < kAcc<M>; ++i) yacc[i] = 0.f;
-        const bool count = head_n != 0 && !head_counted;
-        if (count) {  // every wave's write-through stores must have been acknowledged before the counter moves: they are older than ...
+        const bool count = head.to_count();
+        if (count) {  // every wave's write-through stores must have been acknowledged before the counter moves
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            if (head_age >= D) wait_transfers<D * kTileLoads>();  // ... the transfers in flight
+            if (head.behind_loads<D>()) wait_transfers<D * kTileLoads>();
             else wait_transfers<0>();
         }
         lds_barrier();
@@ -500,49 +486,24 @@ __device__ __forceinline__ void run_share(const LayerDesc &L, const StackParams 
             for (int i = 0; i < MR; ++i)
                 if (w + NW * i < M)
                     __hip_atomic_store(slot_of(worker, ga == 0 ? 1 : 0, w + NW * i), t[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (tail) {
-                tail_n = gb;
-            } else {
-                head_rb = rb;
-                head_n = gb - ga;
-                head_age = 0;
-            }
+            if (tail) tail_n = gb;
+            else head.stored(rb, gb - ga);
         }
     };
 
-    auto next_row_block = [&]() {
-        finish(seg_end - rb * G);
-        ++rb;
-        ga = 0;
-        seg_end = seg_end + G < u_end ? seg_end + G : u_end;
-    };
-    auto multiply = [&](const TileRegs<R, M> &t) {
-        tile_math<R, M, SL>(t, L, lane, xlds, yacc);
-        u += NW;
-        ++head_age;
-    };
-    // Whole rounds of the ring.  The loop has one way out, at its end: with one behind every tile the compiler joins those with the way back
-    // and has every round begin with a wait for all but the last loads (32 Llama-2-7B blocks, mixed widths, M = 1 526 us, 487 so, M = 5 634 / 584).
-    while (u + (NB - 1) * NW < u_end)
-        static_for<NB>([&](auto j) {
-            while (u >= seg_end) next_row_block();
-            prefetch(buf[(j + D) % NB]);
-            multiply(buf[j]);
-        });
-    if (has_tail && w == 0) others = __hip_atomic_load(cnt + tail_rb + own_register(0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    while (u < u_end) {  // the last tiles, D at most, are on their way
-        while (u >= seg_end) next_row_block();
-        multiply(buf[0]);
-        static_for<NB - 1>([&](auto j) { buf[j] = buf[j + 1]; });
-    }
-    while (seg_end < u_end) next_row_block();
-    finish(seg_end - rb * G);
-    if (head_n == 0 && tail_n == 0) return;
-    if (tail_n != 0 || !head_counted) {
+    walk.run<D, NW>(
+        w, head, [&](auto slot, int u, int g) { load_tile<R, M>(buf[slot], L, u, g, lane); },
+        [&](auto slot) { tile_math<R, M, SL>(buf[slot], L, lane, xlds, yacc); }, finish,
+        [&]() {
+            if (has_tail && w == 0) others = __hip_atomic_load(cnt + tail_rb + own_register(0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        },
+        [&]() { static_for<NB - 1>([&](auto j) { buf[j] = buf[j + 1]; }); });
+    if (head.n == 0 && tail_n == 0) return;
+    if (tail_n != 0 || !head.counted) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         wait_transfers<0>();
         lds_barrier();
-        if (head_n != 0 && !head_counted) count_head();
+        if (head.to_count()) count_head();
         if (tail_n != 0 && w == 0 && lane == 0)
             flags[1] = __hip_atomic_fetch_add(cnt + tail_rb, tail_n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + tail_n == G;
     }
@@ -558,7 +519,7 @@ __device__ __forceinline__ void run_share(const LayerDesc &L, const StackParams 
             if (w + NW * i < M) store_row(b, w + NW * i, tot[i]);
         if (w == 0 && lane == 0) __hip_atomic_store(cnt + b, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
-    if (head_n != 0 && __builtin_amdgcn_readfirstlane(flags[0])) complete(head_rb);
+    if (head.n != 0 && __builtin_amdgcn_readfirstlane(flags[0])) complete(head.rb);
     if (tail_n != 0 && __builtin_amdgcn_readfirstlane(flags[1])) complete(tail_rb);
 }
 
