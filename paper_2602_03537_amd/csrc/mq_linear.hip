@@ -225,14 +225,15 @@ __device__ __forceinline__ void tile_math_mfma(const TileRegs<R, M> &t, const La
 // for every two): afterwards dword t of the four holds rows 16 t .. 16 t + 15, and quarter h of the wave the columns of what was dword h.  All codes
 // come to one place of their half, so that one accumulator serves the tile, and the matrix core adds the activations up as well (times 1.0).
 // The place: this instruction adds its products after aligning them as if a subnormal weight began at 2^-14, so codes stand as high in the
-// mantissa as one mask or shift each allows (relative error of 8192 x 28672, r = 2, M = 16 against 64 bits with them at bit 0 2.44e-4, here 2.07e-4; by 32x32x16 instructions on subnormals, with
-// the activations scaled, it was 2.28e-4.  6 and 8 bits are as near at bit 0, which costs one instruction less).
+// mantissa as they can without an exponent (the two lowest widths lower by what one mask or shift allows).  Largest error of one group against 64 bits, units of 2^-24 of the magnitudes
+// added up, one activation 100 times the others, with the codes at bit 0 / here: r = 6 36.9 / 1.9, r = 8 9.6 / 2.8 (4x4x4 instructions 1.9 and 6.9); relative error of 8192 x 28672,
+// r = 2, M = 16 2.44e-4 / 2.07e-4.  At bit 0 6 and 8 bits take an instruction less per pair: 4096 x 4096 r = 6 M = 8 9.1 us, here 9.2; 11008 x 4096 r = 8 M = 16 18.6 / 19.2.
 //   The activations turn from rows to columns in the wave's own LDS (4 or 8 transfers of 1 KB a tile); no wave waits for another.  A tile is
 // 20 matrix and about 200 vector instructions at every width, and the memory bounds it.  us, what this took the place of (4x4x4 instructions, which read all
 // activations from LDS for every four rows of x, or a kernel with an activation launch of its own and a barrier a tile) / now, r = 4: 28672 x 8192 M = 8 30.4 /
 // 25.7, M = 16 41.3 / 28.9; 8192 x 28672 M = 16 38.9 / 27.8; 4096 x 4096 M = 16 12.1 / 8.9; r = 8 28672 x 8192 M = 16 61.4 / 42.4; mixed stacks of four
 // Llama-3-70B blocks M = 8 372 / 323, M = 16 393 / 375, 32 Llama-2-7B blocks M = 8 659 / 603.
-template <int R> constexpr int kCodeBit = R == 2 ? 8 : R == 3 ? 6 : R == 4 ? 4 : 0;
+template <int R> constexpr int kCodeBit = R == 2 ? 8 : R == 3 ? 6 : R == 8 ? 2 : 4;
 template <int R, bool XB, int M>
 __device__ __forceinline__ void tile_math_cols(const TileRegs<R, M> &t, int lane, uint32_t *xlds, float (&yacc)[kAcc<M>]) {
     using T = Layout<R>;
