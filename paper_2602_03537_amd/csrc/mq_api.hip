@@ -170,7 +170,7 @@ struct PlanHeader {
     int32_t n_layers, M, max_cost, n_jobs;
     uint64_t table_off, cnt_off, part_off, total_bytes;
     int32_t from_parent, path_M;
-    int32_t rows;                 // the row kernels serve it
+    int32_t rows;                 // 0 the wide kernel serves it; row kernels: 1 shares of workgroups, 2 of waves (persistent launch)
     int32_t ll_blocks, ll_waves;  // low-latency launch shape of a small stack, or 0
     int32_t any_x_bf16;           // some layer takes bf16 activations (launches of row kernels convert them first)
     int32_t ll_ks_cap;            // low-latency launch shape: most K slices per row block
@@ -269,6 +269,7 @@ mq_status run_single(const mq_layer &l, int64_t M, void *ws, size_t ws_bytes, mq
     p.n_layers = 1;
     const _Float16 *sym_line = nullptr;
     if (!l.zeros_t && !(sym_line = sym_zero_line())) return MQ_ERR_HIP;
+    p.by_wave = rows && wave_shares_single(l.from_parent ? kC : l.r, M);
     p.single = make_desc(l, M, M, rows, 0, 0, 0, act, sym_line);
     p.cost_total = (uint64_t)p.single.CB * p.single.RB * p.single.G * p.single.cost;
     p.cnt = reinterpret_cast<int32_t *>(base);
@@ -546,6 +547,9 @@ mq_status mq_stack_plan(const mq_layer *layers, int n_layers, int64_t M, void *p
 
     const PlanLayout pl = plan_layout(layers, n_layers, Mp);
     const bool rows = M <= kRowMaxM;
+    const bool by_wave = rows && wave_shares(n_layers, M, [&](int i) {
+        return RowLayer{(int)(pad_rows(layers[i].N) / kRowBlock), (int)(layers[i].K / kGroup), layers[i].from_parent ? kC : layers[i].r};
+    });
     char *base_dev = static_cast<char *>(plan_ws);
     int64_t counters = 0, jobs = 0;
     uint64_t cost = 0;
@@ -579,7 +583,7 @@ mq_status mq_stack_plan(const mq_layer *layers, int n_layers, int64_t M, void *p
     h.total_bytes = pl.total;
     h.from_parent = layers[0].from_parent;
     h.path_M = (int32_t)Mp;
-    h.rows = rows;
+    h.rows = rows ? by_wave ? 2 : 1 : 0;
     {
         int nb = 0, nw = 0, kc = 0;
         bool all_resident = false;
@@ -639,6 +643,7 @@ mq_status mq_linear_stack(const mq_plan *plan, mq_stream stream) {
     p.slot_floats = h.rows ? 64 * vector_rows(h.M) : slot_floats(h.path_M);
     if (more_rows(h.path_M) && h.rows) p.worker_cap = slots_in(partial_bytes(h.path_M), h.M);
     p.n_jobs = h.n_jobs;
+    p.by_wave = h.rows == 2;
     p.ks_cap = h.ll_ks_cap;
     std::memcpy(p.ll_start, h.ll_start, sizeof(p.ll_start));
     p.chain_total = h.chain_total;

@@ -16,13 +16,13 @@ namespace mq {
 // Caps on the wavefronts / workgroups of a persistent launch.  They size the partial-sum slots of a workspace, which
 // must be plain host arithmetic (callable without a device); every launcher asks the device for its compute units
 // and the kernel's occupancy and launches min(what is resident there, the cap), so a smaller or larger part stays
-// correct and only loses the slots it cannot use.  (8192 = 256 compute units x 32 waves, the MI355X.)
+// correct and only loses the slots it cannot use.  (8192 = 256 compute units x 32 waves, the MI355X; shares of workgroups use an eighth and less of them.)
 constexpr int kMaxWaves = 8192;
 // 5 .. 16 rows: what a workspace holds (callers see its size, which has room to spare): pairs of partial-sum slots, floats in one, and bytes
 // for the activations of a group
 constexpr int kMidSlots = 256, kMidSlotFloats = 8 * 64 * 16, kMidXBytes = 6 * 1024;
-// Persistent row kernel: each wave serves several interleaved shares of the schedule, so that
-// layers of different widths (different speed per byte) even out over the waves.
+// Persistent row kernels: each wave or workgroup serves up to so many interleaved shares of the schedule, so that
+// layers of different widths (different speed per byte) even out.
 constexpr int kSharesPerWave = 8;
 constexpr size_t kMaxSlotBytes = (size_t)32 << 20;
 inline int max_workers_valu(int64_t M) {
@@ -71,8 +71,8 @@ static_assert(sizeof(SmallTable) <= 2048, "kernel arguments are limited to 4 KiB
 struct StackParams {
     const LayerDesc *table;  // device table, or nullptr to use `single`
     int32_t n_layers;
-    int32_t nwaves;          // row kernels: workgroups launched
-    int32_t nworkers;        // schedule shares ("workers"); workgroup w serves workers w, w + nwaves, ...
+    int32_t nwaves;          // row kernels: workgroups launched (by_wave: waves)
+    int32_t nworkers;        // schedule shares ("workers"); workgroup or wave w serves workers w, w + nwaves, ...
     uint64_t cost_total;
     float *part;             // [nworkers][2][slot_floats] partial sums
     int32_t *cnt;            // row-block counters, zero between launches
@@ -80,6 +80,7 @@ struct StackParams {
     int32_t slot_floats;     // wide: floats per partial-sum slot (4 x chunks x 32*64)
     int32_t n_jobs;          // wide: jobs of the prep kernel
     int32_t finish_apart;    // wide, single layers: row blocks that several shares worked on are finished by a launch of its own
+    int32_t by_wave;         // row kernels: shares of the persistent schedule belong to waves (wave_shares), else to workgroups
     int32_t worker_cap;      // 0, or: `part` holds slots for this many schedule shares only (a small workspace)
     int32_t ks_cap;          // low-latency launch of a small stack: most K slices per row block (0: as one layer would choose)
     int32_t ll_start[16];    // ... and the first workgroup of each layer (a workgroup finds its layer without reading the table)

@@ -388,6 +388,139 @@ template <int R, int M> struct PrefetchDepth {
     static constexpr int value = M > 4 ? (R <= 4 ? 2 : 1) : R <= 2 ? 4 : R == 3 ? 3 : R <= 6 ? 2 : 1;
 };
 
+// End of a wave's run inside a row block: groups [ga, gb) are in acc[NV] (per lane).
+// Complete row block -> final(acc).  Otherwise publish the partial sums; the last
+// contributor sums all slots in wave order and calls final(total).
+//   cnt     : the row block's counter
+//   a       : cost position of the row block's first tile
+// Partial sums travel through agent-scope atomic stores/loads (write-through, cache
+// bypassing), so no whole-L2 write-back or invalidate is needed to publish them.
+template <int NV, class Final>
+__device__ __forceinline__ void finish_row_block(const LayerDesc &L, const StackParams &p, int32_t *cnt, uint64_t a,
+                                                 int ga, int gb, float (&acc)[NV], int worker, int lane, Final &&final) {
+    if (ga == 0 && gb == L.G) {
+        final(acc);
+        return;
+    }
+    const int slot = ga == 0 ? 1 : 0;  // the wave holding a row block's first tile uses slot 1
+    const size_t slot_floats = (size_t)p.slot_floats;
+    float MQ_GLOBAL *mine = gl(p.part + (size_t)(worker * 2 + slot) * slot_floats + lane);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) __hip_atomic_store(mine + v * 64, acc[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // the write-through stores must have been acknowledged before the counter moves
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    int old = 0;
+    if (lane == 0) old = __hip_atomic_fetch_add(gl(cnt), gb - ga, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    old = __builtin_amdgcn_readfirstlane(old);
+    if (old + (gb - ga) != L.G) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    const int w_lo = wave_of(a, p.nworkers, p.cost_total);
+    const int w_hi = wave_of(a + (uint64_t)(L.G - 1) * L.cost, p.nworkers, p.cost_total);
+    // Fixed summation order (w_lo's slot 1, then slot 0 of w_lo+1 .. w_hi); loads are issued
+    // in batches so that their round trips overlap.
+    constexpr int kBatch = NV >= 8 ? 8 : 16;  // slots fetched per round trip (NV * kBatch registers)
+    float tot[NV];
+    const float MQ_GLOBAL *first = gl(p.part + (size_t)(w_lo * 2 + 1) * slot_floats + lane);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) tot[v] = __hip_atomic_load(first + v * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int w0 = w_lo + 1; w0 <= w_hi; w0 += kBatch) {
+        float t[kBatch][NV];
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+            const int w = w0 + j <= w_hi ? w0 + j : w_hi;
+            const float MQ_GLOBAL *src = gl(p.part + (size_t)(w * 2) * slot_floats + lane);
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+                t[j][v] = __hip_atomic_load(src + v * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j)
+            if (w0 + j <= w_hi) {
+#pragma unroll
+                for (int v = 0; v < NV; ++v) tot[v] += t[j][v];
+            }
+    }
+    final(tot);
+    if (lane == 0) __hip_atomic_store(gl(cnt), 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Tiles [u_begin, u_end) of one layer, owned by share `wave`.
+template <int R, int M, bool SL = false>
+__device__ __forceinline__ void run_units(const LayerDesc &L, const StackParams &p, int u_begin, int u_end, int wave,
+                                          int lane, uint32_t *xlds) {
+    constexpr int D = PrefetchDepth<R, M>::value, NB = D + 1;
+    int rb = u_begin / L.G;
+    int g = u_begin - rb * L.G;
+    int ga = g;
+    float yacc[kAcc<M>];
+#pragma unroll
+    for (int i = 0; i < kAcc<M>; ++i) yacc[i] = 0.f;
+
+    // ring of NB tile buffers with compile-time indices (no register copies, which would wait
+    // for the loads); past the end of the run the last tile is fetched again instead of
+    // branching around the loads
+    TileRegs<R, M> buf[NB];
+    int u_pf = u_begin, g_pf = g;
+    auto prefetch = [&](TileRegs<R, M> &t) {
+        load_tile<R, M>(t, L, u_pf, g_pf, lane);
+        if (u_pf + 1 < u_end) {
+            ++u_pf;
+            g_pf = g_pf + 1 == L.G ? 0 : g_pf + 1;
+        }
+    };
+    static_for<D>([&](auto j) { prefetch(buf[j]); });
+    int u = u_begin;
+    while (u < u_end) {
+        static_for<NB>([&](auto j) {
+            if (u >= u_end) return;
+            prefetch(buf[(j + D) % NB]);
+            tile_math<R, M, SL>(buf[j], L, lane, xlds, yacc);
+            ++g;
+            ++u;
+            if (g == L.G || u == u_end) {
+                const int row = rb * kRowBlock + lane;
+                float rows[M];
+                rows_of<M>(yacc, xlds, lane, rows);
+                finish_row_block<M>(L, p, p.cnt + L.cnt_off + rb, L.cost_start + (uint64_t)rb * L.G * L.cost, ga, g,
+                                    rows, wave, lane, [&](const float(&tot)[M]) {
+#pragma unroll
+                                        for (int m = 0; m < M; ++m)
+                                            if (row < L.N && m < row_count<M>(L)) store_y(L.y, (size_t)m * L.N + row, tot[m], L.flags);
+                                    });
+                ++rb;
+                g = 0;
+                ga = 0;
+#pragma unroll
+                for (int i = 0; i < kAcc<M>; ++i) yacc[i] = 0.f;
+            }
+        });
+    }
+}
+
+template <int M, bool SL = false> __global__ __launch_bounds__(256, M > 4 ? 2 : 1) void stack_wave_kernel(const StackParams p) {
+    __shared__ __attribute__((aligned(16))) uint32_t xlds_all[4 * M * kRowDwords<M>];
+    uint32_t *xlds = xlds_all + (threadIdx.x >> 6) * M * kRowDwords<M>;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6));
+    if (wave >= p.nwaves) return;
+    for (int worker = wave; worker < p.nworkers; worker += p.nwaves) {
+        walk_tiles(p, worker, [&](const LayerDesc &L, int u_begin, int u_end) {
+            if constexpr (SL) {
+                run_units<8, M, true>(L, p, u_begin, u_end, worker, lane, xlds);
+            } else {
+                switch (L.r) {
+                    case 2: run_units<2, M>(L, p, u_begin, u_end, worker, lane, xlds); break;
+                    case 3: run_units<3, M>(L, p, u_begin, u_end, worker, lane, xlds); break;
+                    case 4: run_units<4, M>(L, p, u_begin, u_end, worker, lane, xlds); break;
+                    case 6: run_units<6, M>(L, p, u_begin, u_end, worker, lane, xlds); break;
+                    default: run_units<8, M>(L, p, u_begin, u_end, worker, lane, xlds); break;
+                }
+            }
+        });
+    }
+}
+
 // A share of the persistent schedule belongs to a workgroup: its waves take the groups of a row block in turn and add their sums up through
 // LDS where the row block ends, so that what a share hands over to others is one set of sums for each of its two ends.  (A share per wave handed over eight
 // times as much: 28672 x 8192, r = 4, M = 16 37.3 us, 33.1 so, M = 4 26.9 / 25.3.)
@@ -928,8 +1061,48 @@ template <int M, bool SL> static hipError_t launch_stack_mx(StackParams p, int m
     p.nworkers = (int)(spw * (uint64_t)p.nwaves);
     return launch((stack_kernel<M, SL>), dim3((unsigned)p.nwaves), dim3(64 * kWgWaves), 0, s, p);
 }
-template <int M> static hipError_t launch_stack_m(StackParams p, int max_cost, bool from_parent, hipStream_t s) {
-    return from_parent ? launch_stack_mx<M, true>(p, max_cost, s) : launch_stack_mx<M, false>(p, max_cost, s);
+// waves of the persistent launch by waves that the device keeps resident, in workgroups of four
+template <int M, bool SL> static int wave_resident() {
+    static int cached = 0;
+    if (!cached) {
+        int dev = 0, cus = 0, b = 0;
+        if (hipGetDevice(&dev) != hipSuccess) return 0;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, (stack_wave_kernel<M, SL>), 256, 0) != hipSuccess) return 0;
+        const int waves = cus * (b < 1 ? 1 : b) * 4;
+        cached = waves < kMaxWaves ? waves : kMaxWaves;
+    }
+    return cached;
+}
+
+template <int M, bool SL> static hipError_t launch_stack_waves(StackParams p, int max_cost, hipStream_t s) {
+    const int hw = wave_resident<M, SL>();
+    if (!hw) return hipErrorUnknown;
+    const uint64_t most = (uint64_t)(p.worker_cap ? p.worker_cap : max_workers_valu(M));
+    uint64_t cap = p.cost_total / (uint64_t)max_cost;  // (as below)
+    if (cap > most) cap = most;
+    if (cap < 1) cap = 1;
+    p.nwaves = (int)(cap < (uint64_t)hw ? cap : (uint64_t)hw);
+    // A single big layer is over in 25-50 us: with every resident wave a share is only a few tiles
+    // long and each row block is handed over many times.  2048 waves still saturate HBM for that
+    // long (each keeps its 8 KB in flight) and take 10-25 % off the call (measured on the Llama-3-70B MLP shapes).
+    if (!p.table && p.nwaves > 2048) p.nwaves = 2048;
+    // Several interleaved shares per wave even out layers of different width (a wave serves
+    // shares w, w + nwaves, ...), but every share ends with up to two hand-overs of a few
+    // microseconds, so shares stay at least ~128 tiles long (measured: Llama-2-7B stacks are
+    // best with one share per wave, Llama-3-70B stacks gain 15 % from eight).
+    uint64_t spw = p.cost_total / ((uint64_t)max_cost * 128 * (uint64_t)p.nwaves);  // whole shares per wave
+    if (spw > (uint64_t)kSharesPerWave) spw = kSharesPerWave;
+    while (spw > 1 && spw * (uint64_t)p.nwaves > most) --spw;
+    if (spw < 1) spw = 1;
+    p.nworkers = (int)(spw * (uint64_t)p.nwaves);
+    return launch((stack_wave_kernel<M, SL>), dim3((unsigned)((p.nwaves + 3) / 4)), dim3(256), 0, s, p);
+}
+template <int M, bool SL> static hipError_t launch_stack_x(const StackParams &p, int max_cost, hipStream_t s) {
+    return p.by_wave ? launch_stack_waves<M, SL>(p, max_cost, s) : launch_stack_mx<M, SL>(p, max_cost, s);
+}
+template <int M> static hipError_t launch_stack_m(const StackParams &p, int max_cost, bool from_parent, hipStream_t s) {
+    return from_parent ? launch_stack_x<M, true>(p, max_cost, s) : launch_stack_x<M, false>(p, max_cost, s);
 }
 
 hipError_t launch_stack(StackParams p, int max_cost, bool from_parent, hipStream_t s) {
@@ -940,7 +1113,7 @@ hipError_t launch_stack(StackParams p, int max_cost, bool from_parent, hipStream
         case 4: return launch_stack_m<4>(p, max_cost, from_parent, s);
         default:
             if (p.M > 16 || from_parent) return hipErrorInvalidValue;
-            return p.M <= 8 ? launch_stack_mx<8, false>(p, max_cost, s) : launch_stack_mx<16, false>(p, max_cost, s);
+            return p.M <= 8 ? launch_stack_x<8, false>(p, max_cost, s) : launch_stack_mx<16, false>(p, max_cost, s);
     }
 }
 

@@ -8,18 +8,24 @@ from paper_2602_03537_amd import synth
 
 pytestmark = pytest.mark.gpu
 
-# 17 layers are more than a low-latency launch takes: (rows, columns) of one, and 16 small ones
+# 17 layers are more than a low-latency launch takes: (rows, columns) of one, 15 small ones, and one of 8 bits that is most of the work, so that shares belong
+# to workgroups (tests/test_persistent_shares.py)
 LONG, MANY, SMALL, WHOLE = (130, 28672), (4100, 640), (65, 128), (64 * 40, 3200)
+
+
+def stack_of(shape, M):
+    shapes = [shape] + [(64 * (1 + i % 3), 128 * (1 + i % 2)) for i in range(15)] + [(700, 14336)]
+    return shapes, [WIDTHS[(i + M) % 5] for i in range(16)] + [8]
 
 
 @pytest.mark.parametrize("shape", [LONG, MANY, SMALL, WHOLE], ids=["cut", "few_groups", "short", "about_whole"])
 @pytest.mark.parametrize("M", (1, 2, 4, 5, 8, 9, 16))
 def test_shares(M, shape):
-    shapes = [shape] + [(64 * (1 + i % 3), 128 * (1 + i % 2)) for i in range(16)]
+    shapes, widths = stack_of(shape, M)
     host = [synth.make_layer(N, K, M=M, seed=[601, M, N, i]) for i, (N, K) in enumerate(shapes)]
     layers = []
     for i, L in enumerate(host):
-        lay = mq.prepare_layer(dev(L["parent"]), dev(L["scales"]), dev(L["zeros"]), WIDTHS[(i + M) % 5])
+        lay = mq.prepare_layer(dev(L["parent"]), dev(L["scales"]), dev(L["zeros"]), widths[i])
         x = torch.empty(M * lay["K"] + 2, dtype=torch.float16, device=DEV)[2:].view(M, lay["K"])  # 4 bytes past an aligned address
         x.copy_(dev(L["x"]))
         layers.append(dict(lay, x=x, y=torch.full((M, lay["N"]), float("nan"), dtype=torch.float16, device=DEV)))
