@@ -41,14 +41,18 @@ def test_shapes_hold_to_their_bounds(lib):
         RB, G, M, r = int(np.exp(rng.uniform(0, 9))), int(np.exp(rng.uniform(0, 6))), int(rng.integers(1, 17)), int(rng.choice([2, 3, 4, 6, 8]))
         lib.shape(RB, G, r, M, out)
         assert 1 <= out[0] <= 8 and (out[0] == 1 or G // out[0] >= 4)          # slots and groups of a slice
-        assert out[1] in ((4, 8, 16) if M <= 4 else (4,))                      # waves the kernels are built for
+        assert out[1] in ((4, 8, 16) if M <= 4 else (4, 8) if M <= 8 else (4,))  # waves the kernels are built for
+        # 5 .. 8 rows: a compute unit holds all workgroups of a shape that is cut for it (registers: four waves a SIMD up to 4 bits, three beyond)
+        if 4 < M <= 8 and RB <= 256 and out[0] > 1:
+            assert -(-RB * out[0] // 256) * out[1] <= (16 if r <= 4 else 12), (RB, G, r, M, list(out))
 
 
 # row blocks, groups, r, M: K slices and waves measured faster than the slices of pick_k_slices (us: those / these)
 @pytest.mark.parametrize("RB,G,r,M,shape", [
     (204, 40, 6, 3, (1, 16)), (157, 64, 4, 2, (3, 8)), (157, 64, 4, 1, (3, 16)), (204, 64, 4, 4, (1, 16)), (448, 16, 4, 2, (1, 8)), (64, 32, 4, 8, (4, 4)),
-    (172, 32, 4, 8, (4, 4)), (64, 32, 4, 1, (4, 8)), (392, 13, 3, 1, (1, 16))],
-    ids=["16.9/12.2", "14.9/11.7", "12.6/10.5", "17.4/14.8", "9.4/8.4", "8.3/7.6", "11.4/9.9", "kept_a", "kept_b"])
+    (172, 32, 4, 8, (4, 4)), (64, 32, 4, 1, (4, 8)), (392, 13, 3, 1, (1, 16)), (37, 54, 4, 1, (7, 8)), (133, 27, 8, 1, (1, 16)), (133, 27, 8, 3, (1, 16)),
+    (13, 195, 6, 6, (8, 8)), (11, 206, 4, 5, (8, 8)), (16, 139, 6, 7, (8, 8))],
+    ids=["16.9/12.2", "14.9/11.7", "12.6/10.5", "17.4/14.8", "9.4/8.4", "8.3/7.6", "11.4/9.9", "kept_a", "kept_b", "7.0/6.7", "9.4/8.8", "10.0/9.7", "14.4/12.8", "13.4/11.6", "12.8/12.3"])
 def test_measured_shapes(lib, RB, G, r, M, shape):
     out = (ctypes.c_int * 2)()
     lib.shape(RB, G, r, M, out)
