@@ -19,7 +19,7 @@ STACKS = {
     "49_groups_192": [(64 * 190, 49), (100, 49)],
     "256_blocks": [(64 * 200, 5), (64 * 56, 16)],
     "40_groups_208": [(64 * 150, 40), (64 * 58, 7)],
-    "cut_in_2": [(64 * 32, 31), (64 * 32 - 5, 24)],
+    "cut_in_4_of_64": [(64 * 32, 31), (64 * 32 - 5, 24)],
     "cut_in_4": [(64 * 20, 32), (64 * 28, 48)],
     "cut_in_2_of_128": [(64 * 100, 33), (64 * 28, 64)],
     "257_blocks": [(64 * 200, 5), (64 * 57, 16)],

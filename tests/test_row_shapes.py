@@ -21,6 +21,11 @@ extern "C" void stack(int n, int RB, int G, int r, int M, int *out) {
     out[0] = s.ks_cap;
     out[1] = s.waves;
 }
+extern "C" void uneven(int n, const int *RB, int G, const int *r, int M, int *out) {
+    const RowStackShape s = row_stack_shape(n, M, false, [&](int i) { return RowLayer{RB[i], G, r[i]}; }, [](int waves) { return waves > 8 ? 256 : 512; });
+    out[0] = s.ks_cap;
+    out[1] = s.waves;
+}
 extern "C" int low_latency(int64_t RB, int64_t G, int r, int64_t M) { return low_latency_call(RB, G, r, M, (size_t)1 << 24); }
 """
 
@@ -80,3 +85,24 @@ def test_measured_stack_shapes(lib, n, RB, G, r, M, shape):
     out = (ctypes.c_int * 2)()
     lib.stack(n, RB, G, r, M, out)
     assert (out[0], out[1]) == shape if shape else out[0] != 1
+
+
+# row blocks, groups, widths, M: most slices (times in the ids, cut as each layer would be alone / in two / in four)
+@pytest.mark.parametrize("RB,G,r,M,cap", [
+    ((52, 21, 21), 26, (4, 3, 8), 1, 4), ((60, 15, 15), 30, (4, 6, 3), 1, 4), ((62, 3, 3), 31, (2, 4, 8), 4, 4), ((56, 4, 4), 28, (2, 2, 6), 1, 4),
+    ((60, 4, 4), 30, (2, 4, 6), 4, 4), ((88, 15, 15), 44, (8, 4, 4), 4, 2)],
+    ids=["1/1.11/0.99", "1/1.11/0.99", "1/1.06/0.96", "1/1.05/0.92", "1/1.08/0.97", "1/0.84/0.94"])
+def test_stacks_of_uneven_layers(lib, RB, G, r, M, cap):
+    out = (ctypes.c_int * 2)()
+    ints = ctypes.c_int * 3
+    lib.uneven(3, ints(*RB), G, ints(*r), M, out)
+    assert out[0] == cap
+
+
+def test_six_bits_stay_cut_up_to_160_row_blocks(lib):
+    out = (ctypes.c_int * 2)()
+    ints = ctypes.c_int * 3
+    lib.uneven(3, ints(54, 48, 48), 27, ints(4, 2, 6), 4, out)      # cut / uncut 1 / 1.06
+    assert out[0] != 1
+    lib.uneven(3, ints(54, 53, 53), 27, ints(4, 2, 6), 4, out)
+    assert out[0] == 1
