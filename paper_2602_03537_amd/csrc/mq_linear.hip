@@ -419,7 +419,7 @@ __device__ __forceinline__ void finish_row_block(const LayerDesc &L, const Stack
     const int w_hi = wave_of(a + (uint64_t)(L.G - 1) * L.cost, p.nworkers, p.cost_total);
     // Fixed summation order (w_lo's slot 1, then slot 0 of w_lo+1 .. w_hi); loads are issued
     // in batches so that their round trips overlap.
-    constexpr int kBatch = NV >= 8 ? 8 : 16;  // slots fetched per round trip (NV * kBatch registers)
+    constexpr int kBatch = NV >= 16 ? 4 : NV >= 8 ? 8 : 16;  // slots fetched per round trip (NV * kBatch registers)
     float tot[NV];
     const float MQ_GLOBAL *first = gl(p.part + (size_t)(w_lo * 2 + 1) * slot_floats + lane);
 #pragma unroll
@@ -1113,7 +1113,7 @@ hipError_t launch_stack(StackParams p, int max_cost, bool from_parent, hipStream
         case 4: return launch_stack_m<4>(p, max_cost, from_parent, s);
         default:
             if (p.M > 16 || from_parent) return hipErrorInvalidValue;
-            return p.M <= 8 ? launch_stack_x<8, false>(p, max_cost, s) : launch_stack_mx<16, false>(p, max_cost, s);
+            return p.M <= 8 ? launch_stack_x<8, false>(p, max_cost, s) : launch_stack_x<16, false>(p, max_cost, s);
     }
 }
 

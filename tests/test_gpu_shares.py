@@ -14,7 +14,7 @@ LONG, MANY, SMALL, WHOLE = (130, 28672), (4100, 640), (65, 128), (64 * 40, 3200)
 
 
 def stack_of(shape, M):
-    shapes = [shape] + [(64 * (1 + i % 3), 128 * (1 + i % 2)) for i in range(15)] + [(700, 14336)]
+    shapes = [shape] + [(64 * (1 + i % 3), 128 * (1 + i % 2)) for i in range(15)] + [(1400, 14336)]
     return shapes, [WIDTHS[(i + M) % 5] for i in range(16)] + [8]
 
 

@@ -1,4 +1,4 @@
-"""The persistent launch whose shares belong to waves (up to 8 rows): row blocks cut into many shares, whole ones, one group a row block, shares of one tile, layers computed from
+"""The persistent launch whose shares belong to waves: row blocks cut into many shares, whole ones, one group a row block, shares of one tile, layers computed from
 their parent, single layers, and a small workspace.  tests/test_persistent_shares.py holds that these calls take it."""
 import numpy as np
 import pytest
@@ -20,11 +20,10 @@ def _shapes(name):
     return [STACKS[name][0]] + [(64 * (1 + i % 3), 128 * (1 + i % 2)) for i in range(16)]
 
 
-@pytest.mark.parametrize("name", STACKS)
-@pytest.mark.parametrize("M,parent", [(1, 0), (2, 0), (3, 0), (4, 0), (5, 0), (8, 0), (1, 1), (2, 1), (3, 1), (4, 1)])
+# (from the parent all tiles are of 8 bits: the stacks of few groups a row block)
+@pytest.mark.parametrize("M,parent,name", [(M, 0, name) for M in (1, 2, 3, 4, 5, 8, 9, 16) for name in STACKS] +
+                         [(M, 1, name) for M in (1, 2, 3, 4) for name in ("few_groups", "one_group", "short", "eight_groups")])
 def test_shares_of_waves(M, parent, name):
-    if parent and name not in ("few_groups", "one_group", "short", "eight_groups"):
-        pytest.skip("workgroups' shares: the tiles are the parent's")
     widths = STACKS[name][1]
     host = [synth.make_layer(N, K, M=M, seed=[611, M, N, i]) for i, (N, K) in enumerate(_shapes(name))]
     layers = []

@@ -47,7 +47,12 @@ def _block(hidden, kv, ffn):
     ((8192, 1024, 28672), 4, (2,), 1, 191.5, 162.3), ((8192, 1024, 28672), 4, (3,), 1, 224.7, 215.3), ((8192, 1024, 28672), 4, (4,), 1, 268.9, 273.8),
     ((2048, 512, 5632), 22, (2,), 1, 74.7, 58.3), ((2048, 512, 5632), 22, (3,), 1, 91.6, 72.9), ((2048, 512, 5632), 22, (8,), 1, 157.2, 161.2),
     ((4096, 4096, 11008), 32, (2,), 2, 379.0, 322.0), ((4096, 4096, 11008), 32, (4,), 3, 535.3, 572.0), ((4096, 4096, 11008), 32, (2,), 4, 408.3, 372.1),
-    ((1280, 1152, 4608), 26, (3, 4), 4, 78.6, 58.2), ((1280, 1152, 4608), 26, (3, 4), 8, 89.9, 59.0), ((4096, 4096, 11008), 32, (8,), 5, 1030.5, 1116.2)])
+    ((1280, 1152, 4608), 26, (3, 4), 4, 78.6, 58.2), ((1280, 1152, 4608), 26, (3, 4), 8, 89.9, 59.0), ((4096, 4096, 11008), 32, (8,), 5, 1030.5, 1116.2),
+    ((512, 256, 16512), 40, (4,), 16, 200.9, 155.2), ((6784, 1216, 1408), 10, (4,), 16, 186.8, 170.6), ((128, 3136, 13568), 40, (3,), 12, 165.7, 48.3),
+    ((128, 960, 10112), 40, (2, 8), 9, 155.2, 42.5), ((1280, 1152, 4608), 26, (3, 4), 16, 106.2, 86.0), ((2048, 512, 5632), 22, (2,), 16, 119.6, 100.0),
+    ((4096, 4096, 11008), 32, (2,), 16, 564.4, 511.0), ((4096, 4096, 11008), 32, (4,), 16, 732.7, 716.6), ((4096, 4096, 11008), 32, (8,), 16, 1139.3, 1148.0),
+    ((4096, 4096, 11008), 32, (2, 3, 4, 6, 8), 16, 809.9, 860.8), ((8192, 1024, 28672), 4, (3,), 16, 344.7, 335.1),
+    ((8192, 1024, 28672), 4, (2, 4, 8), 16, 412.3, 428.1), ((8192, 1024, 28672), 4, (8,), 16, 569.6, 586.4)])
 def test_stacks_take_the_faster_shares(lib, block, blocks, widths, M, workgroups, waves):
     shapes = _block(*block) * blocks
     assert _waves(lib, shapes, [widths[i % len(widths)] for i in range(len(shapes))], M) == (waves < workgroups)
@@ -58,14 +63,11 @@ def test_single_layers_take_the_faster_shares(lib, r, M, workgroups, waves):
     assert bool(lib.waves_single(r, ctypes.c_int64(M))) == (waves < workgroups)
 
 
-def test_nine_rows_and_more_have_shares_of_workgroups(lib):
-    assert not any(_waves(lib, _block(1024, 512, 2048) * 9, [2] * 63, M) for M in (9, 16))
-
-
 def test_calls_by_which_the_gpu_tests_reach_shares_of_waves(lib):
     for name, (_, widths) in STACKS.items():
         shapes = _shapes(name)
-        assert _waves(lib, shapes, [widths[i % len(widths)] for i in range(17)], 8), name
+        for M in (1, 2, 3, 4, 5, 8, 9, 16):
+            assert _waves(lib, shapes, [widths[i % len(widths)] for i in range(17)], M), (name, M)
         if name in ("few_groups", "one_group", "short", "eight_groups"):
             assert _waves(lib, shapes, [8] * 17, 4), name
     for N, K in SINGLES:
@@ -75,5 +77,5 @@ def test_calls_by_which_the_gpu_tests_reach_shares_of_waves(lib):
 
 def test_calls_by_which_the_gpu_tests_reach_shares_of_workgroups(lib):
     for shape in (LONG, MANY, SMALL, WHOLE):
-        for M in (1, 2, 4, 5, 8):
+        for M in (1, 2, 4, 5, 8, 9, 16):
             assert not _waves(lib, *stack_of(shape, M), M), (shape, M)
