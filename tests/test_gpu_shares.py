@@ -1,5 +1,7 @@
 """The persistent launch of the row kernels, whose shares belong to workgroups: row blocks cut into many shares, whole ones, shares shorter than a
 workgroup has waves, few groups a row block; from 5 rows on with activations at any address of a pair."""
+import functools
+
 import pytest
 
 import paper_2602_03537_amd as mq
@@ -8,21 +10,26 @@ from paper_2602_03537_amd import synth
 
 pytestmark = pytest.mark.gpu
 
-# 17 layers are more than a low-latency launch takes: (rows, columns) of one, 15 small ones, and one of 8 bits that is most of the work, so that shares belong
-# to workgroups (tests/test_persistent_shares.py)
-LONG, MANY, SMALL, WHOLE = (130, 28672), (4100, 640), (65, 128), (64 * 40, 3200)
+# 17 layers are more than a low-latency launch takes: (rows, columns) of one, 15 small ones, and one of 8 bits and 20 groups that has most row blocks and
+# most of the work, so that shares belong to workgroups (tests/test_persistent_shares.py)
+LONG, MANY, SMALL, WHOLE = (130, 28672), (1100, 640), (65, 128), (64 * 40, 3200)
 
 
 def stack_of(shape, M):
-    shapes = [shape] + [(64 * (1 + i % 3), 128 * (1 + i % 2)) for i in range(15)] + [(1400, 14336)]
+    shapes = [shape] + [(64, 128 * (1 + i % 2)) for i in range(15)] + [(12200, 2560)]
     return shapes, [WIDTHS[(i + M) % 5] for i in range(16)] + [8]
+
+
+@functools.lru_cache(maxsize=1)
+def _big():
+    return synth.make_layer(12200, 2560, M=16, seed=[603])
 
 
 @pytest.mark.parametrize("shape", [LONG, MANY, SMALL, WHOLE], ids=["cut", "few_groups", "short", "about_whole"])
 @pytest.mark.parametrize("M", (1, 2, 4, 5, 8, 9, 16))
 def test_shares(M, shape):
     shapes, widths = stack_of(shape, M)
-    host = [synth.make_layer(N, K, M=M, seed=[601, M, N, i]) for i, (N, K) in enumerate(shapes)]
+    host = [synth.make_layer(N, K, M=M, seed=[601, M, N, i]) for i, (N, K) in enumerate(shapes[:-1])] + [dict(_big(), x=_big()["x"][:M])]
     layers = []
     for i, L in enumerate(host):
         lay = mq.prepare_layer(dev(L["parent"]), dev(L["scales"]), dev(L["zeros"]), widths[i])

@@ -48,7 +48,7 @@ def _block(hidden, kv, ffn):
     ((2048, 512, 5632), 22, (2,), 1, 74.7, 58.3), ((2048, 512, 5632), 22, (3,), 1, 91.6, 72.9), ((2048, 512, 5632), 22, (8,), 1, 157.2, 161.2),
     ((4096, 4096, 11008), 32, (2,), 2, 379.0, 322.0), ((4096, 4096, 11008), 32, (4,), 3, 535.3, 572.0), ((4096, 4096, 11008), 32, (2,), 4, 408.3, 372.1),
     ((1280, 1152, 4608), 26, (3, 4), 4, 78.6, 58.2), ((1280, 1152, 4608), 26, (3, 4), 8, 89.9, 59.0), ((4096, 4096, 11008), 32, (8,), 5, 1030.5, 1116.2),
-    ((6016, 832, 1280), 14, (3, 4), 4, 161.5, 128.5), ((1408, 384, 7808), 15, (6,), 5, 103.1, 90.7), ((1664, 576, 1280), 40, (6,), 8, 102.5, 91.4),
+    ((8064, 2304, 1280), 9, (3, 4), 1, 170.4, 140.7), ((4096, 3840, 1152), 6, (2, 8), 9, 90.4, 78.4), ((6016, 832, 1280), 14, (3, 4), 4, 161.5, 128.5), ((1408, 384, 7808), 15, (6,), 5, 103.1, 90.7), ((1664, 576, 1280), 40, (6,), 8, 102.5, 91.4),
     ((512, 256, 16512), 40, (4,), 16, 200.9, 155.2), ((6784, 1216, 1408), 10, (4,), 16, 186.8, 170.6), ((128, 3136, 13568), 40, (3,), 12, 165.7, 48.3),
     ((128, 960, 10112), 40, (2, 8), 9, 155.2, 42.5), ((1280, 1152, 4608), 26, (3, 4), 16, 106.2, 86.0), ((2048, 512, 5632), 22, (2,), 16, 119.6, 100.0),
     ((4096, 4096, 11008), 32, (2,), 16, 564.4, 511.0), ((4096, 4096, 11008), 32, (4,), 16, 732.7, 716.6), ((4096, 4096, 11008), 32, (8,), 16, 1139.3, 1148.0),
