@@ -12,8 +12,8 @@ streams from HBM.
 
 Prints ONE JSON line: effective HBM GB/s over the step (algorithmic bytes:
 r/8 per weight + fp16 scale and zero per group + activations in and out), the
-per-r microseconds and GB/s, the roofline object of the dominant kernel
-(mq::stack_kernel<1, false>, HBM-bound) measured with events on the launch stream, and
+per-r microseconds and GB/s, the roofline object of the dominant kernels
+(mq::stack_kernel<1, false>, at 2 and 3 bits mq::stack_wave_kernel<1, false>; HBM-bound) measured with events on the launch stream, and
 the CPU oracle timed on the host cores on a bounded sample.
 """
 from __future__ import annotations
@@ -31,8 +31,8 @@ if ROOT not in sys.path:
 HBM_PEAK_GBPS = 8000.0
 WIDTHS = (2, 3, 4, 6, 8)
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "stack_kernel_llama2_7b_m1_hbm_traffic.txt")
-# the sources that define mq::stack_kernel<1, false>: a traffic figure is quoted only while they are the ones profiled
-KERNEL_SOURCES = ("mq_linear.hip", "mq_device.h", "mq_layout.h", "mq_internal.h", "mq_routes.h", "mq_static_for.h")
+# the sources that define the persistent launch of one row: a traffic figure is quoted only while they are the ones profiled
+KERNEL_SOURCES = ("mq_linear.hip", "mq_device.h", "mq_dma.h", "mq_share_walk.h", "mq_layout.h", "mq_internal.h", "mq_routes.h", "mq_static_for.h")
 
 
 def kernel_sources_sha() -> str:
@@ -204,12 +204,12 @@ def main() -> int:
                          "frac_of_8TBps": round(gbps / HBM_PEAK_GBPS, 4), "algorithmic_MB": round(stacks[r]["bytes"] / 1e6, 1)}
     value = step_bytes / (ms_per_step * 1e-3) / 1e9
 
-    # roofline of the dominant kernel (mq::stack_kernel<1, false>): algorithmic bytes per launch / mean launch duration
+    # roofline of the dominant kernels (shares of workgroups from 4 bits on, of waves below): algorithmic bytes per launch / mean launch duration
     launches = [u for r in WIDTHS for u in per_r_us[r]]
     avg_launch_us = float(np.mean(launches))
     bytes_per_launch = step_bytes / len(WIDTHS)
     achieved = bytes_per_launch / avg_launch_us / 1e3
-    roofline = {"bound": "hbm", "kernel": "mq::stack_kernel<1, false>", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS,
+    roofline = {"bound": "hbm", "kernel": "mq::stack_kernel<1, false> (r = 4, 6, 8), mq::stack_wave_kernel<1, false> (r = 2, 3)", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4),
                 "avg_launch_us": round(avg_launch_us, 1), "algorithmic_bytes_per_launch": int(bytes_per_launch)}
     traffic, traffic_src = traffic_from_profile() if args.layers == 32 else (None, "not the profiled workload")
@@ -431,6 +431,7 @@ def measure_mixed_stack(mq, synth, torch, np, dev, big, n_blocks, M, steps, warm
     torch.cuda.synchronize()
     ms = (time.perf_counter() - t0) * 1e3 / steps
     us = [evs[k].elapsed_time(evs[k + 1]) * 1e3 for k in range(steps)]
+    # (mixed widths of these blocks: shares of workgroups)
     kernel = "mq::stack_kernel<%d, false>" % (M if M <= 4 else 8 if M <= 8 else 16) if M <= 16 else "mq::wide_stack_kernel"
     return {"ms_wall": ms, "us": us, "bytes": nbytes, "mean_bits": mean, "n_linears": len(layers), "n_blocks": n_blocks,
             "kernel": kernel, "weights": weights}

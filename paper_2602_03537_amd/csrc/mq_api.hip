@@ -189,7 +189,7 @@ constexpr uint64_t kPlanMagic = 0x4d51504c414e3039ull;  // "MQPLAN09"
 // The array's name is only a host-side stand-in; its device address is looked up once per device (each device
 // holds its own copy at its own address) and only that pointer is ever handed to a kernel.
 constexpr size_t kScratchBytes = MQ_NOALLOC_SCRATCH_BYTES;
-constexpr size_t kNoallocMinWorkers = 256;  // fewer schedule shares (waves) than this would leave most of the chip idle
+constexpr size_t kNoallocMinWorkers = 256;  // fewer schedule shares (of waves or workgroups) than this would leave much of the chip idle
 constexpr size_t kNoallocMinMid = 32;       // the same from 5 rows on, where the workspace counts in kMidSlotFloats
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 std::mutex g_scratch_mutex;
@@ -262,7 +262,7 @@ mq_status run_single(const mq_layer &l, int64_t M, void *ws, size_t ws_bytes, mq
     const size_t part_b = worker_cap ? (size_t)worker_cap * 2 * (size_t)slot_floats(M) * sizeof(float) : partial_bytes(M);
     char *act = base + cnt_b + part_b;
     const int64_t row_blocks = pad_rows(l.N) / kRowBlock;
-    const bool rows = M <= kRowMaxM || row_kernels_single(row_blocks, l.K / kGroup, l.r, M, part_b);
+    const bool rows = row_kernels_single(row_blocks, l.K / kGroup, M, part_b);
     StackParams p{};
     p.worker_cap = more_rows(M) && rows ? slots_in(part_b, M) : worker_cap;
     p.table = nullptr;
@@ -546,7 +546,7 @@ mq_status mq_stack_plan(const mq_layer *layers, int n_layers, int64_t M, void *p
     if (plan_bytes < need) return MQ_ERR_BUF_TOO_SMALL;
 
     const PlanLayout pl = plan_layout(layers, n_layers, Mp);
-    const bool rows = M <= kRowMaxM;
+    const bool rows = row_kernels_stack(M);
     const bool by_wave = rows && wave_shares(n_layers, M, [&](int i) {
         return RowLayer{(int)(pad_rows(layers[i].N) / kRowBlock), (int)(layers[i].K / kGroup), layers[i].from_parent ? kC : layers[i].r};
     });

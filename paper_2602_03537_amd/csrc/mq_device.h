@@ -3,12 +3,12 @@
 //
 // Schedule.  A layer is CB x RB x G tiles (pass of the wide kernel, row block of 64 rows, or super row block,
 // group of 128 columns; CB = 1 for the row kernels).
-// Tiles of all layers form one line in "cost" space (cost ~ time of a tile); share ("worker") w of W, a workgroup's,
+// Tiles of all layers form one line in "cost" space (cost ~ time of a tile); share ("worker") w of W, a workgroup's or (wave_shares) a wave's,
 // owns the tiles whose start lies in [w*C/W, (w+1)*C/W): a
 // contiguous run, group index fastest, i.e. a contiguous piece of packed
-// memory, while the workgroup keeps fp32 running sums for its current row block.
+// memory, while the workgroup or wave keeps fp32 running sums for its current row block.
 //
-// Split-K.  When a run ends inside a row block its workgroup leaves its partial sums
+// Split-K.  When a run ends inside a row block its owner leaves the partial sums
 // in a slot of its own and adds the number of groups it covered to the row
 // block's counter; whoever brings the counter to G adds the slots up in share
 // order (so the result does not depend on timing), writes y and resets the

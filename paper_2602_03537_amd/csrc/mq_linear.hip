@@ -229,10 +229,11 @@ __device__ __forceinline__ void tile_math_mfma(const TileRegs<R, M> &t, const La
 // added up, one activation 100 times the others, with the codes at bit 0 / here: r = 6 36.9 / 1.9, r = 8 9.6 / 2.8 (4x4x4 instructions 1.9 and 6.9); relative error of 8192 x 28672,
 // r = 2, M = 16 2.44e-4 / 2.07e-4.  At bit 0 6 and 8 bits take an instruction less per pair: 4096 x 4096 r = 6 M = 8 9.1 us, here 9.2; 11008 x 4096 r = 8 M = 16 18.6 / 19.2.
 //   The activations turn from rows to columns in the wave's own LDS (4 or 8 transfers of 1 KB a tile); no wave waits for another.  A tile is
-// 20 matrix and about 200 vector instructions at every width, and the memory bounds it.  us, what this took the place of (4x4x4 instructions, which read all
-// activations from LDS for every four rows of x, or a kernel with an activation launch of its own and a barrier a tile) / now, r = 4: 28672 x 8192 M = 8 30.4 /
-// 25.7, M = 16 41.3 / 28.9; 8192 x 28672 M = 16 38.9 / 27.8; 4096 x 4096 M = 16 12.1 / 8.9; r = 8 28672 x 8192 M = 16 61.4 / 42.4; mixed stacks of four
-// Llama-3-70B blocks M = 8 372 / 323, M = 16 393 / 375, 32 Llama-2-7B blocks M = 8 659 / 603.
+// 20 matrix and 226 .. 319 vector instructions (counted, hand-overs included: r = 2, 3, 4, 6, 8, M = 16 256, 278, 260, 319, 297), the matrix pipe is busy 9 .. 24 % of the time; memory bounds it from 4 bits on,
+// instruction issue with two waves a SIMD below.  us, what this took the place of (4x4x4 instructions, which read all
+// activations from LDS for every four rows of x, or a kernel with an activation launch of its own and a barrier a tile) / now, r = 4: 28672 x 8192 M = 8 31.1 /
+// 27.1, M = 16 41.6 / 30.4; 8192 x 28672 M = 16 40.2 / 29.1; 4096 x 4096 M = 8 8.6 / 7.6, M = 16 12.1 / 8.9; r = 8 28672 x 8192 M = 16 61.8 / 44.2; mixed stacks, every layer its own x: four
+// Llama-3-70B blocks M = 8 356 / 325, M = 16 379 / 362, 32 Llama-2-7B blocks M = 8 647 / 633, M = 16 704 / 711.
 template <int R> constexpr int kCodeBit = R == 2 ? 8 : R == 3 ? 6 : R == 8 ? 2 : 4;
 template <int R, bool XB, int M>
 __device__ __forceinline__ void tile_math_cols(const TileRegs<R, M> &t, int lane, uint32_t *xlds, float (&yacc)[kAcc<M>]) {
@@ -395,7 +396,7 @@ __device__ __forceinline__ unsigned die_order() {
     return gridDim.x % 8 == 0 ? blockIdx.x % 8 * (gridDim.x / 8) + blockIdx.x / 8 : blockIdx.x;
 }
 
-// End of a wave's run inside a row block: groups [ga, gb) are in acc[NV] (per lane).
+// Shares of waves.  End of a run inside a row block: groups [ga, gb) are in acc[NV] (per lane).
 // Complete row block -> final(acc).  Otherwise publish the partial sums; the last
 // contributor sums all slots in wave order and calls final(total).
 //   cnt     : the row block's counter
@@ -505,6 +506,9 @@ __device__ __forceinline__ void run_units(const LayerDesc &L, const StackParams 
     }
 }
 
+// Shares of waves (wave_shares in mq_routes.h says for which stacks): no barrier and no sums of other waves at the end of a row block, and as many waves as registers allow
+// (143 registers and 12 waves a compute unit at one row, 244 and 8 at 16), for which every share hands its two ends over.  32 Llama-2-7B blocks, r = 2, one row 313 us (5.8 TB/s; 382 by shares of
+// workgroups), 40 blocks of 128 / 3136 / 13568, r = 3, M = 12 48 (166).  One row is bound by the vector ALUs at 2 bits, by memory from 4 bits on.
 template <int M, bool SL = false> __global__ __launch_bounds__(256, M > 4 ? 2 : 1) void stack_wave_kernel(const StackParams p) {
     __shared__ __attribute__((aligned(16))) uint32_t xlds_all[4 * M * kRowDwords<M>];
     uint32_t *xlds = xlds_all + (threadIdx.x >> 6) * M * kRowDwords<M>;
@@ -528,9 +532,9 @@ template <int M, bool SL = false> __global__ __launch_bounds__(256, M > 4 ? 2 : 
     }
 }
 
-// A share of the persistent schedule belongs to a workgroup: its waves take the groups of a row block in turn and add their sums up through
+// Shares of workgroups: the waves take the groups of a row block in turn and add their sums up through
 // LDS where the row block ends, so that what a share hands over to others is one set of sums for each of its two ends.  (A share per wave handed over eight
-// times as much: 28672 x 8192, r = 4, M = 16 37.3 us, 33.1 so, M = 4 26.9 / 25.3.)
+// times as much: 28672 x 8192, r = 4, M = 16 37.3 us, 33.1 so, M = 4 26.9 / 25.3, before what follows and the launch's order.)
 //   The first of them (the end of a row block that earlier shares began) is stored as soon as it is known and counted when the next
 // row block ends.  The last one is kept in registers: the counter, read while the last tiles are multiplied, shows as a rule that all others
 // have been counted, and then the share adds their sums to its own and is done.  Otherwise it stores and counts its own, too, and
@@ -1037,8 +1041,8 @@ hipError_t launch_linear_rb_stack(const StackParams &p, const SmallTable &t, int
     }
 }
 
-// workgroups of the persistent launch that the device keeps resident
-template <int M, bool SL> static int stack_resident() {
+// workgroups of the persistent launch: one per compute unit
+static int stack_workgroups() {
     static int cached = 0;
     if (!cached) {
         int dev = 0, cus = 0;
@@ -1050,7 +1054,7 @@ template <int M, bool SL> static int stack_resident() {
 }
 
 template <int M, bool SL> static hipError_t launch_stack_mx(StackParams p, int max_cost, hipStream_t s) {
-    const int hw = stack_resident<M, SL>();
+    const int hw = stack_workgroups();
     if (!hw) return hipErrorUnknown;
     const uint64_t most = (uint64_t)(p.worker_cap ? p.worker_cap : max_workers_valu(M));
     // every share must be at least one tile long, so that each share between the first
@@ -1068,7 +1072,7 @@ template <int M, bool SL> static hipError_t launch_stack_mx(StackParams p, int m
     p.nworkers = (int)(spw * (uint64_t)p.nwaves);
     return launch((stack_kernel<M, SL>), dim3((unsigned)p.nwaves), dim3(64 * kWgWaves), 0, s, p);
 }
-// waves of the persistent launch by waves that the device keeps resident, in workgroups of four
+// waves that the device keeps resident of the kernel whose shares belong to waves, in workgroups of four
 template <int M, bool SL> static int wave_resident() {
     static int cached = 0;
     if (!cached) {
@@ -1086,7 +1090,7 @@ template <int M, bool SL> static hipError_t launch_stack_waves(StackParams p, in
     const int hw = wave_resident<M, SL>();
     if (!hw) return hipErrorUnknown;
     const uint64_t most = (uint64_t)(p.worker_cap ? p.worker_cap : max_workers_valu(M));
-    uint64_t cap = p.cost_total / (uint64_t)max_cost;  // (as below)
+    uint64_t cap = p.cost_total / (uint64_t)max_cost;  // (as above)
     if (cap > most) cap = most;
     if (cap < 1) cap = 1;
     p.nwaves = (int)(cap < (uint64_t)hw ? cap : (uint64_t)hw);

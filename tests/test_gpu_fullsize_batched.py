@@ -41,7 +41,7 @@ def test_llama3_70b_mlp_shapes_at_m64_m256_sampled_rows(shape):
 
 
 def test_llama3_70b_down_projection_small_batches_sampled_rows():
-    # the down-projection (224 groups: the longest split-K chains) on the vector-ALU and narrow matrix-core paths
+    # the down-projection (224 groups: the longest split-K chains) on the vector ALUs, by 4x4x4 and by 16x16x32 matrix instructions
     N, K = 8192, 28672
     L = synth.make_layer(N, K, M=16, seed=[54])
     rng = np.random.default_rng(55)

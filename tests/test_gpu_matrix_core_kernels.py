@@ -1,7 +1,7 @@
-"""The narrow and the wide kernel in the calls that they serve.  Most small shapes up to 128 rows go to the row kernels, so the shapes here are
-chosen by the rules of csrc/mq_routes.h: a single layer of 233 groups (eight K slices leave a wave eight tiles; its row blocks are finished by a
-launch of their own), a stack of 17 layers for the narrow kernel (more than a low-latency launch takes) and any stack above 16 rows for the wide one
-(row blocks finished by their last contributor)."""
+"""Matrix-core kernels in the calls that the low-latency launch does not take: the persistent launch of the row kernels at 9 .. 16 rows, the wide
+kernel above.  The shapes are chosen by the rules of csrc/mq_routes.h: a single layer of 233 groups (eight K slices leave a wave eight tiles; under
+the wide kernel its row blocks are finished by a launch of their own), a stack of 17 layers up to 16 rows (more than a low-latency launch takes) and
+any stack above (row blocks finished by their last contributor).  tests/test_routes.py holds that they take these ways."""
 import numpy as np
 import pytest
 
@@ -14,7 +14,7 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 LONG = 233 * 128
-# (kernel, M): one chunk of 16 columns; one to four chunks of 32
+# 16 columns; one to four chunks of 32
 BATCHES = (9, 16, 17, 64, 65, 128)
 ROUTES = ("single", "stack")
 
@@ -29,7 +29,7 @@ def _y(M, N, dtype):
 
 
 def _run(route, lay, x, dtype=torch.float16):
-    """y of `lay` from the narrow (up to 16 rows) or wide kernel: twice, the same bits, nothing written around it."""
+    """y of `lay` from the persistent launch of the row kernels (up to 16 rows) or the wide kernel: three times, the same bits, nothing written around it."""
     M, N, K, r = x.shape[0], lay["N"], lay["K"], lay["r"]
     buf, y = _y(M, N, dtype)
     if route == "single":
@@ -115,7 +115,7 @@ def test_bf16_activations_and_outputs(route, M):
 
 
 @pytest.mark.parametrize("M", (9, 16))
-def test_noalloc_narrow(M):
+def test_noalloc_9_to_16_rows(M):
     # few schedule shares (the array's room): row blocks of two and three contributors and of one
     N, K, r = 321, LONG, 3
     L = synth.make_layer(N, K, M=M, seed=[604, M])

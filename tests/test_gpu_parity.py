@@ -224,7 +224,7 @@ def test_linear_rejects_oversized_batch_loudly():
 
 
 # ------------------------------------------------------------------ batches of 5 rows and more
-# (single layers of these sizes go to the row kernels up to 128 rows; the narrow and the wide kernel: test_gpu_matrix_core_kernels.py)
+# (single layers of these sizes go to the row kernels up to 128 rows; the persistent launch and the wide kernel: test_gpu_matrix_core_kernels.py)
 @pytest.mark.parametrize("r", WIDTHS)
 @pytest.mark.parametrize("M", [5, 8, 16])
 def test_linear_5_to_16_rows(r, M):

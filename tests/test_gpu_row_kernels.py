@@ -1,5 +1,5 @@
-"""Batches where one kernel takes over from another, 2 .. 256 rows: the row kernels by 4x4x4 matrix instructions (built for 2, 3, 4, 8 and 16
-rows), the narrow kernel behind them, single layers, small stacks, stacks of more layers than travel with a launch, and bf16."""
+"""Batches where one kernel takes over from another, 2 .. 256 rows: the row kernels (built for 2, 3, 4, 8 and 16 rows; by 4x4x4 and from 5 rows on
+16x16x32 matrix instructions), single layers, small stacks, stacks of more layers than travel with a launch, and bf16."""
 import numpy as np
 import pytest
 
@@ -98,7 +98,7 @@ def _put(L, r, M):
     return dict(lay, x=dev(L["x"]), y=torch.full((M, N), float("nan"), dtype=torch.float16, device=DEV))
 
 
-# 3 layers: one launch in the low-latency shape; 17: the persistent row kernel up to 8 rows, the narrow kernel above
+# 3 layers: one launch in the low-latency shape; 17: the persistent launch (of waves' shares up to 8 rows, workgroups' above)
 @pytest.mark.parametrize("M", BATCHES)
 @pytest.mark.parametrize("n", [3, 17])
 def test_stacks(M, n):
@@ -147,7 +147,7 @@ def test_infinities_stay_in_their_batch_row(M):
 
 
 def test_layers_beyond_the_low_latency_shape_sampled_rows():
-    # 12 416 tiles: the persistent row kernel up to 8 rows, the narrow kernel above
+    # 12 416 tiles: the low-latency launch up to 8 rows, the persistent one above
     N, K = 12401, 8192
     L = synth.make_layer(N, K, M=16, seed=[505])
     rows = np.unique(np.concatenate([[0, 63, 64, N - 2, N - 1], np.random.default_rng(506).integers(0, N, 90)]))
@@ -163,7 +163,7 @@ def test_layers_beyond_the_low_latency_shape_sampled_rows():
 
 
 def test_two_bits_of_many_tiles_single_and_as_a_stack():
-    # 5 rows, 62 720 tiles: the narrow kernel as a single layer, a row kernel as a stack.  Products are exact in both; fp32 sums in another
+    # 5 rows, 62 720 tiles: as a single layer shares of workgroups, as a stack shares of waves.  Products are exact in both; fp32 sums in another
     # order change the fp16 rounding of few values, each by one spacing (2^-10), where all of them would be 4.9e-4 in the 2-norm
     N, K, r, M = 28672, 17920, 2, 5
     L = synth.make_layer_device(N, K, seed=515, device=DEV, want_x=False)
