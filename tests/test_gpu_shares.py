@@ -47,6 +47,25 @@ def test_shares(M, shape):
         assert torch.equal(outs[0][i], outs[1][i]) and torch.equal(outs[0][i], outs[2][i])   # fixed summation order
 
 
+# 238 and 240 tiles, a share each: grids that are not and that are a multiple of the eight dies
+def few_shares(tiles):
+    return [(64, 1792)] * 17 if tiles == 238 else [(64, 1792)] * 16 + [(60, 2048)]
+
+
+@pytest.mark.parametrize("tiles", (238, 240))
+@pytest.mark.parametrize("M", (1, 3, 8, 16))
+def test_fewer_shares_than_compute_units(M, tiles):
+    host = [synth.make_layer(N, K, M=M, seed=[604, i, M]) for i, (N, K) in enumerate(few_shares(tiles))]
+    layers = [dict(mq.prepare_layer(dev(L["parent"]), dev(L["scales"]), dev(L["zeros"]), 8), x=dev(L["x"]),
+                   y=torch.full((M, L["parent"].shape[0]), float("nan"), dtype=torch.float16, device=DEV)) for L in host]
+    plan = mq.mq_stack_plan(layers, M, device=DEV)
+    for _ in range(2):
+        mq.mq_linear_stack(plan)
+    torch.cuda.synchronize()
+    for i, (lay, L) in enumerate(zip(layers, host)):
+        check_layer(lay["y"], L, 8, f"layer {i} M={M}")
+
+
 # single layers whose 256 shares are whole row blocks, halves and eighths of one
 @pytest.mark.parametrize("N,K", [(16384, 1024), (16384, 4096), (4096, 4096), (2048, 8192)])
 @pytest.mark.parametrize("M", (9, 16))

@@ -6,7 +6,7 @@ import subprocess
 
 import pytest
 
-from test_gpu_shares import LONG, MANY, SMALL, WHOLE, stack_of
+from test_gpu_shares import LONG, MANY, SMALL, WHOLE, few_shares, stack_of
 from test_gpu_wave_shares import SINGLES, STACKS, _shapes
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -80,3 +80,8 @@ def test_calls_by_which_the_gpu_tests_reach_shares_of_workgroups(lib):
     for shape in (LONG, MANY, SMALL, WHOLE):
         for M in (1, 2, 4, 5, 8, 9, 16):
             assert not _waves(lib, *stack_of(shape, M), M), (shape, M)
+    for tiles in (238, 240):
+        shapes = few_shares(tiles)
+        assert sum(-(-N // 64) * (K // 128) for N, K in shapes) == tiles
+        for M in (1, 3, 8, 16):
+            assert not _waves(lib, shapes, [8] * 17, M), (tiles, M)
