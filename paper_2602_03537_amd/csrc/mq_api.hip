@@ -115,8 +115,8 @@ const _Float16 *sym_zero_line() {
 
 // xt: where the wide kernel keeps this layer's prepared activations (row kernels: the fp16 copy of bf16 activations)
 // sym_line: sym_zero_line() of the current device; needed (non-null) when the layer is symmetric
-// Mp: the batch that the workspace is laid out for (see stack_path_m); rows: the row kernels serve it
-LayerDesc make_desc(const mq_layer &l, int64_t M, int64_t Mp, bool rows, uint64_t cost_start, int cnt_off, int job_start, void *xt,
+// Mp: the batch that the workspace is laid out for (see stack_path_m); rows: the row kernels serve it; by_wave: with shares of waves, where it is the persistent launch
+LayerDesc make_desc(const mq_layer &l, int64_t M, int64_t Mp, bool rows, bool by_wave, uint64_t cost_start, int cnt_off, int job_start, void *xt,
                     const _Float16 *sym_line) {
     LayerDesc d{};
     d.Wp = static_cast<const uint4 *>(l.packed_W);
@@ -140,11 +140,11 @@ LayerDesc make_desc(const mq_layer &l, int64_t M, int64_t Mp, bool rows, uint64_
     d.G = (int32_t)(l.K / kGroup);
     d.RB = (int32_t)(pad_rows(l.N) / kRowBlock);
     d.r = l.r;
-    d.cost = valu_tile_cost(l.r, (int)M);  // replaced below for the other kernels
+    d.cost = valu_tile_cost(l.r, (int)M, by_wave);  // replaced below for the other kernels
     if (l.from_parent) {  // the tiles are those of the 8-bit parent; Eq. 1 to l.r bits happens in registers
         d.r = kC;
         d.rs = l.r;
-        d.cost = valu_tile_cost(kC, (int)M);
+        d.cost = valu_tile_cost(kC, (int)M, by_wave);
     }
     if (!rows) {  // scheduled in super-tiles of four row blocks
         d.RB = (d.RB + 3) / 4;
@@ -270,7 +270,7 @@ mq_status run_single(const mq_layer &l, int64_t M, void *ws, size_t ws_bytes, mq
     const _Float16 *sym_line = nullptr;
     if (!l.zeros_t && !(sym_line = sym_zero_line())) return MQ_ERR_HIP;
     p.by_wave = rows && wave_shares_single(l.from_parent ? kC : l.r, M);
-    p.single = make_desc(l, M, M, rows, 0, 0, 0, act, sym_line);
+    p.single = make_desc(l, M, M, rows, p.by_wave != 0, 0, 0, 0, act, sym_line);
     p.cost_total = (uint64_t)p.single.CB * p.single.RB * p.single.G * p.single.cost;
     p.cnt = reinterpret_cast<int32_t *>(base);
     p.part = reinterpret_cast<float *>(base + cnt_b);
@@ -560,7 +560,7 @@ mq_status mq_stack_plan(const mq_layer *layers, int n_layers, int64_t M, void *p
     for (int i = 0; i < n_layers; ++i) {
         const size_t xb = xt_bytes(Mp, layers[i].K, layers[i].r);
         if (!layers[i].zeros_t && !sym_line && !(sym_line = sym_zero_line())) return MQ_ERR_HIP;
-        table[i] = make_desc(layers[i], M, Mp, rows, cost, (int)counters, (int)jobs, xb ? base_dev + act : nullptr, sym_line);
+        table[i] = make_desc(layers[i], M, Mp, rows, by_wave, cost, (int)counters, (int)jobs, xb ? base_dev + act : nullptr, sym_line);
         act += xb;
         cost += (uint64_t)table[i].CB * table[i].RB * table[i].G * table[i].cost;
         counters += counters_of(Mp, layers[i].N);

@@ -23,7 +23,7 @@ extern "C" int stack_rows(int64_t M) { return row_kernels_stack(M); }
 extern "C" int stack_low_latency(int n, const int *RB, const int *G, int64_t M, size_t part_bytes) {
     return low_latency_stack(n, M, part_bytes, [&](int i) { return RowLayer{RB[i], G[i], 4}; });
 }
-extern "C" int tile_cost(int r, int M) { return valu_tile_cost(r, M); }
+extern "C" int tile_cost(int r, int M, int by_wave) { return valu_tile_cost(r, M, by_wave); }
 extern "C" void single_shape(int RB, int G, int M, int *out) {
     out[0] = pick_k_slices(RB, G, M);
     out[1] = quad_wave_tiles(G, out[0]);
@@ -179,9 +179,17 @@ def test_small_stacks_of_5_to_8_rows_take_the_faster_launch(lib, layers, low, pe
 # at M = 1 the costs are near the bytes, 3.4 times as many
 @pytest.mark.parametrize("M,least,most", [(1, 2.5, 3.4), (2, 1.5, 2.1), (3, 1.5, 2.1)])
 def test_cost_of_wide_tiles_in_mixed_stacks(lib, M, least, most):
-    assert least <= lib.tile_cost(8, M) / lib.tile_cost(2, M) <= most
-    costs = [lib.tile_cost(r, M) for r in (2, 3, 6, 8)]
-    assert costs == sorted(costs)
+    for by_wave in (0, 1):
+        assert least <= lib.tile_cost(8, M, by_wave) / lib.tile_cost(2, M, by_wave) <= most
+        costs = [lib.tile_cost(r, M, by_wave) for r in (2, 3, 6, 8)]
+        assert costs == sorted(costs)
+
+
+# shares of waves, three rows: 1.6 times as long at 8 bits, not 2.1
+def test_cost_of_wide_tiles_in_shares_of_waves_of_three_rows(lib):
+    assert lib.tile_cost(8, 3, 1) <= 1.7 * lib.tile_cost(2, 3, 1)
+    for M in (1, 2, 4, 5, 8, 9, 16):
+        assert all(lib.tile_cost(r, M, 1) == lib.tile_cost(r, M, 0) for r in (2, 3, 4, 6, 8))
 
 
 def test_row_shapes_hold_to_their_bounds(lib):
